@@ -125,12 +125,20 @@ __device__ inline void body_sum(const StepArgs& a, int beg, int end, double r, d
 }
 
 // The same sum in the integrate kernel, called by every lane of the wave.
-// A lane walks at most kSoloEntries entries of its row by itself; longer
-// rows (a large sphere among small ones has ~10x the entries of its
-// neighbours, and its lane would hold the whole wave) are finished by the
-// wave together, 64 entries at a time: each lane reads one entry and its
-// pair's record into the wave's slice of LDS, then the row's own lane adds
-// them in row order, with the same arithmetic as the walk.
+// Each lane first walks up to kSoloEntries entries of its row by itself, four
+// at a time.  What is left is finished in one of two ways, chosen again after
+// every batch: the lanes go on walking, four entries each at once, or the
+// wave takes the longest row, 64 entries per round (each lane reads one entry
+// and its pair's record into the wave's slice of LDS, then the row's own lane
+// adds them in row order, with the same arithmetic as the walk).  A batch and
+// a round cost about one dependent pair of loads each, so the wave walks on
+// while the longest row left needs no more batches than there are rows left
+// (one round each), and shares the work where a few rows are much longer
+// than the rest (a large sphere among small ones has ~10x their entries).
+// Sharing every row past 12 entries instead took one round per lane where
+// all rows are a little longer: 32,000 dense equal spheres with 18 candidates
+// each took 75 us per launch that way (150 steps from a new state, everything
+// included: 17.1 -> 7.3 ms); 8 M spheres of two sizes are as fast either way.
 constexpr int kSoloEntries = 12;
 constexpr int kCoopWords = 64 * (kForceWords + 1);  // doubles per wave: 64 entries x 6, then 64 entry words
 template <int PREC, bool FREC>
@@ -139,15 +147,26 @@ __device__ inline void body_sum_wave(const StepArgs& a, int beg, int end, double
 {
     F[0] = F[1] = F[2] = 0.0;
     T[0] = T[1] = T[2] = 0.0;
-    const int solo = min(end, beg + kSoloEntries);
-    row_walk<PREC, FREC>(a, beg, solo, r, F, T);
+    int next = min(end, beg + kSoloEntries);
+    row_walk<PREC, FREC>(a, beg, next, r, F, T);
+    if (__ballot(next < end) == 0ull) return;
+    auto longest_left = [&]() {
+        int v = end - next;
+        for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, 64));
+        return v;
+    };
+    int longest = longest_left();
     const int lane = threadIdx.x & 63;
     uint32_t* lu = reinterpret_cast<uint32_t*>(lds + 64 * kForceWords);
-    int next = solo;
-    for (;;) {
-        const unsigned long long need = __ballot(next < end);
-        if (need == 0ull) break;
-        const int src = __builtin_ctzll(need);
+    while (longest > 0) {
+        if (longest <= 4 * (int)__popcll(__ballot(next < end))) {
+            const int stop = min(end, next + 4);
+            row_walk<PREC, FREC>(a, next, stop, r, F, T);
+            next = stop;
+            longest -= 4;
+            continue;
+        }
+        const int src = __builtin_ctzll(__ballot(end - next == longest));
         const int c0 = __shfl(next, src, 64), c1 = __shfl(end, src, 64);
         const int e = c0 + lane;
         uint32_t u = 0u;
@@ -177,6 +196,7 @@ __device__ inline void body_sum_wave(const StepArgs& a, int beg, int end, double
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_wave_barrier();
+        longest = longest_left();
     }
 }
 
