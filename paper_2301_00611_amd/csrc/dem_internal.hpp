@@ -543,6 +543,36 @@ void launch_cell_update(const StepArgs* args, int parity, hipStream_t st);
 void launch_max_account(const Bodies& b, int n, unsigned long long* out, hipStream_t st);
 // first reduction level of the controller's partial sums (update steps only)
 void launch_ctrl_reduce(const StepArgs* args, int parity, hipStream_t st);
+
+// state.hip
+// Bodies [first, first + count) of one scene: body `first + i` is gid
+// gids[first + i] (gids null: itself), slot_of_id gives its slot, or -1 - w
+// for boundary w.  All pointers are device memory; a null output or input is
+// left alone; slot_force3 / slot_torque3 null: zero forces.
+struct StateArgs {
+    Bodies bod;
+    const Wall* walls;
+    const int32_t* slot_of_id;
+    const int32_t* gids;
+    int32_t first, count;
+    const double* slot_force3;
+    const double* slot_torque3;
+};
+struct StateOut {
+    double *pos3, *vel3, *angvel3, *ori4, *force3, *torque3;
+};
+struct StateIn {
+    const double *pos3, *vel3, *angvel3, *ori4;
+};
+void launch_gather_state(const StateArgs& a, const StateOut& o, hipStream_t st);
+void launch_scatter_state(const StateArgs& a, const StateIn& in, hipStream_t st);
+// boundary pairs that touched at the last step: flags (npairs + 1), then,
+// after an exclusive scan of them, boundary index and force on the sphere
+// (from launch_pair_forces), 4 doubles per flagged pair in pair order
+void launch_wall_flags(const StepArgs& a, int precision, uint32_t* flag, hipStream_t st);
+void launch_wall_pack(const StepArgs& a, const uint32_t* flag, const uint32_t* scan, const double* f3, double* out,
+                      hipStream_t st);
+
 void launch_body_forces(const StepArgs& a, int precision, double* f3, double* t3, hipStream_t st);
 // Sums over the last step's real contacts, kNetworkWords doubles per block
 // (stress.hip): Love-Weber stress (9), modulus of the normal springs per

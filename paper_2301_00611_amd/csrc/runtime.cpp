@@ -204,6 +204,7 @@ struct HostMaterial {
 struct HostScene {
     dem_params p;
     std::vector<int32_t> gids;  // local id -> gid
+    size_t gid_at = 0;          // where its gids start in the device table (batches)
     int64_t n_spheres = 0, n_walls = 0;
     int64_t iter = 0;
     double time = 0.0;
@@ -255,6 +256,9 @@ struct World {
     std::vector<HostBody> bodies;      // by gid (authoritative only while host_dirty)
     bool host_dirty = false;           // bodies added / state set: upload before stepping
     bool on_device = false;            // device arrays hold the current state
+    // the state was set on the device since the last broad-phase run: what
+    // the last step's contacts gave (forces, contact list) no longer applies
+    bool state_set = false;
     bool need_rebuild = true;
     bool contacts_valid = false;
 
@@ -267,7 +271,7 @@ struct World {
     int nslots = 0;
     int ngids_dev = 0;                 // number of gids the device arrays were built for
     int old_ngids = 0;                 // gids covered by the active own arrays
-    DBuf slot_of_id, keys, vals, keys_alt, vals_alt, cell_start, cell_end, counts, row_start;
+    DBuf slot_of_id, d_gids, d_state, keys, vals, keys_alt, vals_alt, cell_start, cell_end, counts, row_start;
     DBuf ent_slot, ent_pid, ent_cell, ent_own, own_scan, rows_ent, scan_tmp, radix_tmp;
     DBuf d_ve;
     DBuf d_scenes, d_walls, d_mats, d_tanphi, d_ctr, d_part_c, d_part_i, d_bounds, d_total, d_tmp3, d_args;
@@ -334,7 +338,7 @@ struct World {
         graphs.clear();
         for (auto& b : bs) b.release();
         for (auto& p : ps) p.release();
-        for (DBuf* d : {&slot_of_id, &keys, &vals, &keys_alt, &vals_alt, &cell_start, &cell_end, &counts, &row_start,
+        for (DBuf* d : {&slot_of_id, &d_gids, &d_state, &keys, &vals, &keys_alt, &vals_alt, &cell_start, &cell_end, &counts, &row_start,
                         &ent_slot, &ent_pid, &ent_cell, &ent_own, &own_scan, &rows_ent, &scan_tmp, &radix_tmp,
                         &d_scenes, &d_walls, &d_mats, &d_tanphi, &d_ctr, &d_part_c, &d_part_i, &d_bounds, &d_total,
                         &d_tmp3, &d_args, &d_ctrl_cfg, &d_ctrl_state, &d_acc_ctrl, &d_acc_ctrl2, &pb_ca, &pb_cb, &pb_found,
@@ -751,7 +755,20 @@ struct World {
         slot_of_id.ensure(4 * (size_t)std::max(ng, 1));
         std::vector<int32_t> sl((size_t)std::max(ng, 1), -1);
         for (int i = 0; i < nslots; ++i) sl[sph[i]] = i;
+        for (int i = 0; i < (int)walls.size(); ++i) sl[walls[i].id] = -1 - i;
         HIPC(hipMemcpyAsync(slot_of_id.p, sl.data(), 4 * (size_t)ng, hipMemcpyHostToDevice, stream));
+        // a batch's scenes: their gids one after another (a single scene's ids are its gids)
+        std::vector<int32_t> gid_table;
+        if (batched()) {
+            gid_table.reserve(bodies.size());
+            for (HostScene& S : scenes) {
+                S.gid_at = gid_table.size();
+                gid_table.insert(gid_table.end(), S.gids.begin(), S.gids.end());
+            }
+            d_gids.ensure(4 * std::max<size_t>(gid_table.size(), 1));
+            if (!gid_table.empty())
+                HIPC(hipMemcpyAsync(d_gids.p, gid_table.data(), 4 * gid_table.size(), hipMemcpyHostToDevice, stream));
+        }
         // walls, scene table wall ranges
         d_walls.ensure(sizeof(Wall) * std::max<size_t>(walls.size(), 1));
         if (!walls.empty())
@@ -778,6 +795,7 @@ struct World {
         }
         ngids_dev = ng;
         host_dirty = false;
+        state_set = false;
         on_device = true;
         need_rebuild = true;
         invalidate_graphs();
@@ -1174,6 +1192,7 @@ struct World {
         HIPC(hipStreamSynchronize(stream));
         upload_args();
         need_rebuild = false;
+        state_set = false;
         ++rebuilds;
         iter_at_rebuild = scenes[0].iter;
         // the run ends with a synchronisation: its wall time is its cost
@@ -1849,77 +1868,143 @@ struct World {
             }
             return;
         }
-        Snapshot sn = snapshot();
-        std::vector<double> f, t;
-        std::vector<double> wallF(3 * walls.size(), 0.0);
-        if (force3 || torque3) {
-            f.assign(3 * (size_t)nslots, 0.0);
-            t.assign(3 * (size_t)nslots, 0.0);
-            if (nslots > 0 && contacts_valid) {
-                d_tmp3.ensure(sizeof(double) * 6 * (size_t)nslots);
-                StepArgs a = step_args();
-                launch_body_forces(a, precision, d_tmp3.as<double>(), d_tmp3.as<double>() + 3 * (size_t)nslots, stream);
+        // the device puts a range of bodies in id order, at most
+        // kStateChunk at a time through one scratch buffer
+        const bool forces = (force3 || torque3) && nslots > 0 && contacts_valid && !state_set;
+        std::vector<double> wallF;
+        StateArgs g = state_args(s, first);
+        if (forces) {
+            if (S.n_walls > 0) wallF = wall_reactions();
+            d_tmp3.ensure(sizeof(double) * 6 * (size_t)nslots);
+            double* const f3 = d_tmp3.as<double>();
+            launch_body_forces(step_args(), precision, f3, f3 + 3 * (size_t)nslots, stream);
+            g.slot_force3 = f3;
+            g.slot_torque3 = f3 + 3 * (size_t)nslots;
+        }
+        double* const dst[6] = {pos3, vel3, angvel3, ori4, force3, torque3};
+        for (int64_t at = 0; at < count; at += kStateChunk) {
+            const int64_t n = std::min(count - at, kStateChunk);
+            d_state.ensure(sizeof(double) * 19 * (size_t)n);
+            double* src[6];
+            g.first = (int32_t)(first + at);
+            g.count = (int32_t)n;
+            const StateOut o = scratch_out(d_state.as<double>(), n, dst, src);
+            launch_gather_state(g, o, stream);
+            HIPC(hipGetLastError());
+            for (int k = 0; k < 6; ++k)
+                if (dst[k])
+                    HIPC(hipMemcpyAsync(dst[k] + kStateWords[k] * at, src[k], 8 * kStateWords[k] * (size_t)n,
+                                        hipMemcpyDeviceToHost, stream));
+        }
+        HIPC(hipStreamSynchronize(stream));
+        if (force3 && !wallF.empty())
+            for (int64_t i = 0; i < count; ++i) {
+                const HostBody& b = bodies[S.gids[first + i]];
+                if (b.kind == 1)
+                    for (int k = 0; k < 3; ++k) force3[3 * i + k] = wallF[3 * b.wall + k];
+            }
+    }
+
+    // dem_get_state_device: straight into the caller's buffers where the
+    // device can write them, else through the scratch buffer and a copy.
+    void get_state_device(int s, int64_t first, int64_t count, double* pos3, double* vel3, double* angvel3,
+                          double* ori4)
+    {
+        double* const dst[6] = {pos3, vel3, angvel3, ori4, nullptr, nullptr};
+        StateArgs g = state_args(s, first);
+        bool direct = true;
+        for (int k = 0; k < 4; ++k)
+            if (dst[k] && !device_writable(dst[k], 8 * kStateWords[k] * (size_t)count)) direct = false;
+        if (direct) {
+            g.count = (int32_t)count;
+            launch_gather_state(g, StateOut{pos3, vel3, angvel3, ori4, nullptr, nullptr}, stream);
+            HIPC(hipGetLastError());
+        } else {
+            for (int64_t at = 0; at < count; at += kStateChunk) {
+                const int64_t n = std::min(count - at, kStateChunk);
+                d_state.ensure(sizeof(double) * 13 * (size_t)n);
+                double* src[6];
+                g.first = (int32_t)(first + at);
+                g.count = (int32_t)n;
+                const StateOut o = scratch_out(d_state.as<double>(), n, dst, src);
+                launch_gather_state(g, o, stream);
                 HIPC(hipGetLastError());
-                HIPC(hipMemcpyAsync(f.data(), d_tmp3.p, 8 * 3 * (size_t)nslots, hipMemcpyDeviceToHost, stream));
-                HIPC(hipMemcpyAsync(t.data(), d_tmp3.as<double>() + 3 * (size_t)nslots, 8 * 3 * (size_t)nslots,
-                                    hipMemcpyDeviceToHost, stream));
-                HIPC(hipStreamSynchronize(stream));
-                // reaction on walls: minus the force on the sphere, in pair order
-                PairSnapshot p = pair_snapshot();
-                for (int k = 0; k < npairs; ++k)
-                    if (p.a[k] < 0 && (p.nx[k] != 0.0 || p.ny[k] != 0.0 || p.nz[k] != 0.0)) {
-                        const int w = -1 - p.a[k];
-                        wallF[3 * w + 0] += -p.fx[k];
-                        wallF[3 * w + 1] += -p.fy[k];
-                        wallF[3 * w + 2] += -p.fz[k];
-                    }
+                for (int k = 0; k < 4; ++k)
+                    if (dst[k])
+                        HIPC(hipMemcpyAsync(dst[k] + kStateWords[k] * at, src[k], 8 * kStateWords[k] * (size_t)n,
+                                            hipMemcpyDefault, stream));
             }
         }
-        for (int64_t i = 0; i < count; ++i) {
-            const int32_t g = S.gids[first + i];
-            const HostBody& b = bodies[g];
-            if (b.kind == 1) {
-                const Wall& W = walls[b.wall];
-                for (int k = 0; k < 3; ++k) {
-                    if (pos3) pos3[3 * i + k] = boundary_position(W, k);
-                    if (vel3) vel3[3 * i + k] = 0.0;
-                    if (angvel3) angvel3[3 * i + k] = 0.0;
-                    if (force3) force3[3 * i + k] = wallF[3 * b.wall + k];
-                    if (torque3) torque3[3 * i + k] = 0.0;
-                }
-                if (ori4) {
-                    ori4[4 * i] = 1.0;
-                    ori4[4 * i + 1] = ori4[4 * i + 2] = ori4[4 * i + 3] = 0.0;
-                }
-                continue;
-            }
-            const int sl = sn.slot_of[g];
-            if (pos3) {
-                pos3[3 * i] = sn.x[sl];
-                pos3[3 * i + 1] = sn.y[sl];
-                pos3[3 * i + 2] = sn.z[sl];
-            }
-            if (vel3) {
-                vel3[3 * i] = sn.vx[sl];
-                vel3[3 * i + 1] = sn.vy[sl];
-                vel3[3 * i + 2] = sn.vz[sl];
-            }
-            if (angvel3) {
-                angvel3[3 * i] = sn.wx[sl];
-                angvel3[3 * i + 1] = sn.wy[sl];
-                angvel3[3 * i + 2] = sn.wz[sl];
-            }
-            if (ori4) {
-                ori4[4 * i] = sn.qw[sl];
-                ori4[4 * i + 1] = sn.qx[sl];
-                ori4[4 * i + 2] = sn.qy[sl];
-                ori4[4 * i + 3] = sn.qz[sl];
-            }
-            for (int k = 0; k < 3; ++k) {
-                if (force3) force3[3 * i + k] = f[3 * (size_t)sl + k];
-                if (torque3) torque3[3 * i + k] = t[3 * (size_t)sl + k];
-            }
+        HIPC(hipStreamSynchronize(stream));
+    }
+
+    // doubles per body of pos, vel, angvel, ori, force, torque
+    static constexpr size_t kStateWords[6] = {3, 3, 3, 4, 3, 3};
+    static constexpr int64_t kStateChunk = 1 << 20;  // 159 MB of scratch
+    StateArgs state_args(int s, int64_t first) const
+    {
+        StateArgs g{};
+        g.bod = bs[active].view();
+        g.walls = d_walls.as<Wall>();
+        g.slot_of_id = slot_of_id.as<int32_t>();
+        g.gids = batched() ? d_gids.as<int32_t>() + scenes[s].gid_at : nullptr;
+        g.first = (int32_t)first;
+        return g;
+    }
+    // the wanted arrays one after another in `base`
+    static StateOut scratch_out(double* base, int64_t n, double* const* dst, double** src)
+    {
+        for (int k = 0; k < 6; ++k) {
+            src[k] = dst[k] ? base : nullptr;
+            if (dst[k]) base += kStateWords[k] * (size_t)n;
         }
+        return StateOut{src[0], src[1], src[2], src[3], src[4], src[5]};
+    }
+    // a buffer of this device's own memory that holds `bytes` from p on
+    bool device_writable(const void* p, size_t bytes) const
+    {
+        hipPointerAttribute_t at;
+        hipDeviceptr_t base = nullptr;
+        size_t size = 0;
+        if (reinterpret_cast<uintptr_t>(p) % 8 != 0 || hipPointerGetAttributes(&at, p) != hipSuccess ||
+            at.type != hipMemoryTypeDevice || at.device != device ||
+            hipMemGetAddressRange(&base, &size, const_cast<void*>(p)) != hipSuccess) {
+            (void)hipGetLastError();  // not a failure: the copy takes such a pointer
+            return false;
+        }
+        return static_cast<const char*>(p) + bytes <= static_cast<const char*>(base) + size;
+    }
+    // Reaction on every boundary: minus the force on each sphere that
+    // touched it at the last step, added in pair order.
+    std::vector<double> wall_reactions()
+    {
+        std::vector<double> wallF(3 * walls.size(), 0.0);
+        if (npairs <= 0) return wallF;
+        const size_t np = (size_t)npairs;
+        const StepArgs a = step_args();
+        // the pair build's scratch is free between broad-phase runs
+        pb_flag.ensure(4 * (np + 1));
+        pb_scan.ensure(4 * (np + 1));
+        scan_tmp.ensure(scan_temp_bytes(npairs + 1));
+        d_total.ensure(16);
+        launch_wall_flags(a, precision, pb_flag.as<uint32_t>(), stream);
+        exclusive_scan_u32(pb_flag.as<uint32_t>(), pb_scan.as<uint32_t>(), npairs + 1, scan_tmp.p,
+                           d_total.as<uint32_t>(), stream);
+        uint32_t n = 0;
+        HIPC(hipMemcpyAsync(&n, d_total.p, 4, hipMemcpyDeviceToHost, stream));
+        HIPC(hipStreamSynchronize(stream));
+        if (!n) return wallF;
+        d_tmp3.ensure(sizeof(double) * (3 * np + 4 * (size_t)n));
+        double* const f3 = d_tmp3.as<double>();
+        launch_pair_forces(a, precision, f3, stream);
+        launch_wall_pack(a, pb_flag.as<uint32_t>(), pb_scan.as<uint32_t>(), f3, f3 + 3 * np, stream);
+        HIPC(hipGetLastError());
+        std::vector<double> rec(4 * (size_t)n);
+        HIPC(hipMemcpyAsync(rec.data(), f3 + 3 * np, 8 * rec.size(), hipMemcpyDeviceToHost, stream));
+        HIPC(hipStreamSynchronize(stream));
+        for (uint32_t i = 0; i < n; ++i)
+            for (int k = 0; k < 3; ++k) wallF[3 * (size_t)rec[4 * i] + k] += -rec[4 * i + 1 + k];
+        return wallF;
     }
 
     void set_state(int s, const double* pos3, const double* vel3, const double* angvel3, const double* ori4)
@@ -1929,6 +2014,34 @@ struct World {
             if ((pos3 && !std::isfinite(pos3[i])) || (vel3 && !std::isfinite(vel3[i])) ||
                 (angvel3 && !std::isfinite(angvel3[i])))
                 fail(DEM_EINVAL, "dem_set_state: non-finite value");
+        if (on_device && !host_dirty) {
+            // the device arrays are the current state: the given components
+            // replace theirs in place
+            const double* const src[4] = {pos3, vel3, angvel3, ori4};
+            StateArgs g = state_args(s, 0);
+            const int64_t total = (int64_t)S.gids.size();
+            for (int64_t at = 0; at < total; at += kStateChunk) {
+                const int64_t n = std::min(total - at, kStateChunk);
+                d_state.ensure(sizeof(double) * 13 * (size_t)n);
+                double* p = d_state.as<double>();
+                const double* in[4];
+                for (int k = 0; k < 4; ++k) {
+                    in[k] = src[k] ? p : nullptr;
+                    if (!src[k]) continue;
+                    HIPC(hipMemcpyAsync(p, src[k] + kStateWords[k] * at, 8 * kStateWords[k] * (size_t)n,
+                                        hipMemcpyHostToDevice, stream));
+                    p += kStateWords[k] * (size_t)n;
+                }
+                g.first = (int32_t)at;
+                g.count = (int32_t)n;
+                launch_scatter_state(g, StateIn{in[0], in[1], in[2], in[3]}, stream);
+                HIPC(hipGetLastError());
+            }
+            HIPC(hipStreamSynchronize(stream));  // the caller's arrays are free again
+            state_set = true;
+            need_rebuild = true;
+            return;
+        }
         pull_bodies();
         for (size_t i = 0; i < S.gids.size(); ++i) {
             HostBody& b = bodies[S.gids[i]];
@@ -2198,7 +2311,7 @@ struct World {
     // or a state set since the last step are refused rather than uploaded).
     void stress_noalloc(int s, double volume, double* out9)
     {
-        if (host_dirty)
+        if (host_dirty || state_set)
             fail(DEM_EINVAL, "dem_get_stress_noalloc: bodies or state changed since the last step; step first");
         double V = volume;
         if (!(V > 0.0)) {
@@ -2227,7 +2340,7 @@ struct World {
     std::vector<dem_contact> contacts(int s)
     {
         std::vector<dem_contact> out;
-        if (!contacts_valid || host_dirty || npairs == 0) return out;
+        if (!contacts_valid || host_dirty || state_set || npairs == 0) return out;
         Snapshot sn = snapshot();
         PairSnapshot p = pair_snapshot();
         const std::vector<int64_t> loc = local_ids();
@@ -2741,6 +2854,10 @@ dem_status dem_get_state_device(dem_scene* s, int64_t first_id, int64_t count, d
     return guarded([&] {
         dem::World* w = world_of(s);
         w->check_scene_id(s->s, first_id, count);
+        if (w->on_device && !w->host_dirty) {
+            w->get_state_device(s->s, first_id, count, pos3, vel3, angvel3, ori4);
+            return;
+        }
         std::vector<double> p(pos3 ? 3 * count : 0), v(vel3 ? 3 * count : 0), a(angvel3 ? 3 * count : 0),
             q(ori4 ? 4 * count : 0);
         w->get_state(s->s, first_id, count, pos3 ? p.data() : nullptr, vel3 ? v.data() : nullptr,
