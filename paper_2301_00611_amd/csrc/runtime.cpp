@@ -928,6 +928,35 @@ struct World {
                 P.origin2[k] = 0.0;
                 P.cellw2[k] = hmax;
             }
+            // Two levels only where they are estimated to save work, in tests
+            // of one sphere against another: a group of three neighbour cells
+            // costs about four tests (its two dependent range reads), a cell
+            // holds its volume times the mean density, and a sphere of level 1
+            // takes a wave of 64 lanes for at least six tests' time.  A loose
+            // column of radii 0.5 to 1.5 mm, three quarters of which fall on
+            // level 1, is searched faster on one level (200,000 spheres,
+            // 1,000 steps with about 10 runs: 33.2 ms on two levels, 25.3 on
+            // one); 8 M dense spheres of 0.5 and 2 mm would test 18 times as
+            // many pairs on one.
+            if (rs > 0.0) {
+                double vol = 1.0;
+                if (periodic) {
+                    const double* H = P.H;
+                    vol = std::fabs(H[0] * (H[4] * H[8] - H[5] * H[7]) - H[1] * (H[3] * H[8] - H[5] * H[6]) +
+                                    H[2] * (H[3] * H[7] - H[4] * H[6]));
+                } else {
+                    for (int k = 0; k < 3; ++k) vol *= std::max(bnd[6 * s + 3 + k] - bnd[6 * s + k], hmax);
+                }
+                const double n = (double)scenes[s].n_spheres, nl = (double)scenes[s].n_large;
+                const double h0 = 2.0 * rs + dl2, group = 4.0;
+                const double fine = h0 * h0 * h0 * n / vol, coarse = hmax * hmax * hmax * nl / vol;
+                const double plain = 9.0 * group + 27.0 * hmax * hmax * hmax * n / vol;
+                const double w = 2.0 * std::ceil((rmax[s] + rs + dl2) / h0) + 1.0;
+                const double on0 = 18.0 * group + 27.0 * (fine + coarse);
+                const double on1 = std::max(64.0 * 6.0, w * w * std::ceil(w / 3.0) * group + 9.0 * group +
+                                                            w * w * w * fine + 27.0 * coarse);
+                if (n * plain <= (n - nl) * on0 + nl * on1) rs = 0.0;
+            }
             if (rs > 0.0) {
                 // level 0 (radii <= r_split) and level 1 (the others)
                 const double h0 = (2.0 * rs + dl2) * (1.0 + 1e-9);
