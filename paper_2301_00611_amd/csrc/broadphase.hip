@@ -1,14 +1,16 @@
 // broadphase.hip -- the collider's role (section 2.1.1, InsertionSortCollider)
 // rebuilt for the GPU: bodies are binned in cells no smaller than the largest
-// candidate distance (2 r_max + 2 Delta L), sorted by the Morton code of their
-// cell, and each body sweeps the 27 cells around its own for candidates whose
-// enlarged spheres overlap (distance < r_i + r_j + 2 Delta L).  The run is
+// candidate distance (2 r_max + 2 Delta L), put in cell order by a counting
+// sort (cells are numbered along Morton bricks, bodies of a cell by id), and
+// each body sweeps the 27 cells around its own for candidates whose enlarged
+// spheres overlap (distance < r_i + r_j + 2 Delta L).  The run is
 // needed only when some body may have moved farther than Delta L since the
 // last one (eq. 2.3-2.4).  Candidate pairs are stored once (owner = #1 of the
 // contact); every body keeps a row of its candidate pairs sorted by partner
 // id, and the shear history of surviving pairs is carried over by id.
 #include "dem_internal.hpp"
 
+#include <algorithm>
 #include <cfloat>
 
 namespace dem {
@@ -16,33 +18,16 @@ namespace dem {
 namespace {
 
 constexpr int kBlock = 256;
-constexpr uint32_t kEmpty = 0xffffffffu;
 
-__device__ inline uint64_t spread3(uint64_t v)
+// the low 10 bits of v, two zero bits after each
+__device__ inline uint32_t spread3(uint32_t v)
 {
-    v &= 0x1fffffull;
-    v = (v | (v << 32)) & 0x1f00000000ffffull;
-    v = (v | (v << 16)) & 0x1f0000ff0000ffull;
-    v = (v | (v << 8)) & 0x100f00f00f00f00full;
-    v = (v | (v << 4)) & 0x10c30c30c30c30c3ull;
-    v = (v | (v << 2)) & 0x1249249249249249ull;
+    v &= 0x3ffu;
+    v = (v | (v << 16)) & 0x030000ffu;
+    v = (v | (v << 8)) & 0x0300f00fu;
+    v = (v | (v << 4)) & 0x030c30c3u;
+    v = (v | (v << 2)) & 0x09249249u;
     return v;
-}
-
-__device__ inline uint32_t compact3(uint64_t v)
-{
-    v &= 0x1249249249249249ull;
-    v = (v ^ (v >> 2)) & 0x10c30c30c30c30c3ull;
-    v = (v ^ (v >> 4)) & 0x100f00f00f00f00full;
-    v = (v ^ (v >> 8)) & 0x1f0000ff0000ffull;
-    v = (v ^ (v >> 16)) & 0x1f00000000ffffull;
-    v = (v ^ (v >> 32)) & 0x1fffffull;
-    return (uint32_t)v;
-}
-
-__device__ inline uint64_t morton3(int x, int y, int z)
-{
-    return spread3((uint64_t)x) | (spread3((uint64_t)y) << 1) | (spread3((uint64_t)z) << 2);
 }
 
 __device__ inline int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
@@ -76,11 +61,27 @@ struct Level {
     const double* cellw;
     const int32_t* dims;
     int32_t offset;
+    int32_t bits;
 };
 __device__ inline Level level_of(const SceneParams& P, int lv)
 {
-    return lv == 0 ? Level{P.origin, P.inv_h, P.cellw, P.dims, P.cell_offset}
-                   : Level{P.origin2, P.inv_h2, P.cellw2, P.dims2, P.cell_offset2};
+    return lv == 0 ? Level{P.origin, P.inv_h, P.cellw, P.dims, P.cell_offset, P.brick_bits}
+                   : Level{P.origin2, P.inv_h2, P.cellw2, P.dims2, P.cell_offset2, P.brick_bits2};
+}
+// A cell's number: bricks of 2^bits cells a side, x fastest, Morton order
+// inside (the host picks the largest bricks that pad the grid little: see
+// brick_bits).  The part of y and z and the part of x add up.
+__device__ inline uint32_t cell_index_yz(const Level& V, int y, int z)
+{
+    const int m = V.bits, mask = (1 << m) - 1;
+    const uint32_t hx = (uint32_t)(V.dims[0] + mask) >> m, hy = (uint32_t)(V.dims[1] + mask) >> m;
+    const uint32_t brick = (((uint32_t)z >> m) * hy + ((uint32_t)y >> m)) * hx;
+    return (uint32_t)V.offset + (brick << (3 * m)) + (spread3(y & mask) << 1) + (spread3(z & mask) << 2);
+}
+__device__ inline uint32_t cell_index_x(const Level& V, int x)
+{
+    const int m = V.bits, mask = (1 << m) - 1;
+    return (((uint32_t)x >> m) << (3 * m)) + spread3(x & mask);
 }
 // the level a sphere of radius r is binned on
 __device__ inline int level_of_radius(const SceneParams& P, double r) { return (P.r_split > 0.0 && r > P.r_split) ? 1 : 0; }
@@ -147,21 +148,14 @@ __global__ void __launch_bounds__(kBlock) k_bounds(Bodies b, int nslots, int bat
     }
 }
 
-// Single scene: block maxima of the six ordered values, then one block
-// combines them (no contended atomics).
-__global__ void __launch_bounds__(kBlock) k_bounds_block(Bodies b, int nslots, unsigned long long* __restrict__ part)
+__device__ inline double unord_bits(unsigned long long v)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    unsigned long long v[6] = {0ull, 0ull, 0ull, 0ull, 0ull, 0ull};
-    if (i < nslots) {
-        const double4 p = b.xr[i];
-        v[0] = ~ord_bits(p.x);
-        v[1] = ~ord_bits(p.y);
-        v[2] = ~ord_bits(p.z);
-        v[3] = ord_bits(p.x);
-        v[4] = ord_bits(p.y);
-        v[5] = ord_bits(p.z);
-    }
+    return __longlong_as_double((long long)((v & 0x8000000000000000ull) ? (v & 0x7fffffffffffffffull) : ~v));
+}
+
+// Block maximum of the six ordered values; the first six threads get it.
+__device__ inline unsigned long long bounds_block_max(unsigned long long* v)
+{
     for (int k = 0; k < 6; ++k)
         for (int off = 32; off > 0; off >>= 1) {
             const unsigned long long o = __shfl_xor(v[k], off, 64);
@@ -172,15 +166,45 @@ __global__ void __launch_bounds__(kBlock) k_bounds_block(Bodies b, int nslots, u
     if (lane == 0)
         for (int k = 0; k < 6; ++k) s[wave][k] = v[k];
     __syncthreads();
-    if (threadIdx.x < 6) {
-        unsigned long long m = 0ull;
+    unsigned long long m = 0ull;
+    if (threadIdx.x < 6)
         for (int w = 0; w < kBlock / 64; ++w) m = s[w][threadIdx.x] > m ? s[w][threadIdx.x] : m;
-        part[(long)blockIdx.x * 6 + threadIdx.x] = m;
+    return m;
+}
+
+// the six words as doubles: lower corner (stored complemented), upper corner
+__device__ inline void bounds_store(unsigned long long m, double* __restrict__ out)
+{
+    if (threadIdx.x < 6) out[threadIdx.x] = unord_bits(threadIdx.x < 3 ? ~m : m);
+}
+
+// Single scene: block maxima of the six ordered values, then one block
+// combines them (no contended atomics); a scene that one block covers is
+// done in one launch.
+constexpr int kBoundsBlocks = 512;
+
+__global__ void __launch_bounds__(kBlock) k_bounds_block(Bodies b, int nslots, unsigned long long* __restrict__ part,
+                                                         double* __restrict__ out)
+{
+    unsigned long long v[6] = {0ull, 0ull, 0ull, 0ull, 0ull, 0ull};
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nslots; i += gridDim.x * blockDim.x) {
+        const double4 p = b.xr[i];
+        const double x[3] = {p.x, p.y, p.z};
+        for (int k = 0; k < 3; ++k) {
+            const unsigned long long u = ord_bits(x[k]);
+            v[k] = ~u > v[k] ? ~u : v[k];
+            v[3 + k] = u > v[3 + k] ? u : v[3 + k];
+        }
     }
+    const unsigned long long m = bounds_block_max(v);
+    if (gridDim.x == 1)
+        bounds_store(m, out);
+    else if (threadIdx.x < 6)
+        part[(long)blockIdx.x * 6 + threadIdx.x] = m;
 }
 
 __global__ void __launch_bounds__(kBlock) k_bounds_final(const unsigned long long* __restrict__ part, int nblk,
-                                                         unsigned long long* __restrict__ out)
+                                                         double* __restrict__ out)
 {
     unsigned long long v[6] = {0ull, 0ull, 0ull, 0ull, 0ull, 0ull};
     for (int b = threadIdx.x; b < nblk; b += blockDim.x)
@@ -188,51 +212,45 @@ __global__ void __launch_bounds__(kBlock) k_bounds_final(const unsigned long lon
             const unsigned long long o = part[(long)b * 6 + k];
             v[k] = o > v[k] ? o : v[k];
         }
-    for (int k = 0; k < 6; ++k)
-        for (int off = 32; off > 0; off >>= 1) {
-            const unsigned long long o = __shfl_xor(v[k], off, 64);
-            v[k] = o > v[k] ? o : v[k];
-        }
-    __shared__ unsigned long long s[kBlock / 64][6];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane == 0)
-        for (int k = 0; k < 6; ++k) s[wave][k] = v[k];
-    __syncthreads();
-    if (threadIdx.x < 6) {
-        unsigned long long m = 0ull;
-        for (int w = 0; w < kBlock / 64; ++w) m = s[w][threadIdx.x] > m ? s[w][threadIdx.x] : m;
-        out[threadIdx.x] = m;
-    }
+    bounds_store(bounds_block_max(v), out);
 }
 
 __global__ void k_bounds_decode(unsigned long long* __restrict__ bits, double* __restrict__ out, int n6)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n6) return;
-    unsigned long long v = bits[i];
-    if (i % 6 < 3) v = ~v;
-    unsigned long long raw = (v & 0x8000000000000000ull) ? (v & 0x7fffffffffffffffull) : ~v;
-    out[i] = __longlong_as_double((long long)raw);
+    const unsigned long long v = bits[i];
+    out[i] = unord_bits(i % 6 < 3 ? ~v : v);
 }
 
-// -------------------------------------------------------------------- keys
+// ----------------------------------------------------------- counting sort
+//
+// The bodies go to cell order in three passes around a scan of the cells'
+// counts: every body counts itself in its cell (and a large one in its
+// level-1 cell), takes a place in the cell in the order of arrival, and is
+// moved to its rank by id among the bodies of its cell.  The order of
+// arrival depends on the atomics, the final order does not.  The level-1
+// index array keeps the order of arrival: only the order in which a search
+// meets its candidates depends on it, and rows are sorted.  Against a radix
+// sort of 64-bit keys (five launches per 8 bits, twice with two levels) the
+// sort takes five to seven launches whatever the grid.  A whole run, start to
+// first step, with the counts read back once: 1,000 spheres 400 -> 141 us,
+// 9,262 408 -> 271, 200,000 (size ratio 3) 1.4 ms -> 281 us.
 
 template <bool BATCHED, bool PERIODIC>
-__global__ void __launch_bounds__(kBlock) k_keys(GridArgs g, uint64_t* __restrict__ keys,
-                                                 uint32_t* __restrict__ vals)
+__global__ void __launch_bounds__(kBlock) k_cell_count(GridArgs g, CellSortArgs c)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= g.nslots) return;
     const int s = BATCHED ? (int)g.bod.scene[i] : 0;
-    const SceneParams& P = (BATCHED || PERIODIC) ? g.scenes[s] : g.scene0;
-    int c[3], per[3];
+    const SceneParams& P = BATCHED ? g.scenes[s] : g.scene0;
+    int cc[3], per[3];
     const double4 p = g.bod.xr[i];
-    cell_of<PERIODIC>(P, level_of(P, 0), p.x, p.y, p.z, c, per);
-    // key: scene | Morton code of the level-0 cell (every sphere)
-    uint64_t key = morton3(c[0], c[1], c[2]);
-    if (BATCHED) key |= (uint64_t)s << (3 * g.morton_bits);
-    keys[i] = key;
-    vals[i] = (uint32_t)i;
+    const Level V = level_of(P, 0);
+    cell_of<PERIODIC>(P, V, p.x, p.y, p.z, cc, per);
+    const uint32_t lin = cell_index_yz(V, cc[1], cc[2]) + cell_index_x(V, cc[0]);
+    c.cell[i] = lin;
+    c.arrival[i] = atomicAdd(&c.count[lin], 1u);
     if (PERIODIC) {
         // a period is packed in 10 bits per axis: farther than 512 periods
         // from the origin it would wrap, so the run is refused instead
@@ -241,108 +259,62 @@ __global__ void __launch_bounds__(kBlock) k_keys(GridArgs g, uint64_t* __restric
         if (out) *g.period_range = 1;
         g.bod.period[i] = pack_cell(per[0], per[1], per[2]);
     }
+    if (c.nlarge > 0 && level_of_radius(P, p.w) == 1) {
+        const Level V1 = level_of(P, 1);
+        cell_of<PERIODIC>(P, V1, p.x, p.y, p.z, cc, per);
+        const uint32_t lin1 = cell_index_yz(V1, cc[1], cc[2]) + cell_index_x(V1, cc[0]);
+        c.cell1[i] = lin1;
+        c.arrival1[i] = atomicAdd(&c.count[lin1], 1u);
+    }
+}
+
+__global__ void __launch_bounds__(kBlock) k_cell_bucket(GridArgs g, CellSortArgs c)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= g.nslots) return;
+    const uint32_t pos = c.start[c.cell[i]] + c.arrival[i];
+    c.bucket[pos] = (uint32_t)i;
+    c.bucket_id[pos] = g.bod.id[i];
 }
 
 // ----------------------------------------------------------------- permute
 
-__global__ void __launch_bounds__(kBlock) k_permute(Bodies src, Bodies dst, const uint32_t* __restrict__ order,
-                                                    int nslots, int batched, int periodic,
-                                                    int32_t* __restrict__ slot_of_id)
+// One thread per place of the bucket order: the body there moves to its rank
+// by id in its cell.  Also clears the next pair list's range of every body
+// (a body without pairs keeps the empty one).
+template <bool BATCHED>
+__global__ void __launch_bounds__(kBlock) k_permute(GridArgs g, CellSortArgs c, Bodies dst, int periodic,
+                                                    int32_t* __restrict__ slot_of_id, int32_t* __restrict__ own_begin,
+                                                    int32_t* __restrict__ own_count)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nslots) return;
-    const uint32_t o = order[i];
-    dst.xr[i] = src.xr[o];
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= g.nslots) return;
+    const Bodies& src = g.bod;
+    const uint32_t o = c.bucket[t];
+    const int32_t id = c.bucket_id[t];
+    const uint32_t lin = c.cell[o];
+    const uint32_t beg = c.start[lin], end = c.start[lin + 1];
+    const double4 xr = src.xr[o];
+    uint32_t i = beg;
+    for (uint32_t q = beg; q < end; ++q) i += c.bucket_id[q] < id ? 1u : 0u;
+    dst.xr[i] = xr;
     const double4 v = src.vm[o];
     dst.vm[i] = make_double4(v.x, v.y, v.z, 0.0);  // a fresh Verlet account after every broad-phase run
     dst.w[i] = src.w[o];
     dst.q[i] = src.q[o];
     dst.mat[i] = src.mat[o];
     dst.blocked[i] = src.blocked[o];
-    const int32_t id = src.id[o];
     dst.id[i] = id;
-    if (batched) dst.scene[i] = src.scene[o];
+    if (BATCHED) dst.scene[i] = src.scene[o];
     if (periodic) dst.period[i] = src.period[o];
-    slot_of_id[id] = i;
-}
-
-// ------------------------------------------------------------------- cells
-
-template <int LV>
-__device__ inline int cell_linear(const GridArgs& g, uint64_t key)
-{
-    const uint64_t mmask = (3 * g.morton_bits >= 64) ? ~0ull : ((1ull << (3 * g.morton_bits)) - 1ull);
-    const int s = g.nscenes > 1 ? (int)(key >> (3 * g.morton_bits)) : 0;
-    const SceneParams& P = g.nscenes > 1 ? g.scenes[s] : g.scene0;
-    const Level V = level_of(P, LV);
-    const uint64_t m = key & mmask;
-    const int cx = (int)compact3(m), cy = (int)compact3(m >> 1), cz = (int)compact3(m >> 2);
-    return V.offset + cx + V.dims[0] * (cy + V.dims[1] * cz);
-}
-
-__global__ void k_fill_u32(uint32_t* __restrict__ p, uint32_t v, int n)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
-__global__ void __launch_bounds__(kBlock) k_cells(GridArgs g, const uint64_t* __restrict__ keys,
-                                                  uint32_t* __restrict__ cell_start, uint32_t* __restrict__ cell_end,
-                                                  int ncells)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= g.nslots) return;
-    const uint64_t k = keys[i];
-    const int lin = cell_linear<0>(g, k);
-    if (lin < 0 || lin >= ncells) return;
-    if (i == 0 || keys[i - 1] != k) cell_start[lin] = (uint32_t)i;
-    if (i == g.nslots - 1 || keys[i + 1] != k) cell_end[lin] = (uint32_t)(i + 1);
-}
-
-// ---------------------------------------------------- level 1 (two levels)
-
-// flag[i] = 1 for a sphere above its scene's r_split
-template <bool BATCHED>
-__global__ void __launch_bounds__(kBlock) k_large_flags(GridArgs g, uint32_t* __restrict__ flag)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= g.nslots) return;
-    const int s = BATCHED ? (int)g.bod.scene[i] : 0;
-    const SceneParams& P = BATCHED ? g.scenes[s] : g.scene0;
-    flag[i] = level_of_radius(P, g.bod.xr[i].w) == 1 ? 1u : 0u;
-}
-
-// the coarse-cell key and slot of each large sphere, at its scanned position
-template <bool BATCHED, bool PERIODIC>
-__global__ void __launch_bounds__(kBlock) k_large_keys(GridArgs g, const uint32_t* __restrict__ scan,
-                                                       uint64_t* __restrict__ keys2, uint32_t* __restrict__ vals2)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= g.nslots) return;
-    const uint32_t q = scan[i];
-    if (scan[i + 1] == q) return;  // not a large sphere
-    const int s = BATCHED ? (int)g.bod.scene[i] : 0;
-    const SceneParams& P = (BATCHED || PERIODIC) ? g.scenes[s] : g.scene0;
-    const double4 p = g.bod.xr[i];
-    int c[3], per[3];
-    cell_of<PERIODIC>(P, level_of(P, 1), p.x, p.y, p.z, c, per);
-    uint64_t key = morton3(c[0], c[1], c[2]);
-    if (BATCHED) key |= (uint64_t)s << (3 * g.morton_bits);
-    keys2[q] = key;
-    vals2[q] = (uint32_t)i;
-}
-
-__global__ void __launch_bounds__(kBlock) k_cells_large(GridArgs g, const uint64_t* __restrict__ keys2, int n,
-                                                        uint32_t* __restrict__ cell_start,
-                                                        uint32_t* __restrict__ cell_end, int ncells)
-{
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= n) return;
-    const uint64_t k = keys2[q];
-    const int lin = cell_linear<1>(g, k);
-    if (lin < 0 || lin >= ncells) return;
-    if (q == 0 || keys2[q - 1] != k) cell_start[lin] = (uint32_t)q;
-    if (q == n - 1 || keys2[q + 1] != k) cell_end[lin] = (uint32_t)(q + 1);
+    slot_of_id[id] = (int32_t)i;
+    own_begin[id] = 0;
+    own_count[id] = 0;
+    if (c.nlarge > 0) {
+        const SceneParams& P = BATCHED ? g.scenes[src.scene[o]] : g.scene0;
+        if (level_of_radius(P, xr.w) == 1)
+            c.large_slot[c.start[c.cell1[o]] - (uint32_t)g.nslots + c.arrival1[o]] = i;
+    }
 }
 
 // ------------------------------------------------------------------- sweep
@@ -365,15 +337,15 @@ __device__ inline void wrap_axis(int& n, int dim, int& w, bool& skip)
 
 // Visit every candidate of home slot i (27 cells, then the scene's walls).
 // f(partner_slot_or_wall, partner_id, packed_cell) is called per candidate.
-// With SPLIT, the 64 lanes of a wave share one sphere's search: lane `part`
-// visits every 64th group of cells, and every 64th wall.
-template <bool BATCHED, bool PERIODIC, bool SPLIT = false, typename F>
+// LANES lanes of a wave share one sphere's search: lane `part` visits every
+// LANES-th group of cells, and every LANES-th wall.
+template <bool BATCHED, bool PERIODIC, int LANES = 1, typename F>
 __device__ inline void for_each_candidate(const SweepArgs& a, int i, F&& f, int part = 0)
 {
     const GridArgs& g = a.g;
     const Bodies& B = g.bod;
     const int s = BATCHED ? (int)B.scene[i] : 0;
-    const SceneParams& P = (BATCHED || PERIODIC) ? g.scenes[s] : g.scene0;
+    const SceneParams& P = BATCHED ? g.scenes[s] : g.scene0;
     const double4 pi = B.xr[i];
     const double xi = pi.x, yi = pi.y, zi = pi.z, ri = pi.w;
     const int32_t myid = B.id[i];
@@ -436,7 +408,7 @@ __device__ inline void for_each_candidate(const SweepArgs& a, int i, F&& f, int 
         wrap_axis<PERIODIC>(ny, V.dims[1], wy, skip_row);
         wrap_axis<PERIODIC>(nz, V.dims[2], wz, skip_row);
         if (skip_row) return;
-        const int row_lin = V.offset + V.dims[0] * (ny + V.dims[1] * nz);
+        const uint32_t row = cell_index_yz(V, ny, nz);
         uint32_t st[3], en[3];
         int wx[3];
 #pragma unroll
@@ -445,16 +417,14 @@ __device__ inline void for_each_candidate(const SweepArgs& a, int i, F&& f, int 
             bool skip = dx0 + t > kk[0];
             wx[t] = 0;
             wrap_axis<PERIODIC>(nx, V.dims[0], wx[t], skip);
-            st[t] = kEmpty;
-            en[t] = 0;
+            st[t] = en[t] = 0;
             if (!skip) {
-                st[t] = a.cell_start[row_lin + nx];
-                en[t] = a.cell_end[row_lin + nx];
+                const uint32_t lin = row + cell_index_x(V, nx);
+                st[t] = a.cell_start[lin];
+                en[t] = a.cell_start[lin + 1];
             }
         }
-        const uint32_t c0 = st[0] == kEmpty ? 0u : en[0] - st[0];
-        const uint32_t c1 = st[1] == kEmpty ? 0u : en[1] - st[1];
-        const uint32_t c2 = st[2] == kEmpty ? 0u : en[2] - st[2];
+        const uint32_t c0 = en[0] - st[0], c1 = en[1] - st[1], c2 = en[2] - st[2];
         const uint32_t tot = c0 + c1 + c2;
         auto at = [&](uint32_t k, int& wk) -> uint32_t {
             uint32_t q;
@@ -468,7 +438,7 @@ __device__ inline void for_each_candidate(const SweepArgs& a, int i, F&& f, int 
                 q = st[2] + (k - c0 - c1);
                 wk = wx[2];
             }
-            return lv == 0 ? q : g.large_slot[q];
+            return lv == 0 ? q : g.large_slot[q - (uint32_t)g.nslots];
         };
         for (uint32_t k = 0; k < tot; k += 2) {
             const bool two_here = k + 1 < tot;
@@ -482,11 +452,11 @@ __device__ inline void for_each_candidate(const SweepArgs& a, int i, F&& f, int 
             if (two_here) visit(jb, pb, perb, idb, wb, wy, wz);
         }
     };
-    if (SPLIT) {
+    if (LANES > 1) {
         // group gi = ((dz * ndy) + dy) * nch + chunk, lane `part` taking
-        // every 64th, so that the wave's lanes search at the same time
+        // every LANES-th, so that the lanes search at the same time
         const int nch = (2 * kk[0] + 3) / 3, ndy = 2 * kk[1] + 1, ng = nch * ndy * (2 * kk[2] + 1);
-        for (int gi = part; gi < ng; gi += 64) {
+        for (int gi = part; gi < ng; gi += LANES) {
             const int ch = gi % nch, r = gi / nch;
             group(r / ndy - kk[2], r % ndy - kk[1], 3 * ch - kk[0]);
         }
@@ -496,7 +466,7 @@ __device__ inline void for_each_candidate(const SweepArgs& a, int i, F&& f, int 
                 for (int dx0 = -kk[0]; dx0 <= kk[0]; dx0 += 3) group(dz, dy, dx0);
     }
     }
-    for (int k = SPLIT ? part : 0; k < P.wall_count; k += SPLIT ? 64 : 1) {
+    for (int k = part; k < P.wall_count; k += LANES) {
         const int wi = P.wall_begin + k;
         const Wall W = a.walls[wi];
         if (W.kind == kPlane) {
@@ -512,13 +482,16 @@ __device__ inline void for_each_candidate(const SweepArgs& a, int i, F&& f, int 
 }
 
 // The sweeps run in two passes when a scene has two levels: the spheres of
-// level 0 first, one per lane (a large sphere's lane returns at once), then
-// the large ones through their index array, one per wave (a large sphere
-// searches many more cells, which the wave's lanes share).
-template <bool BATCHED>
+// level 0 first (a large sphere's lanes return at once), then the large ones
+// through their index array, one per wave (a large sphere searches many more
+// cells, which the wave's lanes share).  On level 0 a sphere takes LANES
+// lanes: the search is a chain of dependent loads, nine groups of cells long
+// in the plain grid, so a scene too small to fill the chip with a sphere per
+// lane shares each search among as many lanes as fill it (sweep_lanes).
+template <bool BATCHED, int LANES>
 __device__ inline int sweep_body(const SweepArgs& a)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    const int t = (blockIdx.x * blockDim.x + threadIdx.x) / LANES;
     if (t >= a.g.nslots) return -1;
     if (a.nlarge > 0) {
         const int s = BATCHED ? (int)a.g.bod.scene[t] : 0;
@@ -528,14 +501,17 @@ __device__ inline int sweep_body(const SweepArgs& a)
     return t;
 }
 
-template <bool BATCHED, bool PERIODIC>
+template <bool BATCHED, bool PERIODIC, int LANES>
 __global__ void __launch_bounds__(kBlock) k_sweep_count(SweepArgs a)
 {
-    const int i = sweep_body<BATCHED>(a);
+    const int i = sweep_body<BATCHED, LANES>(a);
     if (i < 0) return;
+    const int part = threadIdx.x % LANES;
     uint32_t n = 0;
-    for_each_candidate<BATCHED, PERIODIC>(a, i, [&](int32_t, int32_t, int32_t) { ++n; });
-    a.count[i] = n;
+    for_each_candidate<BATCHED, PERIODIC, LANES>(a, i, [&](int32_t, int32_t, int32_t) { ++n; }, part);
+#pragma unroll
+    for (int off = LANES / 2; off > 0; off >>= 1) n += __shfl_down(n, off, LANES);
+    if (part == 0) a.count[i] = n;
 }
 
 // The level-1 sphere of a wave (-1 past the last: the whole wave returns).
@@ -552,7 +528,7 @@ __global__ void __launch_bounds__(kBlock) k_sweep_count_large(SweepArgs a)
     if (i < 0) return;
     const int lane = threadIdx.x & 63;
     uint32_t n = 0;
-    for_each_candidate<BATCHED, PERIODIC, true>(a, i, [&](int32_t, int32_t, int32_t) { ++n; }, lane);
+    for_each_candidate<BATCHED, PERIODIC, 64>(a, i, [&](int32_t, int32_t, int32_t) { ++n; }, lane);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) n += __shfl_down(n, off, 64);
     if (lane == 0) a.count[i] = n;
@@ -574,42 +550,54 @@ __device__ inline uint64_t row_key(int32_t pid, int32_t cell)
     return ((uint64_t)((uint32_t)pid ^ 0x80000000u) << 32) | (uint32_t)cell;
 }
 
+// Whether this run's entries (and pairs) fit what the host sized the buffers
+// and launches for; if not, every later kernel of the run returns at once
+// and the host runs them again with the sizes it reads back.
+__device__ inline bool entries_fit(const SweepArgs& a) { return *a.nent_dev <= (uint32_t)a.lim_ent; }
+
 // The level-0 fill.  The rows of a block's spheres are contiguous, and the
 // block takes them, in slot order, into its LDS pool while they fit: such a
 // sweep stores nothing to memory (a store inside its loop would hold every
 // later load until the store is done), then ranks its row in LDS and writes
 // it sorted.  A row beyond the pool is written in the order found and
-// sorted by the rank pass.
-template <bool BATCHED, bool PERIODIC>
+// sorted by the rank pass.  The lanes that share a sphere take the next
+// place of its row from a counter in LDS (the order found does not matter).
+template <bool BATCHED, bool PERIODIC, int LANES>
 __global__ void __launch_bounds__(kBlock) k_sweep_fill_staged(SweepArgs a)
 {
     __shared__ int32_t s_slot[kStageEntries];
     __shared__ int32_t s_pid[kStageEntries];
     __shared__ int32_t s_cell[kStageEntries];
     __shared__ uint32_t s_wave[kBlock / 64];
-    const int i = sweep_body<BATCHED>(a);
+    __shared__ int32_t s_found[kBlock / LANES];
+    if (!entries_fit(a)) return;
+    const int i = sweep_body<BATCHED, LANES>(a);
+    const int part = threadIdx.x % LANES, own = threadIdx.x / LANES;
     int beg = 0, len = 0;
     if (i >= 0) {
         beg = a.row_start[i];
         len = a.row_start[i + 1] - beg;
     }
-    // the block's exclusive scan of the row lengths, in slot order
+    // the block's exclusive scan of the row lengths, in slot order (a
+    // sphere's first lane brings its length)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t inc = (uint32_t)len;
+    uint32_t inc = part == 0 ? (uint32_t)len : 0u;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
         const uint32_t y = __shfl_up(inc, off, 64);
         if (lane >= off) inc += y;
     }
     if (lane == 63) s_wave[wave] = inc;
+    if (part == 0) s_found[own] = 0;
     __syncthreads();
     uint32_t base = 0;
     for (int w = 0; w < wave; ++w) base += s_wave[w];
     if (i < 0) return;
     const uint32_t off = base + inc - (uint32_t)len;
     const bool staged = off + (uint32_t)len <= (uint32_t)kStageEntries;
-    int n = 0;
-    for_each_candidate<BATCHED, PERIODIC>(a, i, [&](int32_t slot, int32_t pid, int32_t cell) {
+    int mine = 0;
+    for_each_candidate<BATCHED, PERIODIC, LANES>(a, i, [&](int32_t slot, int32_t pid, int32_t cell) {
+        const int n = LANES == 1 ? mine++ : atomicAdd(&s_found[own], 1);
         if (n < len) {
             if (staged) {
                 s_slot[off + n] = slot;
@@ -621,16 +609,19 @@ __global__ void __launch_bounds__(kBlock) k_sweep_fill_staged(SweepArgs a)
                 a.raw_cell[beg + n] = cell;
             }
         }
-        ++n;
-    });
-    for (int e = 0; e < len; ++e) a.ent_body[beg + e] = i;
-    if (!staged) {
-        a.count[i] = kRowFound;
-        return;
+    }, part);
+    for (int e = part; e < len; e += LANES) a.ent_body[beg + e] = i;
+    if (part == 0) a.count[i] = staged ? kRowSorted : kRowFound;
+    if (!staged) return;
+    if (LANES > 1) {
+        // the sphere's lanes are in one wave: their LDS writes are complete
+        // before any of them ranks the row
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     }
-    a.count[i] = kRowSorted;
     const int32_t myid = a.g.bod.id[i];
-    for (int e = 0; e < len; ++e) {
+    for (int e = part; e < len; e += LANES) {
         const int32_t slot = s_slot[off + e], pid = s_pid[off + e], cell = s_cell[off + e];
         const uint64_t ke = row_key(pid, cell);
         int rank = 0;
@@ -652,11 +643,12 @@ __global__ void __launch_bounds__(kBlock) k_sweep_fill_staged(SweepArgs a)
 template <bool BATCHED, bool PERIODIC>
 __global__ void __launch_bounds__(kBlock) k_sweep_fill_large(SweepArgs a)
 {
+    if (!entries_fit(a)) return;
     const int i = large_sphere_of_wave(a);
     if (i < 0) return;
     const int lane = threadIdx.x & 63;
     uint32_t mine = 0;
-    for_each_candidate<BATCHED, PERIODIC, true>(a, i, [&](int32_t, int32_t, int32_t) { ++mine; }, lane);
+    for_each_candidate<BATCHED, PERIODIC, 64>(a, i, [&](int32_t, int32_t, int32_t) { ++mine; }, lane);
     uint32_t inc = mine;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
@@ -666,7 +658,7 @@ __global__ void __launch_bounds__(kBlock) k_sweep_fill_large(SweepArgs a)
     const int beg = a.row_start[i];
     const int cap = a.row_start[i + 1] - beg;
     int n = (int)(inc - mine);
-    for_each_candidate<BATCHED, PERIODIC, true>(a, i, [&](int32_t slot, int32_t pid, int32_t cell) {
+    for_each_candidate<BATCHED, PERIODIC, 64>(a, i, [&](int32_t slot, int32_t pid, int32_t cell) {
         if (n < cap) {
             a.raw_slot[beg + n] = slot;
             a.raw_pid[beg + n] = pid;
@@ -686,7 +678,7 @@ __global__ void __launch_bounds__(kBlock) k_sweep_fill_large(SweepArgs a)
 __global__ void __launch_bounds__(kBlock) k_row_rank(SweepArgs a)
 {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= a.nent) return;
+    if (!entries_fit(a) || (uint32_t)e >= *a.nent_dev) return;
     const int i = a.ent_body[e];
     if (a.count[i] != kRowFound) return;
     const int beg = a.row_start[i], end = a.row_start[i + 1];
@@ -714,6 +706,7 @@ constexpr int kLargeRowLds = 1024;
 __global__ void __launch_bounds__(kBlock) k_row_rank_large(SweepArgs a)
 {
     __shared__ uint64_t s_key[kBlock / 64][kLargeRowLds];
+    if (!entries_fit(a)) return;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int t = blockIdx.x * (kBlock / 64) + wave;
     if (t >= a.nlarge) return;  // the whole wave
@@ -752,6 +745,11 @@ __global__ void __launch_bounds__(kBlock) k_row_rank_large(SweepArgs a)
 
 // -------------------------------------------------------- pairs and history
 
+__device__ inline bool pairs_fit(const PairBuildArgs& a)
+{
+    return *a.nent_dev <= (uint32_t)a.lim_ent && *a.npairs_dev <= (uint32_t)a.lim_pairs;
+}
+
 // One thread per row entry: an owning entry writes its pair (canonical
 // index = the scan of the owner flags) and its row entry; the other finds
 // its pair by binary search in the partner's sorted row.  The first entry of
@@ -759,7 +757,7 @@ __global__ void __launch_bounds__(kBlock) k_row_rank_large(SweepArgs a)
 __global__ void __launch_bounds__(kBlock) k_pair_build(PairBuildArgs a)
 {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= a.nent) return;
+    if (!pairs_fit(a) || (uint32_t)e >= *a.nent_dev) return;
     const int i = a.ent_body[e];
     const int32_t myid = a.bod.id[i];
     const int32_t slot = a.ent_slot[e];
@@ -811,11 +809,7 @@ __global__ void __launch_bounds__(kBlock) k_pair_build(PairBuildArgs a)
 __global__ void __launch_bounds__(kBlock) k_carry_find(PairBuildArgs a, int old_nbodies)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k > a.npairs) return;
-    if (k == a.npairs) {
-        a.flag[k] = 0u;  // the scan's extra entry
-        return;
-    }
+    if (!pairs_fit(a) || (uint32_t)k >= *a.npairs_dev) return;
     const int32_t sa = a.ca[k], sb = a.cb[k];
     const int32_t owner = sa >= 0 ? a.bod.id[sa] : a.bod.id[sb];
     const int32_t partner = a.hist_new.pid[k];
@@ -854,12 +848,13 @@ constexpr uint32_t kPartitionChunk = 1u << 14;
 __global__ void __launch_bounds__(kBlock) k_partition(PairBuildArgs a)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= a.npairs) return;
-    int x = (int)(((int64_t)k * 8) / a.npairs);
+    if (!pairs_fit(a) || (uint32_t)k >= *a.npairs_dev) return;
+    const int npairs = (int)*a.npairs_dev;
+    int x = (int)(((int64_t)k * 8) / npairs);
     if (x > 7) x = 7;
-    while (x < 7 && (uint32_t)k >= segment_start(x + 1, a.npairs)) ++x;
-    while (x > 0 && (uint32_t)k < segment_start(x, a.npairs)) --x;
-    const uint32_t x0 = segment_start(x, a.npairs), x1 = segment_start(x + 1, a.npairs);
+    while (x < 7 && (uint32_t)k >= segment_start(x + 1, npairs)) ++x;
+    while (x > 0 && (uint32_t)k < segment_start(x, npairs)) --x;
+    const uint32_t x0 = segment_start(x, npairs), x1 = segment_start(x + 1, npairs);
     const uint32_t p0 = x0 + (((uint32_t)k - x0) / kPartitionChunk) * kPartitionChunk;
     const uint32_t p1 = min(p0 + kPartitionChunk, x1);
     const uint32_t s0 = a.flag_scan[p0];
@@ -889,10 +884,10 @@ __global__ void __launch_bounds__(kBlock) k_partition(PairBuildArgs a)
 __global__ void __launch_bounds__(kBlock) k_remap_rows(PairBuildArgs a)
 {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= a.nent) return;
+    if (!pairs_fit(a) || (uint32_t)e >= *a.nent_dev) return;
     const uint32_t u = a.rows.ent[e];
     const uint32_t k = u & kPairMask;
-    if (k < (uint32_t)a.npairs) {
+    if (k < *a.npairs_dev) {
         const uint32_t pos = (uint32_t)a.hist_new.map[k];
         a.rows.ent[e] = (u & kNegSign) | (a.flag[k] ? kRealBit : 0u) | pos;
         if (u & kNegSign)
@@ -906,102 +901,87 @@ inline int nblocks(long n) { return (int)((n + kBlock - 1) / kBlock); }
 
 }  // namespace
 
-size_t bounds_temp_bytes(int nslots) { return sizeof(unsigned long long) * 6 * (size_t)(nblocks(nslots) + 1); }
+size_t bounds_temp_bytes() { return sizeof(unsigned long long) * 6 * kBoundsBlocks; }
 
 void launch_bounds(const Bodies& b, int nslots, int nscenes, double* out6, void* temp, hipStream_t st)
 {
+    if (nslots > 0 && nscenes == 1) {
+        // a block takes up to eight bodies per thread
+        unsigned long long* part = static_cast<unsigned long long*>(temp);
+        const int nblk = std::min(nblocks((nslots + 7L) / 8), kBoundsBlocks);
+        hipLaunchKernelGGL(k_bounds_block, dim3(nblk), dim3(kBlock), 0, st, b, nslots, part, out6);
+        if (nblk > 1) hipLaunchKernelGGL(k_bounds_final, dim3(1), dim3(kBlock), 0, st, part, nblk, out6);
+        return;
+    }
     // out6 doubles as the buffer of ordered bits (same size)
     unsigned long long* bits = reinterpret_cast<unsigned long long*>(out6);
     (void)hipMemsetAsync(bits, 0, sizeof(unsigned long long) * 6 * nscenes, st);
-    if (nslots > 0) {
-        if (nscenes == 1) {
-            unsigned long long* part = static_cast<unsigned long long*>(temp);
-            hipLaunchKernelGGL(k_bounds_block, dim3(nblocks(nslots)), dim3(kBlock), 0, st, b, nslots, part);
-            hipLaunchKernelGGL(k_bounds_final, dim3(1), dim3(kBlock), 0, st, part, nblocks(nslots), bits);
-        } else {
-            // bodies are grouped by scene after the first run, so nearly every
-            // wave is uniform and the atomics spread over the scenes
-            hipLaunchKernelGGL(k_bounds, dim3(nblocks(nslots)), dim3(kBlock), 0, st, b, nslots, 1, bits);
-        }
-    }
+    // bodies are grouped by scene after the first run, so nearly every
+    // wave is uniform and the atomics spread over the scenes
+    if (nslots > 0) hipLaunchKernelGGL(k_bounds, dim3(nblocks(nslots)), dim3(kBlock), 0, st, b, nslots, 1, bits);
     hipLaunchKernelGGL(k_bounds_decode, dim3(nblocks(6 * nscenes)), dim3(kBlock), 0, st, bits, out6, 6 * nscenes);
 }
 
-void launch_keys(const GridArgs& g, uint64_t* keys, uint32_t* vals, hipStream_t st)
+void launch_cell_count(const GridArgs& g, const CellSortArgs& c, bool periodic, hipStream_t st)
 {
     if (g.nslots <= 0) return;
     const bool batched = g.nscenes > 1;
-    const bool periodic = g.scene0.periodic != 0;
-    dim3 grid(nblocks(g.nslots)), blk(kBlock);
+    const dim3 grid(nblocks(g.nslots)), blk(kBlock);
+    (void)hipMemsetAsync(c.count, 0, sizeof(uint32_t) * (size_t)c.ncells, st);
     if (batched)
-        hipLaunchKernelGGL((k_keys<true, false>), grid, blk, 0, st, g, keys, vals);
+        hipLaunchKernelGGL((k_cell_count<true, false>), grid, blk, 0, st, g, c);
     else if (periodic)
-        hipLaunchKernelGGL((k_keys<false, true>), grid, blk, 0, st, g, keys, vals);
+        hipLaunchKernelGGL((k_cell_count<false, true>), grid, blk, 0, st, g, c);
     else
-        hipLaunchKernelGGL((k_keys<false, false>), grid, blk, 0, st, g, keys, vals);
+        hipLaunchKernelGGL((k_cell_count<false, false>), grid, blk, 0, st, g, c);
 }
 
-void launch_permute(const Bodies& src, const Bodies& dst, const uint32_t* order, int nslots, bool batched,
-                    bool periodic, int32_t* slot_of_id, hipStream_t st)
-{
-    if (nslots <= 0) return;
-    hipLaunchKernelGGL(k_permute, dim3(nblocks(nslots)), dim3(kBlock), 0, st, src, dst, order, nslots,
-                       batched ? 1 : 0, periodic ? 1 : 0, slot_of_id);
-}
-
-void launch_cells(const GridArgs& g, const uint64_t* sorted_keys, uint32_t* cell_start, uint32_t* cell_end,
-                  int ncells, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_fill_u32, dim3(nblocks(ncells)), dim3(kBlock), 0, st, cell_start, kEmpty, ncells);
-    hipLaunchKernelGGL(k_fill_u32, dim3(nblocks(ncells)), dim3(kBlock), 0, st, cell_end, 0u, ncells);
-    if (g.nslots > 0)
-        hipLaunchKernelGGL(k_cells, dim3(nblocks(g.nslots)), dim3(kBlock), 0, st, g, sorted_keys, cell_start,
-                           cell_end, ncells);
-}
-
-void launch_large_flags(const GridArgs& g, uint32_t* flag, hipStream_t st)
+void launch_cell_place(const GridArgs& g, const CellSortArgs& c, const Bodies& dst, bool periodic, int32_t* slot_of_id,
+                       int32_t* own_begin, int32_t* own_count, void* scan_temp, hipStream_t st)
 {
     if (g.nslots <= 0) return;
-    if (g.nscenes > 1)
-        hipLaunchKernelGGL((k_large_flags<true>), dim3(nblocks(g.nslots)), dim3(kBlock), 0, st, g, flag);
+    const bool batched = g.nscenes > 1;
+    const dim3 grid(nblocks(g.nslots)), blk(kBlock);
+    exclusive_scan_u32(c.count, c.start, c.ncells, nullptr, scan_temp, nullptr, st);
+    hipLaunchKernelGGL(k_cell_bucket, grid, blk, 0, st, g, c);
+    if (batched)
+        hipLaunchKernelGGL((k_permute<true>), grid, blk, 0, st, g, c, dst, 0, slot_of_id, own_begin, own_count);
     else
-        hipLaunchKernelGGL((k_large_flags<false>), dim3(nblocks(g.nslots)), dim3(kBlock), 0, st, g, flag);
+        hipLaunchKernelGGL((k_permute<false>), grid, blk, 0, st, g, c, dst, periodic ? 1 : 0, slot_of_id, own_begin,
+                           own_count);
 }
 
-void launch_large_keys(const GridArgs& g, const uint32_t* scan, uint64_t* keys2, uint32_t* vals2, hipStream_t st)
-{
-    if (g.nslots <= 0) return;
-    dim3 grid(nblocks(g.nslots)), blk(kBlock);
-    if (g.nscenes > 1)
-        hipLaunchKernelGGL((k_large_keys<true, false>), grid, blk, 0, st, g, scan, keys2, vals2);
-    else if (g.scene0.periodic)
-        hipLaunchKernelGGL((k_large_keys<false, true>), grid, blk, 0, st, g, scan, keys2, vals2);
-    else
-        hipLaunchKernelGGL((k_large_keys<false, false>), grid, blk, 0, st, g, scan, keys2, vals2);
-}
+// Lanes per sphere of the level-0 sweeps: as many as keep the launch within
+// about the threads the chip holds at once (256 CUs x 2,048).  Measured
+// (count + fill) with 1 lane and with the choice: 1,000 spheres 44 + 63 us ->
+// 8.7 + 12.9 on 16 lanes, 200,000 72 + 87 -> 52 + 65 on 4; 8 M keep 1.
+inline int sweep_lanes(int nslots) { return nslots <= 32768 ? 16 : (nslots <= 262144 ? 4 : 1); }
 
-void launch_cells_large(const GridArgs& g, const uint64_t* sorted_keys2, int nlarge, uint32_t* cell_start,
-                        uint32_t* cell_end, int ncells, hipStream_t st)
-{
-    if (nlarge > 0)
-        hipLaunchKernelGGL(k_cells_large, dim3(nblocks(nlarge)), dim3(kBlock), 0, st, g, sorted_keys2, nlarge,
-                           cell_start, cell_end, ncells);
-}
-
-// The level-0 pass (one sphere per lane) and, with two levels, the level-1
-// pass (one sphere per wave) of a sweep kernel pair.
+// The level-0 pass and, with two levels, the level-1 pass (one sphere per
+// wave) of a sweep kernel pair.
+#define DEM_SWEEP_SMALL(K, B, P, A, ST)                                                                        \
+    do {                                                                                                      \
+        const int lanes_ = sweep_lanes((A).g.nslots);                                                         \
+        const dim3 g0_(nblocks((long)(A).g.nslots * lanes_)), b0_(kBlock);                                    \
+        if (lanes_ == 16)                                                                                     \
+            hipLaunchKernelGGL((K<B, P, 16>), g0_, b0_, 0, ST, A);                                            \
+        else if (lanes_ == 4)                                                                                 \
+            hipLaunchKernelGGL((K<B, P, 4>), g0_, b0_, 0, ST, A);                                             \
+        else                                                                                                  \
+            hipLaunchKernelGGL((K<B, P, 1>), g0_, b0_, 0, ST, A);                                             \
+    } while (0)
 #define DEM_SWEEP_LAUNCH(SMALL, LARGE_K, A, ST)                                                                \
     do {                                                                                                      \
-        const dim3 blk(kBlock), g0(nblocks((A).g.nslots));                                                    \
+        const dim3 blk(kBlock);                                                                               \
         const dim3 g1(((A).nlarge + kBlock / 64 - 1) / (kBlock / 64));                                        \
         if ((A).g.nscenes > 1) {                                                                              \
-            hipLaunchKernelGGL((SMALL<true, false>), g0, blk, 0, ST, A);                                      \
+            DEM_SWEEP_SMALL(SMALL, true, false, A, ST);                                                       \
             if ((A).nlarge > 0) hipLaunchKernelGGL((LARGE_K<true, false>), g1, blk, 0, ST, A);                \
         } else if ((A).g.scene0.periodic) {                                                                   \
-            hipLaunchKernelGGL((SMALL<false, true>), g0, blk, 0, ST, A);                                      \
+            DEM_SWEEP_SMALL(SMALL, false, true, A, ST);                                                       \
             if ((A).nlarge > 0) hipLaunchKernelGGL((LARGE_K<false, true>), g1, blk, 0, ST, A);                \
         } else {                                                                                              \
-            hipLaunchKernelGGL((SMALL<false, false>), g0, blk, 0, ST, A);                                     \
+            DEM_SWEEP_SMALL(SMALL, false, false, A, ST);                                                      \
             if ((A).nlarge > 0) hipLaunchKernelGGL((LARGE_K<false, false>), g1, blk, 0, ST, A);               \
         }                                                                                                     \
     } while (0)
@@ -1016,7 +996,7 @@ void launch_sweep_fill(const SweepArgs& a, hipStream_t st)
 {
     if (a.g.nslots <= 0) return;
     DEM_SWEEP_LAUNCH(k_sweep_fill_staged, k_sweep_fill_large, a, st);
-    if (a.nent > 0) hipLaunchKernelGGL(k_row_rank, dim3(nblocks(a.nent)), dim3(kBlock), 0, st, a);
+    if (a.lim_ent > 0) hipLaunchKernelGGL(k_row_rank, dim3(nblocks(a.lim_ent)), dim3(kBlock), 0, st, a);
     if (a.nlarge > 0)
         hipLaunchKernelGGL(k_row_rank_large, dim3((a.nlarge + kBlock / 64 - 1) / (kBlock / 64)), dim3(kBlock), 0, st,
                            a);
@@ -1024,19 +1004,19 @@ void launch_sweep_fill(const SweepArgs& a, hipStream_t st)
 
 void launch_pair_build(const PairBuildArgs& a, hipStream_t st)
 {
-    if (a.nent <= 0) return;
-    hipLaunchKernelGGL(k_pair_build, dim3(nblocks(a.nent)), dim3(kBlock), 0, st, a);
+    if (a.lim_ent > 0) hipLaunchKernelGGL(k_pair_build, dim3(nblocks(a.lim_ent)), dim3(kBlock), 0, st, a);
 }
 
 void launch_carry_find(const PairBuildArgs& a, hipStream_t st, int old_nbodies)
 {
-    hipLaunchKernelGGL(k_carry_find, dim3(nblocks((long)a.npairs + 1)), dim3(kBlock), 0, st, a, old_nbodies);
+    if (a.lim_pairs > 0)
+        hipLaunchKernelGGL(k_carry_find, dim3(nblocks(a.lim_pairs)), dim3(kBlock), 0, st, a, old_nbodies);
 }
 
 void launch_partition(const PairBuildArgs& a, hipStream_t st)
 {
-    if (a.npairs > 0) hipLaunchKernelGGL(k_partition, dim3(nblocks(a.npairs)), dim3(kBlock), 0, st, a);
-    if (a.nent > 0) hipLaunchKernelGGL(k_remap_rows, dim3(nblocks(a.nent)), dim3(kBlock), 0, st, a);
+    if (a.lim_pairs > 0) hipLaunchKernelGGL(k_partition, dim3(nblocks(a.lim_pairs)), dim3(kBlock), 0, st, a);
+    if (a.lim_ent > 0) hipLaunchKernelGGL(k_remap_rows, dim3(nblocks(a.lim_ent)), dim3(kBlock), 0, st, a);
 }
 
 }  // namespace dem

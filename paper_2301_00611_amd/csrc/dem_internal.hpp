@@ -65,6 +65,9 @@ struct SceneParams {
     double cellw2[3];
     int32_t dims2[3];
     int32_t cell_offset2;
+    // cells are numbered in bricks of 2^brick_bits cells a side (per level)
+    int32_t brick_bits;
+    int32_t brick_bits2;
 };
 
 // A fixed boundary: an infinite axis-aligned plane (utils.wall: axis,
@@ -427,12 +430,13 @@ __device__ inline gptr<T> glb(T* p)
 // (defined in the .hip files; all asynchronous on `st`)
 
 // prim.hip
+// out[0 .. n] = exclusive scan of in[0 .. n), out[n] the total (also into
+// *total_dev when given), n = n_max, or *n_dev when given (a count above
+// n_max scans nothing: the run is abandoned).  in != out; both 16-byte
+// aligned; temp holds scan_temp_bytes(n_max).
 size_t scan_temp_bytes(int n);
-void exclusive_scan_u32(const uint32_t* in, uint32_t* out, int n, void* temp, uint32_t* total_dev,
-                        hipStream_t st);
-size_t radix_temp_bytes(int n);
-void radix_sort_pairs(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* vals_alt, int n,
-                      int nbits, void* temp, hipStream_t st, bool* result_in_alt);
+void exclusive_scan_u32(const uint32_t* in, uint32_t* out, int n_max, const uint32_t* n_dev, void* temp,
+                        uint32_t* total_dev, hipStream_t st);
 
 // broadphase.hip
 struct GridArgs {
@@ -441,30 +445,38 @@ struct GridArgs {
     SceneParams scene0;
     int32_t nscenes;
     int32_t nslots;
-    int32_t scene_bits;        // bits of the scene index in the key
-    int32_t morton_bits;       // bits per axis
-    int32_t* period_range;     // set to 1 by k_keys when a body's period is outside [-512, 511]
+    int32_t* period_range;     // set to 1 by k_cell_count when a body's period is outside [-512, 511]
     const uint32_t* large_slot;  // level 1: slots of the spheres above r_split, in coarse-cell order (or null)
 };
-size_t bounds_temp_bytes(int nslots);
+size_t bounds_temp_bytes();
 void launch_bounds(const Bodies& b, int nslots, int nscenes, double* out6, void* temp, hipStream_t st);
-void launch_keys(const GridArgs& g, uint64_t* keys, uint32_t* vals, hipStream_t st);
-void launch_permute(const Bodies& src, const Bodies& dst, const uint32_t* order, int nslots, bool batched,
-                    bool periodic, int32_t* slot_of_id, hipStream_t st);
-void launch_cells(const GridArgs& g, const uint64_t* sorted_keys, uint32_t* cell_start, uint32_t* cell_end,
-                  int ncells, hipStream_t st);
-// Level 1 of a two-level grid: flags of the spheres above their scene's
-// r_split (then scanned by the caller), their coarse-cell keys and slots at
-// the scanned positions, and (after sorting those) the level's cell ranges
-// into the sorted index array.
-void launch_large_flags(const GridArgs& g, uint32_t* flag, hipStream_t st);
-void launch_large_keys(const GridArgs& g, const uint32_t* scan, uint64_t* keys2, uint32_t* vals2, hipStream_t st);
-void launch_cells_large(const GridArgs& g, const uint64_t* sorted_keys2, int nlarge, uint32_t* cell_start,
-                        uint32_t* cell_end, int ncells, hipStream_t st);
+// The counting sort into cell order: the level-0 cells of every scene come
+// first in the cell table, then the level-1 cells; start (ncells + 1) is the
+// scan of count, so a level-0 cell's bodies are the slots start[c] ..
+// start[c + 1], and the level-1 index array (large_slot) holds the large
+// spheres' slots at start[c] - nslots.
+struct CellSortArgs {
+    uint32_t* count;           // ncells
+    uint32_t* start;           // ncells + 1
+    uint32_t* cell;            // per body: its level-0 cell and its order of arrival there
+    uint32_t* arrival;
+    uint32_t* cell1;           // per large body: the same on level 1 (null without one)
+    uint32_t* arrival1;
+    uint32_t* bucket;          // bodies in cell order, in the order of arrival, and their ids
+    int32_t* bucket_id;
+    uint32_t* large_slot;
+    int32_t ncells;
+    int32_t nlarge;
+};
+// the cells' counts (and, periodic, the bodies' periods and their check),
+// then scan, bucket and permute g.bod into dst; own_begin / own_count (the
+// next pair list's ranges, by id) are cleared
+void launch_cell_count(const GridArgs& g, const CellSortArgs& c, bool periodic, hipStream_t st);
+void launch_cell_place(const GridArgs& g, const CellSortArgs& c, const Bodies& dst, bool periodic, int32_t* slot_of_id,
+                       int32_t* own_begin, int32_t* own_count, void* scan_temp, hipStream_t st);
 struct SweepArgs {
     GridArgs g;
-    const uint32_t* cell_start;
-    const uint32_t* cell_end;
+    const uint32_t* cell_start;  // ncells + 1
     const Wall* walls;
     uint32_t* count;           // per slot: the count pass's counts, then how the fill left each row
     const int32_t* row_start;  // fill pass
@@ -480,8 +492,8 @@ struct SweepArgs {
     int32_t* ent_pid;
     int32_t* ent_cell;
     uint32_t* ent_own;         // 1 when this entry owns the pair
-    int32_t max_row;
-    int32_t nent;
+    const uint32_t* nent_dev;  // the run's entries; the fill and what follows run only if at most lim_ent
+    int32_t lim_ent;
     int32_t nlarge;            // spheres on level 1 (their sweeps run as a pass of their own)
 };
 void launch_sweep_count(const SweepArgs& a, hipStream_t st);
@@ -502,11 +514,15 @@ struct PairBuildArgs {
     int32_t* ca;               // canonical #1 / #2 slots (scratch)
     int32_t* cb;
     int32_t* found;            // canonical: index of the pair in the previous list's arrays, -1 if new
-    uint32_t* flag;            // canonical: 1 when the carried history says the pair touched (+1 entry, 0)
+    uint32_t* flag;            // canonical: 1 when the carried history says the pair touched
     uint32_t* flag_scan;       // exclusive scan of flag; flag_scan[npairs] = number of touching pairs
     int32_t nslots;
-    int32_t nent;
-    int32_t npairs;
+    // the run's entries and pairs, on the device; nothing runs when either
+    // exceeds the limit its buffers and launches are sized for
+    const uint32_t* nent_dev;
+    const uint32_t* npairs_dev;
+    int32_t lim_ent;
+    int32_t lim_pairs;
     int32_t has_old;
     int32_t hist_f32;          // history records are HistRec32 (FP32-mixed)
 };
@@ -538,6 +554,11 @@ void launch_integrate(const StepArgs* args, int parity, int grid, int precision,
 // controlled cell is on and the step is one of its updates) the
 // controller, from the contact and integrate kernels' partial sums.
 void launch_cell_update(const StepArgs* args, int parity, hipStream_t st);
+// After a broad-phase run: the step descriptor and the counters are written,
+// the per-block slots of both step kernels cleared (a kernel's arguments carry
+// the values, so nothing is copied from host memory).
+void launch_publish(const StepArgs& a, const Counters& c, StepArgs* dst, int nslots_contact, int nslots_integrate,
+                    hipStream_t st);
 // largest Verlet account over the bodies, as the bits of a double, into
 // *out (which the caller zeroes)
 void launch_max_account(const Bodies& b, int n, unsigned long long* out, hipStream_t st);

@@ -14,6 +14,8 @@
 // one-block kernel after the step.
 #include "dem_internal.hpp"
 
+#include <algorithm>
+
 namespace dem {
 
 namespace {
@@ -736,6 +738,25 @@ __global__ void __launch_bounds__(256) k_max_account(Bodies b, int n, unsigned l
 void launch_max_account(const Bodies& b, int n, unsigned long long* out, hipStream_t st)
 {
     if (n > 0) hipLaunchKernelGGL(k_max_account, dim3((n + 255) / 256), dim3(256), 0, st, b, n, out);
+}
+
+__global__ void __launch_bounds__(256) k_publish(StepArgs a, Counters c, StepArgs* __restrict__ dst, int nc, int ni)
+{
+    const int t = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
+    for (int i = t; i < nc; i += stride) a.acc_contact[i] = ContactAcc{};
+    for (int i = t; i < ni; i += stride) a.acc_integrate[i] = IntAcc{};
+    if (t == 0) {
+        *dst = a;
+        *a.ctr = c;
+    }
+}
+
+void launch_publish(const StepArgs& a, const Counters& c, StepArgs* dst, int nslots_contact, int nslots_integrate,
+                    hipStream_t st)
+{
+    const int n = std::max({nslots_contact, nslots_integrate, 1});
+    hipLaunchKernelGGL(k_publish, dim3(std::min((n + 255) / 256, 1024)), dim3(256), 0, st, a, c, dst, nslots_contact,
+                       nslots_integrate);
 }
 
 void launch_ctrl_reduce(const StepArgs* args, int parity, hipStream_t st)

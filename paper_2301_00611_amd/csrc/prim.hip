@@ -1,12 +1,9 @@
-// prim.hip -- device primitives for gfx950 (wave64): exclusive scan of u32
-// and a stable LSD radix sort of (u64 key, u32 value) pairs.
+// prim.hip -- device primitive for gfx950 (wave64): exclusive scan of u32,
+// over a count the host knows or one that is still on the device.
 //
-// The radix sort ranks keys inside a block with wavefront ballots: the lanes
-// holding the same 8-bit digit are found with 8 ballots (one per digit bit),
-// a lane's rank is the popcount of that mask below it, and per-wave digit
-// counts are combined in LDS in wave order.  Items are taken in (round,
-// wave, lane) order, so the sort is stable and fully deterministic (no
-// ordering depends on atomics).
+// Up to kOneBlock elements take one launch of one block; more take three:
+// the tiles' sums, their scan by one block, the tiles' scans.  Threads read
+// and write eight consecutive elements as two 16-byte vectors.
 #include "dem_internal.hpp"
 
 namespace dem {
@@ -14,11 +11,10 @@ namespace dem {
 namespace {
 
 constexpr int kBlock = 256;           // 4 wavefronts of 64
-constexpr int kWaves = kBlock / 64;
-constexpr int kScanItems = 8;
-constexpr int kScanTile = kBlock * kScanItems;
-constexpr int kSortItems = 8;
-constexpr int kSortTile = kBlock * kSortItems;
+constexpr int kTopBlock = 1024;       // the one-block kernels
+constexpr int kItems = 8;             // consecutive elements per thread
+constexpr int kTile = kBlock * kItems;
+constexpr int kOneBlock = 2 * kTopBlock * kItems;
 
 __device__ inline uint32_t wave_inclusive_scan(uint32_t v)
 {
@@ -32,9 +28,10 @@ __device__ inline uint32_t wave_inclusive_scan(uint32_t v)
 }
 
 // Exclusive scan of one value per thread over the block; returns the block total in *total.
+template <int BLOCK>
 __device__ inline uint32_t block_exclusive_scan(uint32_t v, uint32_t* total)
 {
-    __shared__ uint32_t wave_tot[kWaves];
+    __shared__ uint32_t wave_tot[BLOCK / 64];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     uint32_t inc = wave_inclusive_scan(v);
@@ -42,7 +39,7 @@ __device__ inline uint32_t block_exclusive_scan(uint32_t v, uint32_t* total)
     __syncthreads();
     uint32_t before = 0, all = 0;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
+    for (int w = 0; w < BLOCK / 64; ++w) {
         uint32_t t = wave_tot[w];
         if (w < wave) before += t;
         all += t;
@@ -52,178 +49,140 @@ __device__ inline uint32_t block_exclusive_scan(uint32_t v, uint32_t* total)
     return before + inc - v;
 }
 
-__global__ void __launch_bounds__(kBlock) k_scan_reduce(const uint32_t* __restrict__ in, int n,
-                                                        uint32_t* __restrict__ sums)
+// n = *n_dev where it is given and does not exceed n_max (a larger one means
+// that the run is abandoned: nothing is scanned), else n_max
+__device__ inline int scan_length(int n_max, const uint32_t* n_dev)
 {
-    const long base = (long)blockIdx.x * kScanTile;
+    if (!n_dev) return n_max;
+    const uint32_t n = *n_dev;
+    return n <= (uint32_t)n_max ? (int)n : 0;
+}
+
+// the kItems elements from i on (0 past the end); arrays are 16-byte aligned
+__device__ inline uint32_t load_items(const uint32_t* __restrict__ in, long i, int n, uint32_t* v)
+{
+    if (i + kItems <= n) {
+        const uint4 a = *reinterpret_cast<const uint4*>(in + i), b = *reinterpret_cast<const uint4*>(in + i + 4);
+        v[0] = a.x;
+        v[1] = a.y;
+        v[2] = a.z;
+        v[3] = a.w;
+        v[4] = b.x;
+        v[5] = b.y;
+        v[6] = b.z;
+        v[7] = b.w;
+    } else {
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) v[k] = i + k < n ? in[i + k] : 0u;
+    }
     uint32_t s = 0;
 #pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        long i = base + (long)k * kBlock + threadIdx.x;
-        if (i < n) s += in[i];
+    for (int k = 0; k < kItems; ++k) s += v[k];
+    return s;
+}
+
+// their exclusive scan from `run` on; the thread holding the last element
+// also writes the total at out[n]
+__device__ inline void store_items(uint32_t* __restrict__ out, long i, int n, uint32_t run, const uint32_t* v)
+{
+    uint32_t o[kItems];
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        o[k] = run;
+        run += v[k];
     }
-    uint32_t total;
-    block_exclusive_scan(s, &total);
+    if (i + kItems <= n) {
+        *reinterpret_cast<uint4*>(out + i) = make_uint4(o[0], o[1], o[2], o[3]);
+        *reinterpret_cast<uint4*>(out + i + 4) = make_uint4(o[4], o[5], o[6], o[7]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < kItems; ++k)
+            if (i + k < n) out[i + k] = o[k];
+    }
+    if (i < n && i + kItems >= n) out[n] = run;
+}
+
+__global__ void __launch_bounds__(kTopBlock) k_scan_one(const uint32_t* __restrict__ in, uint32_t* __restrict__ out,
+                                                        int n_max, const uint32_t* __restrict__ n_dev,
+                                                        uint32_t* __restrict__ total_dev)
+{
+    const int n = scan_length(n_max, n_dev);
+    uint32_t carry = 0;
+    for (int c = 0; c < n; c += kTopBlock * kItems) {
+        const long i = c + (long)threadIdx.x * kItems;
+        uint32_t v[kItems], tot;
+        const uint32_t s = load_items(in, i, n, v);
+        const uint32_t ex = block_exclusive_scan<kTopBlock>(s, &tot);
+        store_items(out, i, n, carry + ex, v);
+        carry += tot;
+    }
+    if (threadIdx.x == 0) {
+        if (n == 0) out[0] = 0u;
+        if (total_dev) *total_dev = carry;
+    }
+}
+
+__global__ void __launch_bounds__(kBlock) k_scan_reduce(const uint32_t* __restrict__ in, int n_max,
+                                                        const uint32_t* __restrict__ n_dev,
+                                                        uint32_t* __restrict__ sums)
+{
+    const int n = scan_length(n_max, n_dev);
+    uint32_t v[kItems], total;
+    block_exclusive_scan<kBlock>(load_items(in, (long)blockIdx.x * kTile + (long)threadIdx.x * kItems, n, v), &total);
     if (threadIdx.x == 0) sums[blockIdx.x] = total;
 }
 
-// One block scans the per-tile sums in place, in chunks of kBlock.
-__global__ void __launch_bounds__(kBlock) k_scan_top(uint32_t* __restrict__ sums, int nsums,
-                                                     uint32_t* __restrict__ total_dev)
+// One block scans the tiles' sums in place.
+__global__ void __launch_bounds__(kTopBlock) k_scan_top(uint32_t* __restrict__ sums, int nsums,
+                                                        uint32_t* __restrict__ out,
+                                                        int n_max, const uint32_t* __restrict__ n_dev,
+                                                        uint32_t* __restrict__ total_dev)
 {
     uint32_t carry = 0;
-    for (int c = 0; c < nsums; c += kBlock) {
-        int i = c + threadIdx.x;
-        uint32_t v = i < nsums ? sums[i] : 0u;
+    for (int c = 0; c < nsums; c += kTopBlock) {
+        const int i = c + (int)threadIdx.x;
+        const uint32_t v = i < nsums ? sums[i] : 0u;
         uint32_t tot;
-        uint32_t ex = block_exclusive_scan(v, &tot);
+        const uint32_t ex = block_exclusive_scan<kTopBlock>(v, &tot);
         if (i < nsums) sums[i] = carry + ex;
         carry += tot;
     }
-    if (threadIdx.x == 0 && total_dev) *total_dev = carry;
+    if (threadIdx.x == 0) {
+        if (scan_length(n_max, n_dev) == 0) out[0] = 0u;
+        if (total_dev) *total_dev = carry;
+    }
 }
 
-// Each thread scans kScanItems consecutive elements; in == out is allowed.
-__global__ void __launch_bounds__(kBlock) k_scan_down(const uint32_t* in, uint32_t* out, int n,
+__global__ void __launch_bounds__(kBlock) k_scan_down(const uint32_t* __restrict__ in, uint32_t* __restrict__ out,
+                                                      int n_max, const uint32_t* __restrict__ n_dev,
                                                       const uint32_t* __restrict__ sums)
 {
-    const long base = (long)blockIdx.x * kScanTile + (long)threadIdx.x * kScanItems;
-    uint32_t v[kScanItems];
-    uint32_t s = 0;
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        long i = base + k;
-        v[k] = i < n ? in[i] : 0u;
-        s += v[k];
-    }
-    uint32_t total;
-    uint32_t run = block_exclusive_scan(s, &total) + sums[blockIdx.x];
-#pragma unroll
-    for (int k = 0; k < kScanItems; ++k) {
-        long i = base + k;
-        if (i < n) out[i] = run;
-        run += v[k];
-    }
-}
-
-__global__ void __launch_bounds__(kBlock) k_radix_hist(const uint64_t* __restrict__ keys, int n, int shift,
-                                                       uint32_t* __restrict__ counts, int nblk)
-{
-    __shared__ uint32_t hist[256];
-    hist[threadIdx.x] = 0;
-    __syncthreads();
-    const long base = (long)blockIdx.x * kSortTile;
-#pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
-        long i = base + (long)r * kBlock + threadIdx.x;
-        if (i < n) atomicAdd(&hist[(uint32_t)(keys[i] >> shift) & 255u], 1u);
-    }
-    __syncthreads();
-    counts[(long)threadIdx.x * nblk + blockIdx.x] = hist[threadIdx.x];
-}
-
-__global__ void __launch_bounds__(kBlock) k_radix_scatter(const uint64_t* __restrict__ keys,
-                                                          const uint32_t* __restrict__ vals,
-                                                          uint64_t* __restrict__ keys_out,
-                                                          uint32_t* __restrict__ vals_out, int n, int shift,
-                                                          const uint32_t* __restrict__ offsets, int nblk)
-{
-    __shared__ uint32_t base[256];
-    __shared__ uint32_t wcount[kWaves][256];
-    __shared__ uint32_t woff[kWaves][256];
-    const int t = threadIdx.x;
-    const int lane = t & 63;
-    const int wave = t >> 6;
-    base[t] = offsets[(long)t * nblk + blockIdx.x];
-    const long tile = (long)blockIdx.x * kSortTile;
-    const unsigned long long lanes_below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    for (int r = 0; r < kSortItems; ++r) {
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) wcount[w][t] = 0;
-        __syncthreads();
-        const long i = tile + (long)r * kBlock + t;
-        const bool valid = i < n;
-        uint64_t key = valid ? keys[i] : 0ull;
-        uint32_t val = valid ? vals[i] : 0u;
-        const uint32_t d = (uint32_t)(key >> shift) & 255u;
-        // lanes of this wave holding the same digit
-        unsigned long long m = __ballot(valid);
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const bool bit = (d >> b) & 1u;
-            const unsigned long long bb = __ballot(bit);
-            m &= bit ? bb : ~bb;
-        }
-        const uint32_t rank = (uint32_t)__popcll(m & lanes_below);
-        if (valid && rank == 0) wcount[wave][d] = (uint32_t)__popcll(m);
-        __syncthreads();
-        uint32_t run = base[t];
-#pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-            woff[w][t] = run;
-            run += wcount[w][t];
-        }
-        base[t] = run;
-        __syncthreads();
-        if (valid) {
-            const uint32_t dst = woff[wave][d] + rank;
-            keys_out[dst] = key;
-            vals_out[dst] = val;
-        }
-        __syncthreads();
-    }
+    const int n = scan_length(n_max, n_dev);
+    const long i = (long)blockIdx.x * kTile + (long)threadIdx.x * kItems;
+    uint32_t v[kItems], total;
+    const uint32_t s = load_items(in, i, n, v);
+    const uint32_t ex = block_exclusive_scan<kBlock>(s, &total);
+    store_items(out, i, n, sums[blockIdx.x] + ex, v);
 }
 
 inline int ceil_div(long a, long b) { return (int)((a + b - 1) / b); }
 
 }  // namespace
 
-size_t scan_temp_bytes(int n) { return sizeof(uint32_t) * (size_t)(ceil_div(n, kScanTile) + 1); }
+size_t scan_temp_bytes(int n) { return sizeof(uint32_t) * (size_t)(ceil_div(n, kTile) + 1); }
 
-void exclusive_scan_u32(const uint32_t* in, uint32_t* out, int n, void* temp, uint32_t* total_dev,
-                        hipStream_t st)
+void exclusive_scan_u32(const uint32_t* in, uint32_t* out, int n_max, const uint32_t* n_dev, void* temp,
+                        uint32_t* total_dev, hipStream_t st)
 {
-    if (n <= 0) {
-        if (total_dev) (void)hipMemsetAsync(total_dev, 0, sizeof(uint32_t), st);
+    if (n_max <= kOneBlock) {
+        hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kTopBlock), 0, st, in, out, n_max, n_dev, total_dev);
         return;
     }
-    const int nblk = ceil_div(n, kScanTile);
+    const int nblk = ceil_div(n_max, kTile);
     uint32_t* sums = static_cast<uint32_t*>(temp);
-    hipLaunchKernelGGL(k_scan_reduce, dim3(nblk), dim3(kBlock), 0, st, in, n, sums);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kBlock), 0, st, sums, nblk, total_dev);
-    hipLaunchKernelGGL(k_scan_down, dim3(nblk), dim3(kBlock), 0, st, in, out, n, sums);
-}
-
-size_t radix_temp_bytes(int n)
-{
-    const int nblk = ceil_div(n > 0 ? n : 1, kSortTile);
-    const size_t counts = (size_t)256 * nblk;
-    return sizeof(uint32_t) * counts + scan_temp_bytes((int)counts) + 256;
-}
-
-void radix_sort_pairs(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* vals_alt, int n,
-                      int nbits, void* temp, hipStream_t st, bool* result_in_alt)
-{
-    *result_in_alt = false;
-    if (n <= 1 || nbits <= 0) return;
-    const int nblk = ceil_div(n, kSortTile);
-    const int ncounts = 256 * nblk;
-    uint32_t* counts = static_cast<uint32_t*>(temp);
-    char* scan_tmp = reinterpret_cast<char*>(counts + ncounts);
-    scan_tmp += (256 - (reinterpret_cast<uintptr_t>(scan_tmp) & 255)) & 255;
-    uint64_t* kin = keys;
-    uint32_t* vin = vals;
-    uint64_t* kout = keys_alt;
-    uint32_t* vout = vals_alt;
-    for (int shift = 0; shift < nbits; shift += 8) {
-        hipLaunchKernelGGL(k_radix_hist, dim3(nblk), dim3(kBlock), 0, st, kin, n, shift, counts, nblk);
-        exclusive_scan_u32(counts, counts, ncounts, scan_tmp, nullptr, st);
-        hipLaunchKernelGGL(k_radix_scatter, dim3(nblk), dim3(kBlock), 0, st, kin, vin, kout, vout, n, shift,
-                           counts, nblk);
-        std::swap(kin, kout);
-        std::swap(vin, vout);
-        *result_in_alt = !*result_in_alt;
-    }
+    hipLaunchKernelGGL(k_scan_reduce, dim3(nblk), dim3(kBlock), 0, st, in, n_max, n_dev, sums);
+    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kTopBlock), 0, st, sums, nblk, out, n_max, n_dev, total_dev);
+    hipLaunchKernelGGL(k_scan_down, dim3(nblk), dim3(kBlock), 0, st, in, out, n_max, n_dev, sums);
 }
 
 }  // namespace dem

@@ -157,6 +157,14 @@ struct PairSet {
         frec.ensure(n * kForceWords * (fp32 ? sizeof(float) : sizeof(double)));
         cap = n;
     }
+    // pairs its buffers hold
+    size_t room(bool fp32) const
+    {
+        size_t n = std::min({real.bytes, hist.bytes / hist_bytes(fp32 ? DEM_FP32_MIXED : DEM_FP64),
+                             frec.bytes / (kForceWords * (fp32 ? sizeof(float) : sizeof(double)))});
+        for (const DBuf* d : {&a, &b, &cell, &pid, &ea, &eb, &hpid, &hcell, &hmap}) n = std::min(n, d->bytes / 4);
+        return n;
+    }
     Pairs view() const
     {
         Pairs p;
@@ -271,8 +279,10 @@ struct World {
     int nslots = 0;
     int ngids_dev = 0;                 // number of gids the device arrays were built for
     int old_ngids = 0;                 // gids covered by the active own arrays
-    DBuf slot_of_id, d_gids, d_state, keys, vals, keys_alt, vals_alt, cell_start, cell_end, counts, row_start;
-    DBuf ent_slot, ent_pid, ent_cell, ent_own, own_scan, rows_ent, scan_tmp, radix_tmp;
+    DBuf slot_of_id, d_gids, d_state, counts, row_start;
+    // the counting sort: cell table (counts, starts), per body its cell and order of arrival, bucket order
+    DBuf cell_count, cell_start, body_cell, body_arrival, body_cell1, body_arrival1, bucket, bucket_id, large_slot;
+    DBuf ent_slot, ent_pid, ent_cell, ent_own, own_scan, rows_ent, scan_tmp;
     DBuf d_ve;
     DBuf d_scenes, d_walls, d_mats, d_tanphi, d_ctr, d_part_c, d_part_i, d_bounds, d_total, d_tmp3, d_args;
     DBuf d_ctrl_cfg, d_ctrl_state, d_acc_ctrl, d_acc_ctrl2;  // the controlled cell (device-resident)
@@ -299,9 +309,14 @@ struct World {
     ChunkStart* h_chunk = nullptr;
     int ncells = 0;
     DBuf d_flag;                       // broad phase: a body's period out of the packed range
-    DBuf lflag, lscan, keys2, vals2, keys2_alt, vals2_alt;  // level 1 of a two-level grid
+    DBuf d_bpart;                      // bounds partials
+    HBuf h_read;                       // pinned: what a broad-phase run reads back
+    HBuf h_scenes;                     // pinned copy of the scene table on its way to the device
+    // entries and pairs of the last run (-1: not known for these bodies and
+    // Verlet distance): the next run sizes its launches by them and reads
+    // the true counts back once, at its end
+    int64_t last_ent = -1, last_pairs = -1;
     DBuf raw_slot, raw_pid, raw_cell, ent_body;              // row entries in the order found, and their rows
-    int morton_bits = 1, scene_bits = 0;
     int64_t rebuilds = 0;
     int64_t iter_at_rebuild = 0;       // scene 0's iteration count at the last broad-phase run
     double last_rebuild_ms = 0.0;      // wall time of the last broad-phase run
@@ -338,17 +353,20 @@ struct World {
         graphs.clear();
         for (auto& b : bs) b.release();
         for (auto& p : ps) p.release();
-        for (DBuf* d : {&slot_of_id, &d_gids, &d_state, &keys, &vals, &keys_alt, &vals_alt, &cell_start, &cell_end, &counts, &row_start,
-                        &ent_slot, &ent_pid, &ent_cell, &ent_own, &own_scan, &rows_ent, &scan_tmp, &radix_tmp,
+        for (DBuf* d : {&slot_of_id, &d_gids, &d_state, &cell_count, &cell_start, &body_cell, &body_arrival, &body_cell1, &body_arrival1,
+                        &bucket, &bucket_id, &large_slot, &counts, &row_start,
+                        &ent_slot, &ent_pid, &ent_cell, &ent_own, &own_scan, &rows_ent, &scan_tmp,
                         &d_scenes, &d_walls, &d_mats, &d_tanphi, &d_ctr, &d_part_c, &d_part_i, &d_bounds, &d_total,
                         &d_tmp3, &d_args, &d_ctrl_cfg, &d_ctrl_state, &d_acc_ctrl, &d_acc_ctrl2, &pb_ca, &pb_cb, &pb_found,
-                        &pb_flag, &pb_scan, &d_flag, &lflag, &lscan, &keys2, &vals2, &keys2_alt, &vals2_alt, &raw_slot, &raw_pid,
+                        &pb_flag, &pb_scan, &d_flag, &d_bpart, &raw_slot, &raw_pid,
                         &raw_cell, &ent_body, &d_acct})
             d->release();
         if (h_ctr) (void)hipHostFree(h_ctr);
         h_ctr = nullptr;
         h_slots_c.release();
         h_slots_i.release();
+        h_read.release();
+        h_scenes.release();
         if (h_chunk) (void)hipHostFree(h_chunk);
         h_chunk = nullptr;
         if (own_stream && stream) (void)hipStreamDestroy(stream);
@@ -798,6 +816,7 @@ struct World {
         state_set = false;
         on_device = true;
         need_rebuild = true;
+        last_ent = last_pairs = -1;
         invalidate_graphs();
     }
 
@@ -805,6 +824,14 @@ struct World {
     {
         HIPC(hipMemcpyAsync(sp.data(), d_scenes.p, sizeof(SceneParams) * sp.size(), hipMemcpyDeviceToHost, stream));
         HIPC(hipStreamSynchronize(stream));
+    }
+    // the same without waiting; the caller waits for the stream before the
+    // table is pushed again
+    void push_scene_table_async()
+    {
+        h_scenes.ensure(sizeof(SceneParams) * sp.size());
+        std::memcpy(h_scenes.p, sp.data(), sizeof(SceneParams) * sp.size());
+        HIPC(hipMemcpyAsync(d_scenes.p, h_scenes.p, sizeof(SceneParams) * sp.size(), hipMemcpyHostToDevice, stream));
     }
     void push_scene_table()
     {
@@ -827,6 +854,37 @@ struct World {
     }
 
     // ------------------------------------------------------- broad phase
+    // The largest bricks (2^bits cells a side) that pad the grid by at most
+    // half: a brick's cells, and so the bodies in memory, follow a Morton
+    // curve, and bricks follow one another along x.
+    static int64_t brick_cells(const int32_t* dims, int bits)
+    {
+        int64_t n = 1;
+        for (int k = 0; k < 3; ++k) n *= ((int64_t)dims[k] + (1 << bits) - 1) >> bits;
+        return n << (3 * bits);
+    }
+    static int brick_bits(const int32_t* dims)
+    {
+        int bits = 8;
+        while (bits > 0 && 2 * brick_cells(dims, bits) > 3 * brick_cells(dims, 0) + 512) --bits;
+        return bits;
+    }
+    // entries and pairs that the run's buffers hold now
+    int64_t ent_room() const
+    {
+        size_t b = SIZE_MAX;
+        for (const DBuf* d : {&ent_slot, &ent_pid, &ent_cell, &ent_own, &own_scan, &rows_ent, &raw_slot, &raw_pid,
+                              &raw_cell, &ent_body})
+            b = std::min(b, d->bytes);
+        return (int64_t)std::min<size_t>(b / 4, 0x7ffffff0u) - 1;
+    }
+    int64_t pair_room(bool f32) const
+    {
+        size_t n = ps[1 - pactive].room(f32);
+        for (const DBuf* d : {&pb_ca, &pb_cb, &pb_found, &pb_flag, &pb_scan}) n = std::min(n, d->bytes / 4);
+        return (int64_t)std::min<size_t>(n, kPairMask - 1) - 1;
+    }
+
     void rebuild()
     {
         const auto rb_t0 = std::chrono::steady_clock::now();
@@ -850,22 +908,27 @@ struct World {
             if (std::isfinite(rmin[s])) limit = std::min(limit, dl);
         }
         // grid per scene
-        std::vector<double> bnd(6 * (size_t)nsc, 0.0);
+        h_read.ensure(std::max(sizeof(double) * 6 * (size_t)nsc, sizeof(uint32_t) * 4));
+        const double* bnd = h_read.as<double>();
         // bounds: the grid of an aperiodic scene; in both cases the check
         // that no position went non-finite before it is binned
         if (nslots > 0) {
             d_bounds.ensure(sizeof(double) * 6 * nsc);
-            radix_tmp.ensure(std::max(radix_temp_bytes(nslots), bounds_temp_bytes(nslots)));
-            launch_bounds(bs[active].view(), nslots, nsc, d_bounds.as<double>(), radix_tmp.p, stream);
+            d_bpart.ensure(bounds_temp_bytes());
+            launch_bounds(bs[active].view(), nslots, nsc, d_bounds.as<double>(), d_bpart.p, stream);
             HIPC(hipGetLastError());
-            HIPC(hipMemcpyAsync(bnd.data(), d_bounds.p, sizeof(double) * 6 * nsc, hipMemcpyDeviceToHost, stream));
+            HIPC(hipMemcpyAsync(h_read.p, d_bounds.p, sizeof(double) * 6 * nsc, hipMemcpyDeviceToHost, stream));
             HIPC(hipStreamSynchronize(stream));
             for (int s = 0; s < nsc; ++s)
                 if (scenes[s].n_spheres > 0)
                     for (int k = 0; k < 6; ++k)
                         if (!std::isfinite(bnd[6 * s + k])) fail(DEM_ENONFINITE, "non-finite sphere position");
         }
-        int cells = 0, maxdim = 1;
+        std::vector<double> bnd_none;
+        if (nslots == 0) {
+            bnd_none.assign(6 * (size_t)nsc, 0.0);
+            bnd = bnd_none.data();
+        }
         for (int s = 0; s < nsc; ++s) {
             SceneParams& P = sp[s];
             const double dl2 = 2.0 * P.verlet;
@@ -881,16 +944,32 @@ struct World {
             // largest body of the scene reaches `far` (its largest candidate
             // distance on this level), which must stay within 2 k + 1 distinct
             // cells so that no image is visited twice.
-            auto periodic_level = [&](double h, double far, int32_t* dims, double* inv_h, double* origin,
-                                      double* cellw) -> bool {
+            // An axis has no more cells than leave the table 4 per body and 4,096
+            // (wider cells hold the same candidates).
+            auto periodic_level = [&](double h, double far, int64_t nbodies, int32_t* dims, double* inv_h,
+                                      double* origin, double* cellw) -> bool {
+                const double most = 4.0 * (double)std::max<int64_t>(nbodies, 1) + 4096.0;
+                double per_axis[3], all = 1.0;
+                for (int k = 0; k < 3; ++k) {
+                    const double rn = std::sqrt(Hinv[3 * k] * Hinv[3 * k] + Hinv[3 * k + 1] * Hinv[3 * k + 1] +
+                                                Hinv[3 * k + 2] * Hinv[3 * k + 2]);
+                    per_axis[k] = std::min(std::floor(1.0 / rn / h), (double)(1 << 20));
+                    all *= std::max(per_axis[k], 1.0);
+                }
+                const double shrink = all > most ? std::cbrt(most / all) : 1.0;
                 for (int k = 0; k < 3; ++k) {
                     const double rn = std::sqrt(Hinv[3 * k] * Hinv[3 * k] + Hinv[3 * k + 1] * Hinv[3 * k + 1] +
                                                 Hinv[3 * k + 2] * Hinv[3 * k + 2]);
                     const double width = 1.0 / rn;  // distance between opposite faces
-                    int n = (int)std::min(std::floor(width / h), (double)(1 << 20));
+                    int n = (int)per_axis[k];
                     if (n < 3) return false;
-                    const int kk = std::max(1, (int)std::ceil(far / (width / (double)n)));
+                    int kk = std::max(1, (int)std::ceil(far / (width / (double)n)));
                     if (n < 2 * kk + 1) return false;
+                    if (shrink < 1.0) {
+                        const int less = std::max((int)(shrink * n), 3);
+                        const int kl = std::max(1, (int)std::ceil(far / (width / (double)less)));
+                        if (less >= 2 * kl + 1) n = less;
+                    }
                     dims[k] = n;
                     inv_h[k] = (double)n;
                     origin[k] = 0.0;
@@ -962,8 +1041,9 @@ struct World {
                 const double h0 = (2.0 * rs + dl2) * (1.0 + 1e-9);
                 bool ok;
                 if (periodic) {
-                    ok = periodic_level(h0, (rmax[s] + rs) + dl2, P.dims, P.inv_h, P.origin, P.cellw) &&
-                         periodic_level(hmax, 2.0 * rmax[s] + dl2, P.dims2, P.inv_h2, P.origin2, P.cellw2);
+                    ok = periodic_level(h0, (rmax[s] + rs) + dl2, scenes[s].n_spheres, P.dims, P.inv_h, P.origin, P.cellw) &&
+                         periodic_level(hmax, 2.0 * rmax[s] + dl2, scenes[s].n_large, P.dims2, P.inv_h2, P.origin2,
+                                        P.cellw2);
                 } else {
                     box_level(h0, scenes[s].n_spheres - scenes[s].n_large, P.dims, P.inv_h, P.origin, P.cellw);
                     box_level(hmax, scenes[s].n_large, P.dims2, P.inv_h2, P.origin2, P.cellw2);
@@ -973,18 +1053,15 @@ struct World {
             }
             if (rs == 0.0) {
                 if (periodic) {
-                    if (!periodic_level(hmax, 2.0 * rmax[s] + dl2, P.dims, P.inv_h, P.origin, P.cellw))
+                    if (!periodic_level(hmax, 2.0 * rmax[s] + dl2, scenes[s].n_spheres, P.dims, P.inv_h, P.origin, P.cellw))
                         fail(DEM_EPERIODIC, "periodic cell narrower than 3 x (2 r_max + 2 Delta L) along an axis");
                 } else {
                     box_level(hmax, scenes[s].n_spheres, P.dims, P.inv_h, P.origin, P.cellw);
                 }
             }
             P.r_split = rs;
-            P.cell_offset = cells;
-            cells += P.dims[0] * P.dims[1] * P.dims[2];
-            P.cell_offset2 = cells;
-            if (rs > 0.0) cells += P.dims2[0] * P.dims2[1] * P.dims2[2];
-            for (int k = 0; k < 3; ++k) maxdim = std::max({maxdim, P.dims[k], rs > 0.0 ? P.dims2[k] : 1});
+            P.brick_bits = brick_bits(P.dims);
+            P.brick_bits2 = brick_bits(P.dims2);
             // mean-field share of the Verlet budget (periodic)
             double lf = 0.0;
             for (int k = 0; k < 9; ++k) lf += P.L[k] * P.L[k];
@@ -992,186 +1069,194 @@ struct World {
             scenes[s].rmax = rmax[s];
             P.rmax = rmax[s];
         }
-        ncells = std::max(cells, 1);
-        morton_bits = 1;
-        while ((1 << morton_bits) < maxdim) ++morton_bits;
-        scene_bits = 0;
-        if (nsc > 1)
-            while ((1 << scene_bits) < nsc) ++scene_bits;
-        // key: scene bits | 3 x morton_bits (either level's cell)
-        if (3 * morton_bits + scene_bits > 64) fail(DEM_EINVAL, "grid too large for 64-bit cell keys");
+        // the cell table: every scene's level-0 cells, then the level-1 cells
+        int64_t cells = 0;
+        for (int lv = 0; lv < 2; ++lv)
+            for (int s = 0; s < nsc; ++s) {
+                SceneParams& P = sp[s];
+                (lv == 0 ? P.cell_offset : P.cell_offset2) = (int32_t)cells;
+                if (lv == 1 && !(P.r_split > 0.0)) continue;
+                cells += lv == 0 ? brick_cells(P.dims, P.brick_bits) : brick_cells(P.dims2, P.brick_bits2);
+                if (cells > 0x7ffffff0LL) fail(DEM_EINVAL, "broad-phase grid too large");
+            }
+        ncells = (int)std::max<int64_t>(cells, 1);
         int64_t nlarge = 0;
         for (int s = 0; s < nsc; ++s)
             if (sp[s].r_split > 0.0) nlarge += scenes[s].n_large;
-        push_scene_table();
+        if (nslots > 0)
+            push_scene_table_async();
+        else
+            push_scene_table();
 
         Counters& C = *h_ctr;
         int npairs_new = 0;
+        bool slots_fetched = false;
         if (nslots > 0) {
+            const int ng = (int)bodies.size();
+            const bool f32 = precision == DEM_FP32_MIXED;
             GridArgs g;
             g.bod = bs[active].view();
             g.scenes = d_scenes.as<SceneParams>();
             g.scene0 = sp[0];
             g.nscenes = nsc;
             g.nslots = nslots;
-            g.scene_bits = scene_bits;
-            g.morton_bits = morton_bits;
-            // keys, sort, permute into the other body set
-            keys.ensure(8 * (size_t)nslots);
-            vals.ensure(4 * (size_t)nslots);
-            keys_alt.ensure(8 * (size_t)nslots);
-            vals_alt.ensure(4 * (size_t)nslots);
-            radix_tmp.ensure(std::max(radix_temp_bytes(nslots), bounds_temp_bytes(nslots)));
             d_flag.ensure(4);
             g.period_range = d_flag.as<int32_t>();
-            HIPC(hipMemsetAsync(d_flag.p, 0, 4, stream));
-            launch_keys(g, keys.as<uint64_t>(), vals.as<uint32_t>(), stream);
+            g.large_slot = nullptr;
+            // the bodies into cell order, in the other body set
+            CellSortArgs cs{};
+            cell_count.ensure(4 * (size_t)ncells);
+            cell_start.ensure(4 * ((size_t)ncells + 1));
+            for (DBuf* d : {&body_cell, &body_arrival, &bucket, &bucket_id}) d->ensure(4 * (size_t)nslots);
+            if (nlarge > 0) {
+                body_cell1.ensure(4 * (size_t)nslots);
+                body_arrival1.ensure(4 * (size_t)nslots);
+                large_slot.ensure(4 * (size_t)nlarge);
+            }
+            cs.count = cell_count.as<uint32_t>();
+            cs.start = cell_start.as<uint32_t>();
+            cs.cell = body_cell.as<uint32_t>();
+            cs.arrival = body_arrival.as<uint32_t>();
+            cs.cell1 = body_cell1.as<uint32_t>();
+            cs.arrival1 = body_arrival1.as<uint32_t>();
+            cs.bucket = bucket.as<uint32_t>();
+            cs.bucket_id = bucket_id.as<int32_t>();
+            cs.large_slot = large_slot.as<uint32_t>();
+            cs.ncells = ncells;
+            cs.nlarge = (int)nlarge;
+            scan_tmp.ensure(scan_temp_bytes(std::max(ncells, nslots)));
+            if (periodic) HIPC(hipMemsetAsync(d_flag.p, 0, 4, stream));
+            launch_cell_count(g, cs, periodic, stream);
             if (periodic) {
-                int32_t far = 0;
-                HIPC(hipMemcpyAsync(&far, d_flag.p, 4, hipMemcpyDeviceToHost, stream));
+                int32_t* far = h_read.as<int32_t>();
+                HIPC(hipMemcpyAsync(far, d_flag.p, 4, hipMemcpyDeviceToHost, stream));
                 HIPC(hipStreamSynchronize(stream));
-                if (far)
+                if (*far)
                     fail(DEM_EPERIODIC, "a sphere is more than 511 periods from the periodic cell's origin; "
                                         "bring the positions back into the cell (dem_set_state)");
             }
-            bool in_alt = false;
-            radix_sort_pairs(keys.as<uint64_t>(), vals.as<uint32_t>(), keys_alt.as<uint64_t>(), vals_alt.as<uint32_t>(),
-                             nslots, 3 * morton_bits + scene_bits, radix_tmp.p, stream, &in_alt);
-            const uint64_t* skeys = in_alt ? keys_alt.as<uint64_t>() : keys.as<uint64_t>();
-            const uint32_t* order = in_alt ? vals_alt.as<uint32_t>() : vals.as<uint32_t>();
-            launch_permute(bs[active].view(), bs[1 - active].view(), order, nslots, batched(), periodic,
-                           slot_of_id.as<int32_t>(), stream);
+            PairSet& NP = ps[1 - pactive];
+            PairSet& OP = ps[pactive];
+            NP.own_begin.ensure(4 * (size_t)std::max(ng, 1));
+            NP.own_count.ensure(4 * (size_t)std::max(ng, 1));
+            launch_cell_place(g, cs, bs[1 - active].view(), periodic, slot_of_id.as<int32_t>(),
+                              NP.own_begin.as<int32_t>(), NP.own_count.as<int32_t>(), scan_tmp.p, stream);
             active = 1 - active;
             g.bod = bs[active].view();
-            // cells
-            cell_start.ensure(4 * (size_t)ncells);
-            cell_end.ensure(4 * (size_t)ncells);
-            launch_cells(g, skeys, cell_start.as<uint32_t>(), cell_end.as<uint32_t>(), ncells, stream);
-            g.large_slot = nullptr;
-            if (nlarge > 0) {
-                // level 1: the spheres above r_split, their slots sorted by
-                // coarse cell (the bodies stay in level-0 order)
-                lflag.ensure(4 * ((size_t)nslots + 1));
-                lscan.ensure(4 * ((size_t)nslots + 1));
-                keys2.ensure(8 * (size_t)nlarge);
-                vals2.ensure(4 * (size_t)nlarge);
-                keys2_alt.ensure(8 * (size_t)nlarge);
-                vals2_alt.ensure(4 * (size_t)nlarge);
-                scan_tmp.ensure(scan_temp_bytes(nslots + 1));
-                d_total.ensure(16);
-                launch_large_flags(g, lflag.as<uint32_t>(), stream);
-                HIPC(hipMemsetAsync(lflag.as<uint32_t>() + nslots, 0, 4, stream));
-                exclusive_scan_u32(lflag.as<uint32_t>(), lscan.as<uint32_t>(), nslots + 1, scan_tmp.p,
-                                   d_total.as<uint32_t>(), stream);
-                launch_large_keys(g, lscan.as<uint32_t>(), keys2.as<uint64_t>(), vals2.as<uint32_t>(), stream);
-                bool alt2 = false;
-                radix_sort_pairs(keys2.as<uint64_t>(), vals2.as<uint32_t>(), keys2_alt.as<uint64_t>(),
-                                 vals2_alt.as<uint32_t>(), (int)nlarge, 3 * morton_bits + scene_bits, radix_tmp.p,
-                                 stream, &alt2);
-                const uint64_t* sk2 = alt2 ? keys2_alt.as<uint64_t>() : keys2.as<uint64_t>();
-                launch_cells_large(g, sk2, (int)nlarge, cell_start.as<uint32_t>(), cell_end.as<uint32_t>(), ncells,
-                                   stream);
-                g.large_slot = alt2 ? vals2_alt.as<uint32_t>() : vals2.as<uint32_t>();
-            }
-            // sweep: count, scan, fill
+            if (nlarge > 0) g.large_slot = large_slot.as<uint32_t>();
+            // sweep: count, scan
             SweepArgs sw{};
             sw.g = g;
             sw.nlarge = (int)nlarge;
             sw.cell_start = cell_start.as<uint32_t>();
-            sw.cell_end = cell_end.as<uint32_t>();
             sw.walls = d_walls.as<Wall>();
-            counts.ensure(4 * ((size_t)nslots + 1));
+            counts.ensure(4 * (size_t)nslots);
             row_start.ensure(4 * ((size_t)nslots + 1));
-            HIPC(hipMemsetAsync(counts.as<uint32_t>() + nslots, 0, 4, stream));
             sw.count = counts.as<uint32_t>();
+            sw.row_start = row_start.as<int32_t>();
             launch_sweep_count(sw, stream);
             d_total.ensure(16);
-            scan_tmp.ensure(scan_temp_bytes(nslots + 1));
-            exclusive_scan_u32(counts.as<uint32_t>(), row_start.as<uint32_t>(), nslots + 1, scan_tmp.p,
-                               d_total.as<uint32_t>(), stream);
-            uint32_t nent = 0;
-            HIPC(hipMemcpyAsync(&nent, d_total.p, 4, hipMemcpyDeviceToHost, stream));
-            HIPC(hipStreamSynchronize(stream));
-            HIPC(hipGetLastError());
-            if (nent > 0x7ffffff0u) fail(DEM_ENOMEM, "too many candidate entries");
-            ent_slot.ensure(4 * ((size_t)nent + 1));
-            ent_pid.ensure(4 * ((size_t)nent + 1));
-            ent_cell.ensure(4 * ((size_t)nent + 1));
-            ent_own.ensure(4 * ((size_t)nent + 1));
-            own_scan.ensure(4 * ((size_t)nent + 1));
-            rows_ent.ensure(4 * ((size_t)nent + 1));
-            raw_slot.ensure(4 * ((size_t)nent + 1));
-            raw_pid.ensure(4 * ((size_t)nent + 1));
-            raw_cell.ensure(4 * ((size_t)nent + 1));
-            ent_body.ensure(4 * ((size_t)nent + 1));
-            sw.row_start = row_start.as<int32_t>();
-            sw.raw_slot = raw_slot.as<int32_t>();
-            sw.raw_pid = raw_pid.as<int32_t>();
-            sw.raw_cell = raw_cell.as<int32_t>();
-            sw.ent_body = ent_body.as<int32_t>();
-            sw.nent = (int)nent;
-            sw.ent_slot = ent_slot.as<int32_t>();
-            sw.ent_pid = ent_pid.as<int32_t>();
-            sw.ent_cell = ent_cell.as<int32_t>();
-            sw.ent_own = ent_own.as<uint32_t>();
-            sw.max_row = 0;
-            launch_sweep_fill(sw, stream);
-            HIPC(hipMemsetAsync(ent_own.as<uint32_t>() + nent, 0, 4, stream));
-            scan_tmp.ensure(scan_temp_bytes((int)nent + 1));
-            exclusive_scan_u32(ent_own.as<uint32_t>(), own_scan.as<uint32_t>(), (int)nent + 1, scan_tmp.p,
-                               d_total.as<uint32_t>(), stream);
-            uint32_t np = 0;
-            HIPC(hipMemcpyAsync(&np, d_total.p, 4, hipMemcpyDeviceToHost, stream));
-            HIPC(hipStreamSynchronize(stream));
-            HIPC(hipGetLastError());
+            uint32_t* const d_nent = d_total.as<uint32_t>();
+            uint32_t* const d_np = d_nent + 1;
+            uint32_t* const h_n = h_read.as<uint32_t>();  // entries, pairs
+            exclusive_scan_u32(counts.as<uint32_t>(), row_start.as<uint32_t>(), nslots, nullptr, scan_tmp.p, d_nent,
+                               stream);
+            // What follows is sized either by the counts, read back one after
+            // the other, or by those of the last run with an eighth to spare:
+            // then both are read at the end, and in the rare case that they
+            // did not fit the kernels have returned at once and run again.
+            int64_t lim_ent = 0, lim_pairs = 0;
+            bool sized = false;
+            if (last_ent >= 0) {
+                lim_ent = std::min<int64_t>(last_ent + last_ent / 8 + 1024, ent_room());
+                lim_pairs = std::min<int64_t>(last_pairs + last_pairs / 8 + 1024, pair_room(f32));
+            }
+            for (;;) {
+                const bool guess = !sized && last_ent >= 0 && lim_ent > 0 && lim_pairs > 0;
+                if (!guess) {
+                    HIPC(hipMemcpyAsync(h_n, d_nent, 4, hipMemcpyDeviceToHost, stream));
+                    HIPC(hipStreamSynchronize(stream));
+                    HIPC(hipGetLastError());
+                    if (h_n[0] > 0x7ffffff0u) fail(DEM_ENOMEM, "too many candidate entries");
+                    lim_ent = h_n[0];
+                    for (DBuf* d : {&ent_slot, &ent_pid, &ent_cell, &ent_own, &own_scan, &rows_ent, &raw_slot,
+                                    &raw_pid, &raw_cell, &ent_body})
+                        d->ensure(4 * ((size_t)lim_ent + 1));
+                }
+                sw.raw_slot = raw_slot.as<int32_t>();
+                sw.raw_pid = raw_pid.as<int32_t>();
+                sw.raw_cell = raw_cell.as<int32_t>();
+                sw.ent_body = ent_body.as<int32_t>();
+                sw.ent_slot = ent_slot.as<int32_t>();
+                sw.ent_pid = ent_pid.as<int32_t>();
+                sw.ent_cell = ent_cell.as<int32_t>();
+                sw.ent_own = ent_own.as<uint32_t>();
+                sw.nent_dev = d_nent;
+                sw.lim_ent = (int32_t)lim_ent;
+                launch_sweep_fill(sw, stream);
+                scan_tmp.ensure(scan_temp_bytes((int)lim_ent));
+                exclusive_scan_u32(ent_own.as<uint32_t>(), own_scan.as<uint32_t>(), (int)lim_ent, d_nent, scan_tmp.p,
+                                   d_np, stream);
+                if (!guess) {
+                    HIPC(hipMemcpyAsync(h_n + 1, d_np, 4, hipMemcpyDeviceToHost, stream));
+                    HIPC(hipStreamSynchronize(stream));
+                    HIPC(hipGetLastError());
+                    if (h_n[1] >= kPairMask) fail(DEM_ENOMEM, "too many candidate pairs");
+                    lim_pairs = h_n[1];
+                    NP.ensure((size_t)lim_pairs, f32);
+                    for (DBuf* d : {&pb_ca, &pb_cb, &pb_found, &pb_flag, &pb_scan})
+                        d->ensure(4 * ((size_t)lim_pairs + 1));
+                }
+                PairBuildArgs pb;
+                pb.bod = g.bod;
+                pb.row_start = row_start.as<int32_t>();
+                pb.ent_slot = ent_slot.as<int32_t>();
+                pb.ent_pid = ent_pid.as<int32_t>();
+                pb.ent_cell = ent_cell.as<int32_t>();
+                pb.own_scan = own_scan.as<uint32_t>();
+                pb.ent_own = ent_own.as<uint32_t>();
+                pb.ent_body = ent_body.as<int32_t>();
+                pb.rows.start = row_start.as<int32_t>();
+                pb.rows.ent = rows_ent.as<uint32_t>();
+                pb.pr = NP.view();
+                pb.hist_new = NP.history();
+                pb.hist_old = OP.history();
+                pb.ca = pb_ca.as<int32_t>();
+                pb.cb = pb_cb.as<int32_t>();
+                pb.found = pb_found.as<int32_t>();
+                pb.flag = pb_flag.as<uint32_t>();
+                pb.flag_scan = pb_scan.as<uint32_t>();
+                pb.nslots = nslots;
+                pb.nent_dev = d_nent;
+                pb.npairs_dev = d_np;
+                pb.lim_ent = (int32_t)lim_ent;
+                pb.lim_pairs = (int32_t)lim_pairs;
+                pb.has_old = (OP.cap > 0 && OP.own_begin.p && old_ngids > 0) ? 1 : 0;
+                pb.hist_f32 = f32 ? 1 : 0;
+                launch_pair_build(pb, stream);
+                launch_carry_find(pb, stream, std::min(old_ngids, ng));
+                // touching pairs first: ranks from a scan of the carried flags
+                scan_tmp.ensure(scan_temp_bytes((int)lim_pairs));
+                exclusive_scan_u32(pb.flag, pb.flag_scan, (int)lim_pairs, d_np, scan_tmp.p, nullptr, stream);
+                launch_partition(pb, stream);
+                HIPC(hipGetLastError());
+                if (!guess) break;
+                // the slots' read-back (fold_slots) is waited for with the counts
+                fetch_slots();
+                slots_fetched = true;
+                HIPC(hipMemcpyAsync(h_n, d_nent, 8, hipMemcpyDeviceToHost, stream));
+                HIPC(hipStreamSynchronize(stream));
+                HIPC(hipGetLastError());
+                if ((int64_t)h_n[0] <= lim_ent && (int64_t)h_n[1] <= lim_pairs) break;
+                sized = true;  // run again from the fill, by the true counts
+            }
+            const size_t np = h_n[1];
             if (np >= kPairMask) fail(DEM_ENOMEM, "too many candidate pairs");
             npairs_new = (int)np;
-            n_candidates = np;
-            // new pair set
-            PairSet& NP = ps[1 - pactive];
-            PairSet& OP = ps[pactive];
-            NP.ensure(np, precision == DEM_FP32_MIXED);
-            const int ng = (int)bodies.size();
-            NP.own_begin.ensure(4 * (size_t)std::max(ng, 1));
-            NP.own_count.ensure(4 * (size_t)std::max(ng, 1));
-            HIPC(hipMemsetAsync(NP.own_begin.p, 0, 4 * (size_t)std::max(ng, 1), stream));
-            HIPC(hipMemsetAsync(NP.own_count.p, 0, 4 * (size_t)std::max(ng, 1), stream));
-            PairBuildArgs pb;
-            pb.bod = g.bod;
-            pb.row_start = row_start.as<int32_t>();
-            pb.ent_slot = ent_slot.as<int32_t>();
-            pb.ent_pid = ent_pid.as<int32_t>();
-            pb.ent_cell = ent_cell.as<int32_t>();
-            pb.own_scan = own_scan.as<uint32_t>();
-            pb.ent_own = ent_own.as<uint32_t>();
-            pb.ent_body = ent_body.as<int32_t>();
-            pb.rows.start = row_start.as<int32_t>();
-            pb.rows.ent = rows_ent.as<uint32_t>();
-            pb.pr = NP.view();
-            pb.hist_new = NP.history();
-            pb.hist_old = OP.history();
-            pb_ca.ensure(4 * ((size_t)np + 1));
-            pb_cb.ensure(4 * ((size_t)np + 1));
-            pb_found.ensure(4 * ((size_t)np + 1));
-            pb_flag.ensure(4 * ((size_t)np + 1));
-            pb_scan.ensure(4 * ((size_t)np + 1));
-            pb.ca = pb_ca.as<int32_t>();
-            pb.cb = pb_cb.as<int32_t>();
-            pb.found = pb_found.as<int32_t>();
-            pb.flag = pb_flag.as<uint32_t>();
-            pb.flag_scan = pb_scan.as<uint32_t>();
-            pb.nslots = nslots;
-            pb.nent = (int)nent;
-            pb.npairs = (int)np;
-            pb.has_old = (OP.cap > 0 && OP.own_begin.p && old_ngids > 0) ? 1 : 0;
-            pb.hist_f32 = precision == DEM_FP32_MIXED ? 1 : 0;
-            launch_pair_build(pb, stream);
-            launch_carry_find(pb, stream, std::min(old_ngids, ng));
-            // touching pairs first: ranks from a scan of the carried flags
-            scan_tmp.ensure(scan_temp_bytes((int)np + 1));
-            exclusive_scan_u32(pb.flag, pb.flag_scan, (int)np + 1, scan_tmp.p, d_total.as<uint32_t>(), stream);
-            launch_partition(pb, stream);
-            HIPC(hipGetLastError());
+            n_candidates = (int64_t)np;
+            last_ent = h_n[0];
+            last_pairs = (int64_t)np;
+            NP.cap = std::max<size_t>(np, 1);
             pactive = 1 - pactive;
             old_ngids = ng;
             // The previous list is not read again once this run's kernels
@@ -1179,7 +1264,7 @@ struct World {
             // run (which fills it) allocates nothing.  A buffer it outgrows
             // is freed by hipFree, which waits for the device first.
             PairSet& spare = ps[1 - pactive];
-            spare.ensure(np, precision == DEM_FP32_MIXED);
+            spare.ensure(np + np / 8 + 1024, f32);
             spare.own_begin.ensure(4 * (size_t)std::max(ng, 1));
             spare.own_count.ensure(4 * (size_t)std::max(ng, 1));
         } else {
@@ -1191,7 +1276,7 @@ struct World {
         }
         npairs = npairs_new;
         // fold the per-block slots before the grids change, then size them
-        fold_slots();
+        fold_slots(slots_fetched);
         // the contact kernel gives each of the 8 XCDs one eighth of the
         // pairs: at least ceil(ceil(npairs / 8) / block) blocks per XCD
         const int per_xcd = (int)((((int64_t)npairs + 7) / 8 + block_contact - 1) / block_contact);
@@ -1200,8 +1285,6 @@ struct World {
         grid_i = std::max((nslots + block_integrate - 1) / block_integrate, 1);
         d_part_c.ensure(sizeof(ContactAcc) * (size_t)grid_c);
         d_part_i.ensure(sizeof(IntAcc) * (size_t)grid_i);
-        HIPC(hipMemsetAsync(d_part_c.p, 0, sizeof(ContactAcc) * (size_t)grid_c, stream));
-        HIPC(hipMemsetAsync(d_part_i.p, 0, sizeof(IntAcc) * (size_t)grid_i, stream));
         acc_c_n = grid_c;
         acc_i_n = grid_i;
         // counters: fresh Verlet budget, flags clear, parity 0 (every field
@@ -1216,15 +1299,19 @@ struct World {
         C.iter0 = scenes[0].iter;
         C.nonfinite = 0;  // positions are finite (checked above); an earlier
         C.unstable = 0;   // failure was repaired with dem_set_state
+        C.measure = 0;
         next_parity = 0;
-        HIPC(hipMemcpyAsync(d_ctr.p, h_ctr, sizeof(Counters), hipMemcpyHostToDevice, stream));
-        HIPC(hipStreamSynchronize(stream));
-        upload_args();
+        // the descriptor, the counters and clear slots in one launch
+        d_acc_ctrl.ensure(sizeof(double) * (size_t)kNetworkWords * std::max(grid_c, 1));
+        d_acc_ctrl2.ensure(sizeof(double) * (size_t)(kNetworkWords + 2) * kCtrlReduceGrid);
+        d_args.ensure(sizeof(StepArgs));
+        launch_publish(step_args(), C, d_args.as<StepArgs>(), grid_c, grid_i, stream);
+        HIPC(hipGetLastError());
         need_rebuild = false;
         state_set = false;
         ++rebuilds;
         iter_at_rebuild = scenes[0].iter;
-        // the run ends with a synchronisation: its wall time is its cost
+        // what is left of the run on the device is two short launches
         last_rebuild_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - rb_t0).count();
         rebuild_ms_total += last_rebuild_ms;
     }
@@ -1263,20 +1350,27 @@ struct World {
         double el = 0, plast = 0, kin = 0, rot = 0, grav = 0, damp = 0, visc = 0;
         unsigned long long ss = 0, sw = 0, cum = 0;
     };
-    SlotSums read_slots()
+    void fetch_slots()
     {
-        SlotSums t;
         h_slots_c.ensure(sizeof(ContactAcc) * (size_t)std::max(acc_c_n, 1));
         h_slots_i.ensure(sizeof(IntAcc) * (size_t)std::max(acc_i_n, 1));
-        const ContactAcc* c = h_slots_c.as<ContactAcc>();
-        const IntAcc* i = h_slots_i.as<IntAcc>();
         if (acc_c_n)
             HIPC(hipMemcpyAsync(h_slots_c.p, d_part_c.p, sizeof(ContactAcc) * (size_t)acc_c_n, hipMemcpyDeviceToHost,
                                 stream));
         if (acc_i_n)
             HIPC(hipMemcpyAsync(h_slots_i.p, d_part_i.p, sizeof(IntAcc) * (size_t)acc_i_n, hipMemcpyDeviceToHost,
                                 stream));
-        HIPC(hipStreamSynchronize(stream));
+    }
+    // `fetched`: the slots were fetched since the last step and the stream waited for
+    SlotSums read_slots(bool fetched = false)
+    {
+        if (!fetched) {
+            fetch_slots();
+            HIPC(hipStreamSynchronize(stream));
+        }
+        SlotSums t;
+        const ContactAcc* c = h_slots_c.as<ContactAcc>();
+        const IntAcc* i = h_slots_i.as<IntAcc>();
         for (int k = 0; k < acc_c_n; ++k) {
             const ContactAcc& a = c[k];
             t.el += a.el;
@@ -1295,10 +1389,10 @@ struct World {
         }
         return t;
     }
-    void fold_slots()
+    void fold_slots(bool fetched)
     {
         if (!acc_c_n && !acc_i_n) return;
-        const SlotSums t = read_slots();
+        const SlotSums t = read_slots(fetched);
         base_plast += t.plast;
         base_visc += t.visc;
         base_grav += t.grav;
@@ -1384,6 +1478,7 @@ struct World {
         if (t.verlet_factor > 0.0) {
             for (auto& S : scenes) S.p.verlet_dist = -t.verlet_factor;
             need_rebuild = true;
+            last_ent = last_pairs = -1;
         }
         // the contact grid follows the block size at the next run
         grid_c = 0;
@@ -2014,10 +2109,10 @@ struct World {
         // the pair build's scratch is free between broad-phase runs
         pb_flag.ensure(4 * (np + 1));
         pb_scan.ensure(4 * (np + 1));
-        scan_tmp.ensure(scan_temp_bytes(npairs + 1));
+        scan_tmp.ensure(scan_temp_bytes(npairs));
         d_total.ensure(16);
         launch_wall_flags(a, precision, pb_flag.as<uint32_t>(), stream);
-        exclusive_scan_u32(pb_flag.as<uint32_t>(), pb_scan.as<uint32_t>(), npairs + 1, scan_tmp.p,
+        exclusive_scan_u32(pb_flag.as<uint32_t>(), pb_scan.as<uint32_t>(), npairs, nullptr, scan_tmp.p,
                            d_total.as<uint32_t>(), stream);
         uint32_t n = 0;
         HIPC(hipMemcpyAsync(&n, d_total.p, 4, hipMemcpyDeviceToHost, stream));
