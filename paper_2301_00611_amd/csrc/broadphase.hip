@@ -1,10 +1,10 @@
 // broadphase.hip -- the collider's role (section 2.1.1, InsertionSortCollider)
 // rebuilt for the GPU: bodies are binned in cells no smaller than the largest
 // candidate distance (2 r_max + 2 Delta L), put in cell order by a counting
-// sort (cells are numbered along Morton bricks, bodies of a cell by id), and
-// each body sweeps the 27 cells around its own for candidates whose enlarged
-// spheres overlap (distance < r_i + r_j + 2 Delta L).  The run is
-// needed only when some body may have moved farther than Delta L since the
+// sort (cells are numbered along Morton bricks, a cell's bodies keep their
+// order), and each body sweeps the 27 cells around its own for candidates
+// whose enlarged spheres overlap (distance < r_i + r_j + 2 Delta L).  The run
+// is needed only when some body may have moved farther than Delta L since the
 // last one (eq. 2.3-2.4).  Candidate pairs are stored once (owner = #1 of the
 // contact); every body keeps a row of its candidate pairs sorted by partner
 // id, and the shear history of surviving pairs is carried over by id.
@@ -228,8 +228,9 @@ __global__ void k_bounds_decode(unsigned long long* __restrict__ bits, double* _
 // The bodies go to cell order in three passes around a scan of the cells'
 // counts: every body counts itself in its cell (and a large one in its
 // level-1 cell), takes a place in the cell in the order of arrival, and is
-// moved to its rank by id among the bodies of its cell.  The order of
-// arrival depends on the atomics, the final order does not.  The level-1
+// moved to its rank by its old slot among the bodies of its cell (a stable
+// sort).  The order of arrival depends on the atomics, the final order does
+// not.  The level-1
 // index array keeps the order of arrival: only the order in which a search
 // meets its candidates depends on it, and rows are sorted.  Against a radix
 // sort of 64-bit keys (five launches per 8 bits, twice with two levels) the
@@ -272,15 +273,13 @@ __global__ void __launch_bounds__(kBlock) k_cell_bucket(GridArgs g, CellSortArgs
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= g.nslots) return;
-    const uint32_t pos = c.start[c.cell[i]] + c.arrival[i];
-    c.bucket[pos] = (uint32_t)i;
-    c.bucket_id[pos] = g.bod.id[i];
+    c.bucket[c.start[c.cell[i]] + c.arrival[i]] = (uint32_t)i;
 }
 
 // ----------------------------------------------------------------- permute
 
 // One thread per place of the bucket order: the body there moves to its rank
-// by id in its cell.  Also clears the next pair list's range of every body
+// by old slot in its cell.  Also clears the next pair list's range of every body
 // (a body without pairs keeps the empty one).
 template <bool BATCHED>
 __global__ void __launch_bounds__(kBlock) k_permute(GridArgs g, CellSortArgs c, Bodies dst, int periodic,
@@ -291,12 +290,12 @@ __global__ void __launch_bounds__(kBlock) k_permute(GridArgs g, CellSortArgs c, 
     if (t >= g.nslots) return;
     const Bodies& src = g.bod;
     const uint32_t o = c.bucket[t];
-    const int32_t id = c.bucket_id[t];
+    const int32_t id = src.id[o];
     const uint32_t lin = c.cell[o];
     const uint32_t beg = c.start[lin], end = c.start[lin + 1];
     const double4 xr = src.xr[o];
     uint32_t i = beg;
-    for (uint32_t q = beg; q < end; ++q) i += c.bucket_id[q] < id ? 1u : 0u;
+    for (uint32_t q = beg; q < end; ++q) i += c.bucket[q] < o ? 1u : 0u;
     dst.xr[i] = xr;
     const double4 v = src.vm[o];
     dst.vm[i] = make_double4(v.x, v.y, v.z, 0.0);  // a fresh Verlet account after every broad-phase run

@@ -89,7 +89,8 @@ struct Wall {
 // and the contact kernel).  Box: the clamp of x to [lo, hi]; `inside` when x
 // is in the box.  Triangle: the region test over vertices, edges and face
 // by the signs of the barycentric quantities (Ericson, Real-Time Collision
-// Detection, section 5.1.5).
+// Detection, section 5.1.5), its products and sums fused as written, the same
+// wherever it is inlined.
 __device__ inline void box_closest(const Wall& W, const double* x, double* p, bool* inside)
 {
     bool in = true;
@@ -112,7 +113,9 @@ __device__ inline void facet_closest(const Wall& W, const double* x, double* p)
         ac[k] = c[k] - a[k];
         ap[k] = x[k] - a[k];
     }
-    auto dot = [](const double* u, const double* v) { return (u[0] * v[0] + u[1] * v[1]) + u[2] * v[2]; };
+    auto dot = [](const double* u, const double* v) {
+        return __builtin_fma(u[2], v[2], __builtin_fma(u[0], v[0], u[1] * v[1]));
+    };
     const double d1 = dot(ab, ap), d2 = dot(ac, ap);
     if (d1 <= 0.0 && d2 <= 0.0) {
         for (int k = 0; k < 3; ++k) p[k] = a[k];
@@ -125,10 +128,10 @@ __device__ inline void facet_closest(const Wall& W, const double* x, double* p)
         for (int k = 0; k < 3; ++k) p[k] = b[k];
         return;
     }
-    const double vc = d1 * d4 - d3 * d2;
+    const double vc = __builtin_fma(d1, d4, -(d3 * d2));
     if (vc <= 0.0 && d1 >= 0.0 && d3 <= 0.0) {
         const double t = d1 / (d1 - d3);
-        for (int k = 0; k < 3; ++k) p[k] = a[k] + t * ab[k];
+        for (int k = 0; k < 3; ++k) p[k] = __builtin_fma(t, ab[k], a[k]);
         return;
     }
     double cp[3];
@@ -138,21 +141,21 @@ __device__ inline void facet_closest(const Wall& W, const double* x, double* p)
         for (int k = 0; k < 3; ++k) p[k] = c[k];
         return;
     }
-    const double vb = d5 * d2 - d1 * d6;
+    const double vb = __builtin_fma(d5, d2, -(d1 * d6));
     if (vb <= 0.0 && d2 >= 0.0 && d6 <= 0.0) {
         const double t = d2 / (d2 - d6);
-        for (int k = 0; k < 3; ++k) p[k] = a[k] + t * ac[k];
+        for (int k = 0; k < 3; ++k) p[k] = __builtin_fma(t, ac[k], a[k]);
         return;
     }
-    const double va = d3 * d6 - d5 * d4;
+    const double va = __builtin_fma(d3, d6, -(d5 * d4));
     if (va <= 0.0 && (d4 - d3) >= 0.0 && (d5 - d6) >= 0.0) {
         const double t = (d4 - d3) / ((d4 - d3) + (d5 - d6));
-        for (int k = 0; k < 3; ++k) p[k] = b[k] + t * (c[k] - b[k]);
+        for (int k = 0; k < 3; ++k) p[k] = __builtin_fma(t, c[k] - b[k], b[k]);
         return;
     }
     const double den = 1.0 / ((va + vb) + vc);
     const double v = vb * den, w = vc * den;
-    for (int k = 0; k < 3; ++k) p[k] = (a[k] + ab[k] * v) + ac[k] * w;
+    for (int k = 0; k < 3; ++k) p[k] = __builtin_fma(ac[k], w, __builtin_fma(ab[k], v, a[k]));
 }
 
 // Distance from x to a box or triangle (0 inside a box): the broad phase's
@@ -168,7 +171,7 @@ __device__ inline double boundary_distance(const Wall& W, const double* x)
         facet_closest(W, x, p);
     }
     const double d0 = x[0] - p[0], d1 = x[1] - p[1], d2 = x[2] - p[2];
-    return sqrt((d0 * d0 + d1 * d1) + d2 * d2);
+    return sqrt(__builtin_fma(d2, d2, __builtin_fma(d0, d0, d1 * d1)));
 }
 
 // Material constants as the kernels need them.
@@ -462,8 +465,7 @@ struct CellSortArgs {
     uint32_t* arrival;
     uint32_t* cell1;           // per large body: the same on level 1 (null without one)
     uint32_t* arrival1;
-    uint32_t* bucket;          // bodies in cell order, in the order of arrival, and their ids
-    int32_t* bucket_id;
+    uint32_t* bucket;          // bodies in cell order, in the order of arrival
     uint32_t* large_slot;
     int32_t ncells;
     int32_t nlarge;

@@ -281,7 +281,7 @@ struct World {
     int old_ngids = 0;                 // gids covered by the active own arrays
     DBuf slot_of_id, d_gids, d_state, counts, row_start;
     // the counting sort: cell table (counts, starts), per body its cell and order of arrival, bucket order
-    DBuf cell_count, cell_start, body_cell, body_arrival, body_cell1, body_arrival1, bucket, bucket_id, large_slot;
+    DBuf cell_count, cell_start, body_cell, body_arrival, body_cell1, body_arrival1, bucket, large_slot;
     DBuf ent_slot, ent_pid, ent_cell, ent_own, own_scan, rows_ent, scan_tmp;
     DBuf d_ve;
     DBuf d_scenes, d_walls, d_mats, d_tanphi, d_ctr, d_part_c, d_part_i, d_bounds, d_total, d_tmp3, d_args;
@@ -354,7 +354,7 @@ struct World {
         for (auto& b : bs) b.release();
         for (auto& p : ps) p.release();
         for (DBuf* d : {&slot_of_id, &d_gids, &d_state, &cell_count, &cell_start, &body_cell, &body_arrival, &body_cell1, &body_arrival1,
-                        &bucket, &bucket_id, &large_slot, &counts, &row_start,
+                        &bucket, &large_slot, &counts, &row_start,
                         &ent_slot, &ent_pid, &ent_cell, &ent_own, &own_scan, &rows_ent, &scan_tmp,
                         &d_scenes, &d_walls, &d_mats, &d_tanphi, &d_ctr, &d_part_c, &d_part_i, &d_bounds, &d_total,
                         &d_tmp3, &d_args, &d_ctrl_cfg, &d_ctrl_state, &d_acc_ctrl, &d_acc_ctrl2, &pb_ca, &pb_cb, &pb_found,
@@ -854,17 +854,24 @@ struct World {
     }
 
     // ------------------------------------------------------- broad phase
-    // The largest bricks (2^bits cells a side) that pad the grid by at most
-    // half: a brick's cells, and so the bodies in memory, follow a Morton
-    // curve, and bricks follow one another along x.
+    // Cells are numbered in bricks of 2^bits cells a side: inside a brick
+    // they, and so the bodies in memory, follow a Morton curve, and bricks
+    // follow one another along x.  An aperiodic level takes the largest bricks
+    // that pad its grid by at most half (the table is cleared and scanned on
+    // every run); a periodic one, whose runs are rare and whose bodies never
+    // gather in a corner, one brick over the whole cell while that pads it at
+    // most 32 times.
     static int64_t brick_cells(const int32_t* dims, int bits)
     {
         int64_t n = 1;
         for (int k = 0; k < 3; ++k) n *= ((int64_t)dims[k] + (1 << bits) - 1) >> bits;
         return n << (3 * bits);
     }
-    static int brick_bits(const int32_t* dims)
+    static int brick_bits(const int32_t* dims, bool periodic)
     {
+        int whole = 0;
+        while ((1 << whole) < std::max({dims[0], dims[1], dims[2]})) ++whole;
+        if (periodic && whole <= 10 && brick_cells(dims, whole) <= 32 * brick_cells(dims, 0)) return whole;
         int bits = 8;
         while (bits > 0 && 2 * brick_cells(dims, bits) > 3 * brick_cells(dims, 0) + 512) --bits;
         return bits;
@@ -1060,8 +1067,8 @@ struct World {
                 }
             }
             P.r_split = rs;
-            P.brick_bits = brick_bits(P.dims);
-            P.brick_bits2 = brick_bits(P.dims2);
+            P.brick_bits = brick_bits(P.dims, periodic);
+            P.brick_bits2 = brick_bits(P.dims2, periodic);
             // mean-field share of the Verlet budget (periodic)
             double lf = 0.0;
             for (int k = 0; k < 9; ++k) lf += P.L[k] * P.L[k];
@@ -1107,7 +1114,7 @@ struct World {
             CellSortArgs cs{};
             cell_count.ensure(4 * (size_t)ncells);
             cell_start.ensure(4 * ((size_t)ncells + 1));
-            for (DBuf* d : {&body_cell, &body_arrival, &bucket, &bucket_id}) d->ensure(4 * (size_t)nslots);
+            for (DBuf* d : {&body_cell, &body_arrival, &bucket}) d->ensure(4 * (size_t)nslots);
             if (nlarge > 0) {
                 body_cell1.ensure(4 * (size_t)nslots);
                 body_arrival1.ensure(4 * (size_t)nslots);
@@ -1120,7 +1127,6 @@ struct World {
             cs.cell1 = body_cell1.as<uint32_t>();
             cs.arrival1 = body_arrival1.as<uint32_t>();
             cs.bucket = bucket.as<uint32_t>();
-            cs.bucket_id = bucket_id.as<int32_t>();
             cs.large_slot = large_slot.as<uint32_t>();
             cs.ncells = ncells;
             cs.nlarge = (int)nlarge;
