@@ -31,13 +31,34 @@ __device__ inline V3<T> operator+(V3<T> a, V3<T> b) { return {a.x + b.x, a.y + b
 template <typename T>
 __device__ inline V3<T> operator-(V3<T> a, V3<T> b) { return {a.x - b.x, a.y - b.y, a.z - b.z}; }
 template <typename T>
-__device__ inline V3<T> operator*(T s, V3<T> a) { return {s * a.x, s * a.y, s * a.z}; }
+__device__ inline V3<T> operator-(V3<T> a) { return {-a.x, -a.y, -a.z}; }
 template <typename T>
-__device__ inline T dot(V3<T> a, V3<T> b) { return a.x * b.x + a.y * b.y + a.z * b.z; }
+__device__ inline V3<T> operator*(T s, V3<T> a) { return {s * a.x, s * a.y, s * a.z}; }
+// The force law's products and sums are fused where they are written fused
+// and nowhere else, so that the results do not change with the order in which
+// the compiler meets them.
+__device__ inline double fused(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ inline float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+template <typename T>
+__device__ inline V3<T> fused(T s, V3<T> a, V3<T> c)
+{
+    return {fused(s, a.x, c.x), fused(s, a.y, c.y), fused(s, a.z, c.z)};
+}
+template <typename T>
+__device__ inline T dot(V3<T> a, V3<T> b)
+{
+    return fused(a.z, b.z, fused(a.x, b.x, a.y * b.y));
+}
 template <typename T>
 __device__ inline V3<T> cross(V3<T> a, V3<T> b)
 {
-    return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x};
+    return {fused(a.y, b.z, -(a.z * b.y)), fused(a.z, b.x, -(a.x * b.z)), fused(a.x, b.y, -(a.y * b.x))};
+}
+// -(a x b), with the other product of each component rounded
+template <typename T>
+__device__ inline V3<T> cross_neg(V3<T> a, V3<T> b)
+{
+    return {fused(a.z, b.y, -(a.y * b.z)), fused(a.x, b.z, -(a.z * b.x)), fused(a.y, b.x, -(a.x * b.y))};
 }
 template <typename T, typename U>
 __device__ inline V3<T> cvt(V3<U> a) { return {(T)a.x, (T)a.y, (T)a.z}; }
@@ -87,13 +108,97 @@ __device__ inline void unpack_cell(int32_t p, int* c)
 // [P_x, P_x+1) with P_x = x npairs / 8, so that neighbouring pairs share its
 // L2 and every XCD gets the same share whatever the grid's headroom (the
 // grid has at least ceil(ceil(npairs / 8) / blockDim) blocks per XCD).
-// Returns the pair of this thread, or -1.
-__device__ inline int xcd_pair(int npairs)
+// The wave's 64 lanes take the pairs from `first` on; a lane at or past
+// `end` has none.
+struct PairRange {
+    int first, end;
+};
+__device__ inline PairRange xcd_pairs(int npairs)
 {
     const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
     const int64_t p0 = ((int64_t)xcd * npairs) >> 3, p1 = ((int64_t)(xcd + 1) * npairs) >> 3;
-    const int64_t k = p0 + (int64_t)j * blockDim.x + threadIdx.x;
-    return k < p1 ? (int)k : -1;
+    const int64_t k = p0 + (int64_t)j * blockDim.x + __builtin_amdgcn_readfirstlane((int)(threadIdx.x & ~63u));
+    return {(int)(k < p1 ? k : p1), (int)p1};
+}
+
+// ---- history records of a wave, read and written whole
+//
+// A lane's record is 64 (FP64) or 48 bytes.  Read by its own lane it takes 16
+// bytes per load, each of the 64 lanes in a line of its own, and the cache
+// answers the same line four times; so do its stores (a quarter to a half of
+// the kernel's cache accesses, and most of its write requests to L2).
+// Instead the wave loads its 64 consecutive records in order, 1 KB per load,
+// straight into its share of LDS, where each lane finds its own; the loads
+// hold no registers while they are in flight.  The new records go back the
+// same way.  The kernel, before -> now: 8 M spheres in shear (42 M candidates,
+// 16 M touching, FP64) 1.46 -> 1.11 ms, 500,000 under the controlled cell (4.5
+// M, 2.5 M) 182 -> 140 us, 1 M in shear FP32-mixed 208 -> 178 us; scenes with
+// few contacts within 0.2 us.  A grid of resident blocks that loop over tiles
+// took 1.53 ms at 8 M (the values kept across tiles spill), adding the counts
+// with atomics that return nothing 1.50.
+using Lds = __attribute__((address_space(3))) char*;
+
+// bytes of LDS per wave: its records
+template <int PREC>
+constexpr int kWaveBytes = 64 * (int)sizeof(typename HistOf<PREC>::T);
+
+__device__ inline void wave_lds_sync()
+{
+    // the wave's own LDS accesses before are complete before those after
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// Starts loading the records of the wave's lanes in `mask`; the wave's first
+// record is hist[first].  hist_take waits for them.
+template <int PREC>
+__device__ inline void hist_fetch(const HistRec* hist, int first, unsigned long long mask, char* lds)
+{
+    using H = typename HistOf<PREC>::T;
+    constexpr int kParts = sizeof(H) / 16;
+    const int lane = threadIdx.x & 63;
+    const gptr<const char> from = glb(reinterpret_cast<const char*>(hist)) + (size_t)first * sizeof(H) + 16 * lane;
+#if defined(__HIP_DEVICE_COMPILE__)
+    for (int i = 0; i < kParts; ++i)
+        if (mask >> ((64 * i + lane) / kParts) & 1ull)
+            __builtin_amdgcn_global_load_lds((gptr<const void>)(from + 1024 * i), (Lds)lds + 1024 * i, 16, 0, 0);
+#endif
+}
+// every lane of the wave takes part (a lane not in the mask may get anything)
+template <int PREC>
+__device__ inline typename HistOf<PREC>::T hist_take(const char* lds)
+{
+    using H = typename HistOf<PREC>::T;
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the loads into LDS
+    wave_lds_sync();
+    return *reinterpret_cast<const H*>(lds + (threadIdx.x & 63) * sizeof(H));
+}
+
+// One record T per lane in `mask`, the wave's 64 to consecutive places from
+// `to` on, in accesses of UNIT (a record holds a whole number of them).  A
+// wave with few records stores them from their lanes: the way through LDS
+// would only be longer.
+constexpr int kSparse = 8;
+template <typename UNIT, typename T>
+__device__ inline void wave_store(T* to, unsigned long long mask, const T& v, char* lds)
+{
+    constexpr int kParts = sizeof(T) / sizeof(UNIT);
+    const int lane = threadIdx.x & 63;
+    UNIT u[kParts];
+    __builtin_memcpy(u, &v, sizeof v);
+    const gptr<UNIT> dst = glb(reinterpret_cast<UNIT*>(to));
+    if (__popcll(mask) <= kSparse) {
+        for (int i = 0; i < kParts; ++i)
+            if (mask >> lane & 1ull) dst[kParts * lane + i] = u[i];
+        return;
+    }
+    wave_lds_sync();
+    UNIT* const row = reinterpret_cast<UNIT*>(lds);
+    for (int i = 0; i < kParts; ++i) row[kParts * lane + i] = u[i];
+    wave_lds_sync();
+    for (int i = 0; i < kParts; ++i)
+        if (mask >> ((64 * i + lane) / kParts) & 1ull) dst[64 * i + lane] = row[64 * i + lane];
 }
 
 // A pair that starts or stops touching rewrites its two row entries with
@@ -107,6 +212,22 @@ __device__ inline void set_row_bits(const StepArgs& a, int k, bool real)
     if (ea >= 0) ent[ea] = v | kNegSign;
     if (eb >= 0) ent[eb] = v;
 }
+
+// k1 k2 / (k1 + k2) of two springs k_i = e_i d_i; SECOND: which of the two
+// products the sum is fused with.
+template <bool SECOND, typename R>
+__device__ inline R series_spring(R e1, R d1, R e2, R d2)
+{
+#pragma clang fp contract(off)
+    const R k1 = e1 * d1, k2 = e2 * d2;
+    return k1 * k2 / (SECOND ? fused(e2, d2, k1) : fused(e1, d1, k2));
+}
+
+// a pair's force record: the force on #2 and n x F
+template <typename R>
+struct ForceRec {
+    R fx, fy, fz, tx, ty, tz;
+};
 
 struct ContactPartial {
     double el, plast;
@@ -126,10 +247,18 @@ struct ContactPartial {
 // spheres and planes.
 // VISCEL (a world with visco-elastic materials): pairs of ViscElMat take
 // Law2_ScGeom_ViscElPhys_Basic, the others the linear law.
+// Waves per SIMD the registers are held to: with the history in LDS on its way
+// in, every linear-law instantiation fits 80 registers.  Measured at 8 M
+// spheres in shear (42 M candidates, 16 M touching, FP64): 5 waves 1.17 ms, 6
+// waves 1.11, 7 waves (spills) 1.52.
+template <bool VISCEL>
+constexpr int kContactWaves = VISCEL ? 5 : 6;
+
 template <int PREC, bool BATCHED, bool PERIODIC, bool MEASURE = false, bool PRIMS = false, bool VISCEL = false>
-__global__ void __launch_bounds__(kMaxBlock) k_contact(const StepArgs* __restrict__ args, int parity)
+__global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(kContactWaves<VISCEL>))) k_contact(const StepArgs* __restrict__ args, int parity)
 {
     using R = typename std::conditional<PREC == DEM_FP32_MIXED, float, double>::type;
+    extern __shared__ __align__(16) char s_rec[];  // kWaveBytes per wave
     // the arguments live in device memory so that a captured graph stays
     // valid across broad-phase runs (pair count and buffers change there)
     const StepArgs& a = *args;
@@ -137,7 +266,8 @@ __global__ void __launch_bounds__(kMaxBlock) k_contact(const StepArgs* __restric
     // thread's pair ids and its touched flag are requested (in bounds;
     // nothing is stored before the test), so that its latency overlaps theirs
     const int32_t stalled = a.ctr->stall[parity ^ 1];
-    const int k = xcd_pair(a.npairs);
+    const PairRange range = xcd_pairs(a.npairs);
+    const int k = range.first + (int)(threadIdx.x & 63) < range.end ? range.first + (int)(threadIdx.x & 63) : -1;
     int32_t sa = 0, sb = 0, pcell = 0;
     uint8_t was_real = 0;
     if (k >= 0) {
@@ -163,42 +293,42 @@ __global__ void __launch_bounds__(kMaxBlock) k_contact(const StepArgs* __restric
     // normal as stored, the branch length, k_n; zero for a pair not
     // touching) and forms the terms one at a time at the end
     double mf[3] = {0.0, 0.0, 0.0}, mn[3] = {0.0, 0.0, 0.0}, ml = 0.0, mkn = 0.0, mtouch = 0.0;
+    const gptr<const double4> xr = glb<const double4>(a.bod.xr);
+    const gptr<const double4> vm = glb<const double4>(a.bod.vm);
+    const gptr<const double4> wv = glb<const double4>(a.bod.w);
+    using H = typename HistOf<PREC>::T;
+    const int s = BATCHED && k >= 0 ? (int)glb<const uint16_t>(a.bod.scene)[sb] : 0;
+    // an unbatched scene (periodic included) reads the descriptor's own
+    // copy of its parameters: uniform, read-only here, so scalar loads
+    const SceneParams& S = BATCHED ? a.scenes[s] : a.scene0;
+    const bool wall = sa < 0;
+    const int32_t s1 = wall ? sb : sa;
+    Wall W;
+    double r1 = 0.0, r2 = 0.0;
+    int m1 = 0, m2 = 0;
+    bool real = false;
+    bool in_box = false;       // a centre inside a box: overlap r + depth by definition
+    double pen = 0.0, inv_l = 0.0, l = 0.0;
+    V3<double> n64 = {0.0, 0.0, 0.0};
+    int cc[3] = {0, 0, 0};
     if (k >= 0) {
-        const gptr<const double4> xr = glb<const double4>(a.bod.xr);
-        const gptr<const double4> vm = glb<const double4>(a.bod.vm);
-        const gptr<const double4> wv = glb<const double4>(a.bod.w);
         const gptr<const uint16_t> mat = glb<const uint16_t>(a.bod.mat);
-        const gptr<uint8_t> preal = glb(a.pr.real);
-        using H = typename HistOf<PREC>::T;
-        const gptr<H> hist = glb(reinterpret_cast<H*>(a.pr.h));
-        const int s = BATCHED ? (int)glb<const uint16_t>(a.bod.scene)[sb] : 0;
-        // an unbatched scene (periodic included) reads the descriptor's own
-        // copy of its parameters: uniform, read-only here, so scalar loads
-        const SceneParams& S = BATCHED ? a.scenes[s] : a.scene0;
-        const double dt = S.dt;
-
         // #1's loads are issued without a branch, together with #2's: a
         // wall pair reads #2 in place of #1, a sphere pair reads wall 0 (the
         // wall table always holds at least one entry); the unused values are
         // then set aside
-        const bool wall = sa < 0;
-        const int32_t s1 = wall ? sb : sa;
         const double4 p2 = xr[sb];
         const double4 p1 = xr[s1];
-        const int m2 = mat[sb];
+        m2 = mat[sb];
         const int m1s = mat[s1];
-        const Wall W = glb<const Wall>(a.walls)[wall ? -1 - sa : 0];
-        const double x2 = p2.x, y2 = p2.y, z2 = p2.z, r2 = p2.w;
+        W = glb<const Wall>(a.walls)[wall ? -1 - sa : 0];
+        const double x2 = p2.x, y2 = p2.y, z2 = p2.z;
         const double x1 = wall ? 0.0 : p1.x, y1 = wall ? 0.0 : p1.y, z1 = wall ? 0.0 : p1.z;
-        const double r1 = wall ? 0.0 : p1.w;
-        const int m1 = wall ? W.mat : m1s;
+        r2 = p2.w;
+        r1 = wall ? 0.0 : p1.w;
+        m1 = wall ? W.mat : m1s;
 
         // ---- exact test, normal, overlap (always in double)
-        bool real;
-        bool in_box = false;       // a centre inside a box: overlap r + depth by definition
-        double pen, inv_l = 0.0, l = 0.0;
-        V3<double> n64;
-        int cc[3] = {0, 0, 0};
         if (!wall) {
             if (PERIODIC) unpack_cell(pcell, cc);
             const SpherePairTest t =
@@ -250,7 +380,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_contact(const StepArgs* __restric
                 n64 = v3(ax == 0 ? sgn : 0.0, ax == 1 ? sgn : 0.0, ax == 2 ? sgn : 0.0);
             } else {
                 const double d0 = xs[0] - p[0], d1 = xs[1] - p[1], d2 = xs[2] - p[2];
-                const double dist = sqrt((d0 * d0 + d1 * d1) + d2 * d2);
+                const double dist = sqrt(fused(d2, d2, fused(d0, d0, d1 * d1)));
                 real = dist < r2;
                 pen = r2 - dist;
                 if (dist > 0.0) {
@@ -266,22 +396,34 @@ __global__ void __launch_bounds__(kMaxBlock) k_contact(const StepArgs* __restric
             }
         }
 
-        if (!real) {
-            // the contact is erased: drop its history (once), no force
-            if (was_real) {
-                hist[k] = H{};
-                preal[k] = 0;
-                set_row_bits(a, k, false);
-            }
-        } else {
-            // ---- every load of a touching pair, issued together: both
-            // bodies' velocities and spins, the history, the materials
+    }
+
+    // ---- the touching pairs of the wave.  Their histories are read and
+    // written by the wave together (hist_fetch), so the wave's control flow
+    // stays whole around the two exchanges.  Every load of a touching pair is
+    // issued before the first is waited for: history, both bodies'
+    // velocities and spins, the materials.
+    const unsigned long long touch = __ballot(real);
+    const unsigned long long erase = __ballot(k >= 0 && !real && was_real != 0);
+    if (touch | erase) {
+        char* const lds = s_rec + (threadIdx.x >> 6) * kWaveBytes<PREC>;
+        hist_fetch<PREC>(a.pr.h, range.first, touch, lds);
+        // what the law takes from the bodies and the materials, formed while
+        // the history is on its way
+        const V3<R> n = cvt<R>(n64);
+        R kn = (R)0, ks = (R)0, tanphi = (R)0, spin = (R)0;
+        V3<R> vs = {(R)0, (R)0, (R)0};
+        double kn64 = 0.0, cn64 = 0.0, cs64 = 0.0, un = 0.0;
+        bool ve = false;
+        const double dt = S.dt;
+        const R dtr = (R)dt;
+        if (real) {
+#pragma clang fp contract(off)
             const double4 va = vm[s1], wa = wv[s1];
             const double4 vb = vm[sb], wb = wv[sb];
-            const H hold = hist[k];
             const Material M1 = glb<const Material>(a.mats)[m1];
             const Material M2 = glb<const Material>(a.mats)[m2];
-            const double tanphi64 = glb<const double>(a.tanphi)[m1 * a.nmat + m2];
+            tanphi = (R)glb<const double>(a.tanphi)[m1 * a.nmat + m2];
 
             // ---- ScGeom inputs (a boundary's reference radius: the sphere's,
             // twice the sphere's for a facet)
@@ -296,19 +438,17 @@ __global__ void __launch_bounds__(kMaxBlock) k_contact(const StepArgs* __restric
                 // the image of #2 moves with the cell: (H - H_prev) c / dt
                 // (one FP64 division, then three products)
                 const double* D = S.dH;
-                const double sx = (D[0] * (double)cc[0] + D[1] * (double)cc[1]) + D[2] * (double)cc[2];
-                const double sy = (D[3] * (double)cc[0] + D[4] * (double)cc[1]) + D[5] * (double)cc[2];
-                const double sz = (D[6] * (double)cc[0] + D[7] * (double)cc[1]) + D[8] * (double)cc[2];
-                const double inv_dt = 1.0 / dt;
-                v2d = v3(v2d.x + sx * inv_dt, v2d.y + sy * inv_dt, v2d.z + sz * inv_dt);
+                const double c0 = (double)cc[0], c1 = (double)cc[1], c2 = (double)cc[2];
+                const double sx = fused(D[2], c2, fused(D[0], c0, D[1] * c1));
+                const double sy = fused(D[5], c2, fused(D[3], c0, D[4] * c1));
+                const double sz = fused(D[8], c2, fused(D[6], c0, D[7] * c1));
+                v2d = fused(1.0 / dt, v3(sx, sy, sz), v2d);
             }
             // relative translational velocity in double (difference of absolute values)
             const V3<double> dv64 = v2d - v1d;
 
             // ---- contact stiffnesses (and the visco-elastic dashpots)
-            R kn, ks;
-            double kn64 = 0.0, cn64 = 0.0, cs64 = 0.0;
-            const bool ve = VISCEL && M2.viscel != 0;
+            ve = VISCEL && M2.viscel != 0;
             if (ve) {
                 // Ip2_ViscElMat_ViscElMat_ViscElPhys: the pair's constants
                 // scaled by the reduced mass; a body that cannot move (a
@@ -324,58 +464,55 @@ __global__ void __launch_bounds__(kMaxBlock) k_contact(const StepArgs* __restric
                 const ViscElPair P = glb<const ViscElPair>(a.ve)[m1 * a.nmat + m2];
                 const double pi2 = 3.14159265358979323846 * 3.14159265358979323846;
                 const double tc2 = P.tc * P.tc;
-                kn64 = mr * (pi2 + P.len * P.len) / tc2;
+                kn64 = mr * fused(P.len, P.len, pi2) / tc2;
                 kn = (R)kn64;
                 cn64 = -2.0 * mr * P.len / P.tc;
-                ks = (R)(2.0 / 7.0 * mr * (pi2 + P.let * P.let) / tc2);
+                ks = (R)(2.0 / 7.0 * mr * fused(P.let, P.let, pi2) / tc2);
                 cs64 = -2.0 / 7.0 * mr * P.let / P.tc;
+                // the normal dashpot's rate
+                un = fused(n64.z, dv64.z, fused(n64.x, dv64.x, n64.y * dv64.y));
             } else {
                 // Ip2_FrictMat_FrictMat_FrictPhys: series springs k_i = E_i (2 R_i)
-                const R k1 = (R)M1.young * ((R)2 * (R)R1d), k2 = (R)M2.young * ((R)2 * (R)R2d);
-                kn = k1 * k2 / (k1 + k2);
-                const R q1 = (R)M1.young_poisson * ((R)2 * (R)R1d), q2 = (R)M2.young_poisson * ((R)2 * (R)R2d);
-                ks = q1 * q2 / (q1 + q2);
+                const R d1 = (R)2 * (R)R1d, d2 = (R)2 * (R)R2d;
+                kn = series_spring<PRIMS || VISCEL>((R)M1.young, d1, (R)M2.young, d2);
+                ks = series_spring<PRIMS || VISCEL>((R)M1.young_poisson, d1, (R)M2.young_poisson, d2);
             }
-            const R tanphi = (R)tanphi64;
 
-            const V3<R> n = cvt<R>(n64);
-            const R penr = (R)pen;
+            // ---- ScGeom rates: the mean spin about the normal over the step,
+            // v12 = alpha (v2 - v1) - (r2 w2 + r1 w1) x n, alpha = (r1 + r2)/l,
+            // and its tangential part
+            const V3<R> w1 = cvt<R>(w1d), w2 = cvt<R>(w2d);
+            spin = (dtr / (R)2) * dot(n, w1 + w2);
             const R Rd1 = (R)R1d, Rd2 = (R)R2d;
-            const R dtr = (R)dt;
-
+            const R alpha = wall ? (R)1 : (R)((r1 + r2) * inv_l);
+            const V3<R> rw = PRIMS ? fused(Rd2, w2, Rd1 * w1) : fused(Rd1, w1, Rd2 * w2);
+            const V3<R> v12 = fused(alpha, cvt<R>(dv64), -cross(rw, n));
+            vs = fused(-dot(n, v12), n, v12);
+        }
+        const H hold = hist_take<PREC>(lds);
+        // a pair that no longer touches drops its history and has no force
+        H hnew = {};
+        ForceRec<R> frec = {};
+        if (real) {
+#pragma clang fp contract(off)
             // ---- shear update (section 2.1.3): both rotation increments from
             // the previous vector, then the sliding increment
             const V3<double> fs_old64 = v3(hold.fsx, hold.fsy, hold.fsz);
             const V3<R> fs_old = cvt<R>(fs_old64);
             const V3<R> nprev = v3((R)hold.nx, (R)hold.ny, (R)hold.nz);
-            const V3<R> inc1 = cross(fs_old, cross(nprev, n));
-            const V3<R> w1 = cvt<R>(w1d), w2 = cvt<R>(w2d);
-            const R spin = (dtr / (R)2) * dot(n, w1 + w2);
-            const V3<R> inc2 = cross(fs_old, spin * n);
-            // v12 = alpha (v2 - v1) - (r2 w2 + r1 w1) x n, alpha = (r1 + r2)/l
-            const R alpha = wall ? (R)1 : (R)((r1 + r2) * inv_l);
-            const V3<R> rw = Rd2 * w2 + Rd1 * w1;
-            const V3<R> v12 = alpha * cvt<R>(dv64) - cross(rw, n);
-            const V3<R> vs = v12 - dot(n, v12) * n;
-            const V3<R> dfs = ((v3<R>((R)0, (R)0, (R)0) - inc1) - inc2) - (ks * dtr) * vs;
+            const V3<R> turn = cross_neg(fs_old, cross(nprev, n)) + cross_neg(fs_old, spin * n);
+            const V3<R> dfs = fused(-(ks * dtr), vs, turn);
             V3<double> fs64 = fs_old64 + cvt<double>(dfs);
 
             // ---- Law2_ScGeom_FrictPhys_CundallStrack; Law2_ScGeom_ViscElPhys_Basic
             // adds a normal dashpot on the overlap's rate -(v2 - v1).n (no
             // tension cut-off) and a shear dashpot that carries nothing while
             // the slider slides, the slider bounding the spring's part by
-            // tan(phi) times the compressive normal force
-            R fn_mag;
-            double un = 0.0;
-            if (ve) {
-                // spring and dashpot in FP64 in both modes: near the end of a
-                // contact they cancel, and k_n rounded to FP32 would leave its
-                // rounding error against a small difference
-                un = (n64.x * dv64.x + n64.y * dv64.y) + n64.z * dv64.z;
-                fn_mag = (R)(kn64 * pen - cn64 * un);
-            } else {
-                fn_mag = kn * penr;
-            }
+            // tan(phi) times the compressive normal force.  Its spring and
+            // dashpot are formed in FP64 in both modes: near the end of a
+            // contact they cancel, and k_n rounded to FP32 would leave its
+            // rounding error against a small difference
+            const R fn_mag = ve ? (R)fused(kn64, pen, -(cn64 * un)) : kn * (R)pen;
             const R fmax = (ve && fn_mag < (R)0 ? (R)0 : fn_mag) * tanphi;
             const double fs_norm = sqrt(dot(fs64, fs64));
             const bool slide = fs_norm > (double)fmax;
@@ -388,37 +525,22 @@ __global__ void __launch_bounds__(kMaxBlock) k_contact(const StepArgs* __restric
             if (ve) {
                 const V3<double> vs64 = cvt<double>(vs);
                 const double vss = dot(vs64, vs64);
-                if (!slide) fsr = cvt<R>(fs64 + (-cs64) * vs64);
+                if (!slide) fsr = cvt<R>(fused(-cs64, vs64, fs64));
                 part.visc += ((cn64 * un) * un + (slide ? 0.0 : cs64 * vss)) * dt;
                 part.el += 0.5 * ((kn64 * pen) * pen) + 0.5 * (dot(fs64, fs64) / (double)ks);
             } else {
                 part.el += 0.5 * ((double)fn_mag * (double)fn_mag / (double)kn) + 0.5 * (dot(fs64, fs64) / (double)ks);
             }
-            const V3<R> F = fn_mag * n + fsr;
+            const V3<R> F = fused(fn_mag, n, fsr);
             const V3<R> tau = cross(n, F);
 
             if constexpr (PREC == DEM_FP32_MIXED)
-                hist[k] = H{fs64.x, fs64.y, fs64.z, pen, (float)n.x, (float)n.y, (float)n.z, (float)fn_mag};
+                hnew = H{fs64.x, fs64.y, fs64.z, pen, (float)n.x, (float)n.y, (float)n.z, (float)fn_mag};
             else
-                hist[k] = H{fs64.x, fs64.y, fs64.z, pen, (double)n.x, (double)n.y, (double)n.z, (double)fn_mag};
-            // the force record as three pairs (a record starts on an 8-byte
-            // (FP32) or 16-byte (FP64) boundary of a 256-byte aligned array);
-            // the FP64 linear law's integrate kernel reads the history instead
-            if (PREC == DEM_FP32_MIXED) {
-                const gptr<float2> q = glb(reinterpret_cast<float2*>(a.pr.frecf)) + 3 * (size_t)k;
-                q[0] = make_float2((float)F.x, (float)F.y);
-                q[1] = make_float2((float)F.z, (float)tau.x);
-                q[2] = make_float2((float)tau.y, (float)tau.z);
-            } else if (VISCEL) {
-                const gptr<double2> q = glb(reinterpret_cast<double2*>(a.pr.frec)) + 3 * (size_t)k;
-                q[0] = make_double2((double)F.x, (double)F.y);
-                q[1] = make_double2((double)F.z, (double)tau.x);
-                q[2] = make_double2((double)tau.y, (double)tau.z);
-            }
-            if (!was_real) {
-                preal[k] = 1;
-                set_row_bits(a, k, true);
-            }
+                hnew = H{fs64.x, fs64.y, fs64.z, pen, (double)n.x, (double)n.y, (double)n.z, (double)fn_mag};
+            // the force record (F, n x F); the FP64 linear law's integrate
+            // kernel reads the history instead
+            frec = ForceRec<R>{F.x, F.y, F.z, tau.x, tau.y, tau.z};
             if (wall)
                 part.sw = 1;
             else
@@ -439,6 +561,15 @@ __global__ void __launch_bounds__(kMaxBlock) k_contact(const StepArgs* __restric
                     mkn = (double)kn;
                 }
             }
+        }
+        wave_store<uint4>(reinterpret_cast<H*>(a.pr.h) + range.first, touch | erase, hnew, lds);
+        if constexpr (PREC == DEM_FP32_MIXED)
+            wave_store<uint2>(reinterpret_cast<ForceRec<R>*>(a.pr.frecf) + range.first, touch, frec, lds);
+        else if (VISCEL)
+            wave_store<uint4>(reinterpret_cast<ForceRec<R>*>(a.pr.frec) + range.first, touch, frec, lds);
+        if (k >= 0 && real != (was_real != 0)) {
+            glb(a.pr.real)[k] = real ? 1 : 0;
+            set_row_bits(a, k, real);
         }
     }
 
@@ -522,11 +653,12 @@ template <int PREC, bool BATCHED, bool PERIODIC, bool MEASURE = false, bool PRIM
 void launch_t(const StepArgs* args, int parity, int grid, int block, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1)
 {
     const dim3 g(grid > 0 ? grid : 1), b(block);
+    const size_t lds = (size_t)kWaveBytes<PREC> * (size_t)((block + 63) / 64);
     if (ev0)
-        hipExtLaunchKernelGGL((k_contact<PREC, BATCHED, PERIODIC, MEASURE, PRIMS, VISCEL>), g, b, 0, st, ev0, ev1, 0,
+        hipExtLaunchKernelGGL((k_contact<PREC, BATCHED, PERIODIC, MEASURE, PRIMS, VISCEL>), g, b, lds, st, ev0, ev1, 0,
                               args, parity);
     else
-        hipLaunchKernelGGL((k_contact<PREC, BATCHED, PERIODIC, MEASURE, PRIMS, VISCEL>), g, b, 0, st, args, parity);
+        hipLaunchKernelGGL((k_contact<PREC, BATCHED, PERIODIC, MEASURE, PRIMS, VISCEL>), g, b, lds, st, args, parity);
 }
 
 // the visco-elastic instantiation of a scene kind: boundaries of every kind
