@@ -380,6 +380,10 @@ struct IntAcc {
                                     // at the last step that ended an update period of the controlled cell
 };
 
+// Entries that may be read (never used) past the last row's end: the force
+// sum looks at a row 24 entries at a time.
+constexpr int kRowPad = 24;
+
 struct StepArgs {
     Bodies bod;
     Pairs pr;

@@ -126,79 +126,212 @@ __device__ inline void body_sum(const StepArgs& a, int beg, int end, double r, d
     row_walk<PREC, FREC>(a, beg, end, r, F, T);
 }
 
-// The same sum in the integrate kernel, called by every lane of the wave.
-// Each lane first walks up to kSoloEntries entries of its row by itself, four
-// at a time.  What is left is finished in one of two ways, chosen again after
-// every batch: the lanes go on walking, four entries each at once, or the
-// wave takes the longest row, 64 entries per round (each lane reads one entry
-// and its pair's record into the wave's slice of LDS, then the row's own lane
-// adds them in row order, with the same arithmetic as the walk).  A batch and
-// a round cost about one dependent pair of loads each, so the wave walks on
-// while the longest row left needs no more batches than there are rows left
-// (one round each), and shares the work where a few rows are much longer
-// than the rest (a large sphere among small ones has ~10x their entries).
-// Sharing every row past 12 entries instead took one round per lane where
-// all rows are a little longer: 32,000 dense equal spheres with 18 candidates
-// each took 75 us per launch that way (150 steps from a new state, everything
-// included: 17.1 -> 7.3 ms); 8 M spheres of two sizes are as fast either way.
-constexpr int kSoloEntries = 12;
-constexpr int kCoopWords = 64 * (kForceWords + 1);  // doubles per wave: 64 entries x 6, then 64 entry words
-template <int PREC, bool FREC>
-__device__ inline void body_sum_wave(const StepArgs& a, int beg, int end, double r, double* F, double* T,
-                                     double* lds)
+// ---- the same sum in the integrate kernel, by the wave
+//
+// A lane looks at its row 24 entries at a time, all loaded at once (four per
+// load), and keeps the touching ones (a third to a half) in its column of a
+// list in LDS; the records are then gathered from the list, so that none is
+// read for an entry that does not count, and a row costs one wait for its
+// entries instead of one per four of them.
+//
+// Where the bodies fill the chip the gathers set the pace: a lane's 64-byte
+// history record takes four accesses of 16 bytes, each of the 64 lanes in a
+// line of its own.  QUAD: the four lanes of a quad read one record together,
+// for each of the four in turn, and exchange the parts by quad permutations:
+// 16 lines per load instead of 64.  Two records per lane are in flight then
+// (three spill: 109 us where two take 96, below).  Where waves are few, the
+// exchange only lengthens the chain, and three records are read directly.
+// Force records (24 or 48 bytes) are read directly, four in flight.
+//
+// Before (entries and records four at a time, no list) -> now, per launch:
+// 8 M spheres in shear 974 -> 906 us, 500,000 under the controlled cell 126 ->
+// 96 us, 1 M in shear FP32-mixed 142 -> 131 us, 32,000 dense equal spheres
+// 10.8 -> 9.9 us (in blocks of 64), 24 scenes of 8,000 10.6 -> 9.2 us; a bed
+// of 1,000 within 0.2 us.  Taking the wave's rows as one stream of 64 entries
+// per load, ranked by ballots, took 924 us at 8 M and 5 us more for the
+// 32,000; records brought straight into LDS 951 us.
+//
+// What is left of rows much longer than the rest (a large sphere among small
+// ones has ~10x their entries) is finished by the wave together, one row's
+// next 64 entries per round: each lane reads one record, and six lanes add
+// one component each, in row order.  A span or a round costs about two waits
+// for memory, so the lanes go on by themselves while none has more than four
+// entries left for each row that is not finished.  Sharing every row past 12
+// entries instead took one round per lane where all rows are a little longer
+// (the 32,000 dense spheres: 75 us per launch).
+//
+// Every way takes a body's touching entries in row order with the arithmetic
+// of row_walk, so the sums are the same bit for bit.
+constexpr int kSpan = 24;  // entries of its row that a lane looks at at a time
+static_assert(kSpan <= kRowPad && kSpan % 4 == 0, "a span may read past the last row");
+union alignas(16) WaveRows {
+    uint32_t list[kSpan][64];   // the touching ones of them, per lane
+    double f[kForceWords][64];  // a shared round's forces
+};
+// four entries at once; a row starts anywhere
+typedef uint32_t Entries __attribute__((ext_vector_type(4), aligned(4)));
+
+__device__ inline void wave_lds_sync()
 {
+    // the wave's own LDS accesses before are complete before those after
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// One pair's record per lane, fetched by every lane of the wave (a lane
+// without a pair passes 0), and what the sums take from it.
+template <int PREC, bool FREC, bool QUAD>
+struct Record {
+    double f[kForceWords];
+    __device__ void fetch(const StepArgs& a, uint32_t k) { pair_force<PREC, FREC>(a, k, f); }
+    __device__ void force(double* o)
+    {
+        for (int q = 0; q < kForceWords; ++q) o[q] = f[q];
+    }
+};
+
+typedef uint32_t Chunk __attribute__((ext_vector_type(4)));
+constexpr int quad_ctrl(int a, int b, int c, int d) { return a | (b << 2) | (c << 4) | (d << 6); }
+template <int CTRL>
+__device__ inline Chunk quad_perm(Chunk x)
+{
+    Chunk y;
+    for (int d = 0; d < 4; ++d) y[d] = (uint32_t)__builtin_amdgcn_mov_dpp((int)x[d], CTRL, 0xf, 0xf, true);
+    return y;
+}
+// In: lane s of a quad holds part s of the quad's records 0..3; out: parts
+// 0..3 of record s.
+__device__ inline void quad_transpose(Chunk* v)
+{
+    const bool odd = threadIdx.x & 1, high = threadIdx.x & 2;
+    for (int p = 0; p < 4; p += 2) {
+        const Chunk a = v[p], b = v[p + 1];
+        const Chunk xa = quad_perm<quad_ctrl(1, 0, 3, 2)>(a), xb = quad_perm<quad_ctrl(1, 0, 3, 2)>(b);
+        v[p] = odd ? xb : a;
+        v[p + 1] = odd ? b : xa;
+    }
+    for (int p = 0; p < 2; ++p) {
+        const Chunk a = v[p], b = v[p + 2];
+        const Chunk xa = quad_perm<quad_ctrl(2, 3, 0, 1)>(a), xb = quad_perm<quad_ctrl(2, 3, 0, 1)>(b);
+        v[p] = high ? xb : a;
+        v[p + 2] = high ? b : xa;
+    }
+}
+template <int PREC>
+struct Record<PREC, false, true> {
+    Chunk v[4];
+    __device__ void fetch(const StepArgs& a, uint32_t k)
+    {
+        const gptr<const char> part = glb(reinterpret_cast<const char*>(a.pr.h)) + (threadIdx.x & 3) * 16;
+        const uint32_t q[4] = {(uint32_t)__builtin_amdgcn_mov_dpp((int)k, quad_ctrl(0, 0, 0, 0), 0xf, 0xf, true),
+                               (uint32_t)__builtin_amdgcn_mov_dpp((int)k, quad_ctrl(1, 1, 1, 1), 0xf, 0xf, true),
+                               (uint32_t)__builtin_amdgcn_mov_dpp((int)k, quad_ctrl(2, 2, 2, 2), 0xf, 0xf, true),
+                               (uint32_t)__builtin_amdgcn_mov_dpp((int)k, quad_ctrl(3, 3, 3, 3), 0xf, 0xf, true)};
+        for (int i = 0; i < 4; ++i) v[i] = *(gptr<const Chunk>)(part + (size_t)q[i] * sizeof(HistRec));
+    }
+    __device__ void force(double* f)
+    {
+#pragma clang fp contract(off)
+        quad_transpose(v);
+        const HistRec h = __builtin_bit_cast(HistRec, v);
+        const double fx = h.fn * h.nx + h.fsx, fy = h.fn * h.ny + h.fsy, fz = h.fn * h.nz + h.fsz;
+        f[0] = fx;
+        f[1] = fy;
+        f[2] = fz;
+        f[3] = h.ny * fz - h.nz * fy;
+        f[4] = h.nz * fx - h.nx * fz;
+        f[5] = h.nx * fy - h.ny * fx;
+    }
+};
+
+// Entries [at, at + n) (at most 64) of the row of lane `src` (its radius r),
+// added to its sums by the wave.
+template <int PREC, bool FREC>
+__device__ inline void shared_round(const StepArgs& a, WaveRows& w, int at, int n, int src, double r, double* F,
+                                    double* T)
+{
+#pragma clang fp contract(off)
+    const int lane = threadIdx.x & 63;
+    const uint32_t u = lane < n ? glb<const uint32_t>(a.rows.ent)[at + lane] : 0u;
+    const bool use = (u & kRealBit) != 0u && (u & kPairMask) < (uint32_t)a.npairs;
+    if (use) {
+        double f[kForceWords];
+        pair_force<PREC, FREC>(a, u & kPairMask, f);
+        for (int q = 0; q < kForceWords; ++q) w.f[q][lane] = f[q];
+    }
+    const unsigned long long neg = __ballot(u & kNegSign);
+    wave_lds_sync();
+    // lane q adds component q: the forces with their sign, the torques with
+    // the lever arm
+    const double sum[kForceWords] = {F[0], F[1], F[2], T[0], T[1], T[2]};
+    const double lever = -__shfl(r, src, 64);
+    double acc = 0.0;
+    for (int q = 0; q < kForceWords; ++q) {
+        const double v = __shfl(sum[q], src, 64);
+        if (lane == q) acc = v;
+    }
+    const double* const comp = w.f[lane < kForceWords ? lane : 0];
+    for (unsigned long long left = __ballot(use); left; left &= left - 1ull) {
+        const int j = __builtin_ctzll(left);
+        const double v = comp[j];
+        if (lane < 3)
+            acc += (neg >> j & 1ull) ? -v : v;
+        else
+            acc += lever * v;
+    }
+    for (int q = 0; q < kForceWords; ++q) {
+        const double v = __shfl(acc, q, 64);
+        if (lane == src) (q < 3 ? F[q] : T[q - 3]) = v;
+    }
+    wave_lds_sync();
+}
+
+template <int PREC, bool FREC, bool QUAD>
+__device__ inline void body_sum_wave(const StepArgs& a, int beg, int end, double r, double* F, double* T,
+                                     WaveRows& w)
+{
+    constexpr int kB = FREC ? 4 : QUAD ? 2 : 3;
     F[0] = F[1] = F[2] = 0.0;
     T[0] = T[1] = T[2] = 0.0;
-    int next = min(end, beg + kSoloEntries);
-    row_walk<PREC, FREC>(a, beg, next, r, F, T);
-    if (__ballot(next < end) == 0ull) return;
-    auto longest_left = [&]() {
-        int v = end - next;
-        for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, 64));
-        return v;
-    };
-    int longest = longest_left();
     const int lane = threadIdx.x & 63;
-    uint32_t* lu = reinterpret_cast<uint32_t*>(lds + 64 * kForceWords);
-    while (longest > 0) {
-        if (longest <= 4 * (int)__popcll(__ballot(next < end))) {
-            const int stop = min(end, next + 4);
-            row_walk<PREC, FREC>(a, next, stop, r, F, T);
-            next = stop;
-            longest -= 4;
-            continue;
-        }
-        const int src = __builtin_ctzll(__ballot(end - next == longest));
-        const int c0 = __shfl(next, src, 64), c1 = __shfl(end, src, 64);
-        const int e = c0 + lane;
-        uint32_t u = 0u;
-        if (e < c1) u = glb<const uint32_t>(a.rows.ent)[e];
-        const uint32_t k = u & kPairMask;
-        const bool use = e < c1 && k < (uint32_t)a.npairs && (u & kRealBit) != 0u;
-        double f[kForceWords];
-        if (use) {
-            pair_force<PREC, FREC>(a, k, f);
-            for (int q = 0; q < kForceWords; ++q) lds[q * 64 + lane] = f[q];
-        }
-        lu[lane] = use ? u : 0u;
-        // the wave's own LDS writes are complete before its lanes read them
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        if (lane == src) {
-            const int n = min(64, c1 - c0);
-            for (int j = 0; j < n; ++j) {
-                const uint32_t uj = lu[j];
-                if (!(uj & kRealBit)) continue;
-                double fj[kForceWords];
-                for (int q = 0; q < kForceWords; ++q) fj[q] = lds[q * 64 + j];
-                add_entry(uj, fj, r, F, T);
+    int next = beg;
+    int share = INT32_MAX;  // a row with more left than this is shared
+    while (__any(next < end)) {
+        const unsigned long long longs = __ballot(end - next > share);
+        if (longs) {
+            const int src = __builtin_ctzll(longs);
+            const int at = __shfl(next, src, 64), n = min(__shfl(end, src, 64) - at, 64);
+            shared_round<PREC, FREC>(a, w, at, n, src, r, F, T);
+            if (lane == src) next += n;
+        } else {
+            const int n = min(end - next, kSpan);
+            const gptr<const Entries> from = (gptr<const Entries>)(glb<const uint32_t>(a.rows.ent) + next);
+            Entries e[kSpan / 4] = {};
+            for (int j = 0; j < kSpan / 4; ++j)
+                if (j < 2 || __any(n > 4 * j)) e[j] = from[j];
+            int count = 0;
+            for (int j = 0; j < kSpan; ++j) {
+                const uint32_t u = e[j / 4][j % 4];
+                if (j < n && (u & kRealBit) != 0u && (u & kPairMask) < (uint32_t)a.npairs) w.list[count++][lane] = u;
             }
-            next = c0 + n;
+            next += n;
+            for (int c = 0; __any(c < count); c += kB) {
+                // an entry that does not count is 0 and reads pair 0's record
+                // (always cached), which is then ignored
+                uint32_t u[kB];
+                for (int j = 0; j < kB; ++j) u[j] = c + j < count ? w.list[c + j][lane] : 0u;
+                Record<PREC, FREC, QUAD> rec[kB];
+                for (int j = 0; j < kB; ++j) rec[j].fetch(a, u[j] & kPairMask);
+                for (int j = 0; j < kB; ++j) {
+                    double f[kForceWords];
+                    rec[j].force(f);
+                    if (u[j]) add_entry(u[j], f, r, F, T);
+                }
+            }
+            wave_lds_sync();  // the list and a shared round's forces lie in the same place
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_wave_barrier();
-        longest = longest_left();
+        share = 4 * __popcll(__ballot(next < end));
     }
 }
 
@@ -213,7 +346,7 @@ struct IntPartial {
     double kin, rot, grav, damp, fsum, fcnt;
 };
 
-template <int PREC, bool BATCHED, bool PERIODIC, bool FREC>
+template <int PREC, bool BATCHED, bool PERIODIC, bool FREC, bool QUAD>
 __global__ void __launch_bounds__(kMaxBlock) k_integrate(const StepArgs* __restrict__ args, int parity)
 {
     const StepArgs& a = *args;
@@ -251,9 +384,10 @@ __global__ void __launch_bounds__(kMaxBlock) k_integrate(const StepArgs* __restr
     bool over = false;
     // the contact force sum, by every lane of the wave (a lane past the last
     // body has an empty row)
-    extern __shared__ double s_coop[];
+    extern __shared__ __align__(16) char s_rows[];
     double F[3], T[3];
-    body_sum_wave<PREC, FREC>(a, beg, end, xr0.w, F, T, s_coop + (threadIdx.x >> 6) * kCoopWords);
+    body_sum_wave<PREC, FREC, QUAD>(a, beg, end, xr0.w, F, T,
+                                    reinterpret_cast<WaveRows*>(s_rows)[threadIdx.x >> 6]);
     if (live) {
         const int s = BATCHED ? (int)glb<const uint16_t>(a.bod.scene)[i] : 0;
         // an unbatched scene (periodic included) reads the descriptor's own
@@ -326,8 +460,10 @@ __global__ void __launch_bounds__(kMaxBlock) k_integrate(const StepArgs* __restr
             const double4 q0 = bq[i];
             double q[4] = {q0.x, q0.y, q0.z, q0.w};
             const double half = 0.5 * wn * dt;
-            const double sh = sin(half) / wn;
-            const double d0 = cos(half), d1 = w[0] * sh, d2 = w[1] * sh, d3 = w[2] * sh;
+            double sn, cs;
+            sincos(half, &sn, &cs);
+            const double sh = sn / wn;
+            const double d0 = cs, d1 = w[0] * sh, d2 = w[1] * sh, d3 = w[2] * sh;
             const double n0 = d0 * q[0] - d1 * q[1] - d2 * q[2] - d3 * q[3];
             const double n1 = d0 * q[1] + d1 * q[0] + d2 * q[3] - d3 * q[2];
             const double n2 = d0 * q[2] - d1 * q[3] + d2 * q[0] + d3 * q[1];
@@ -689,16 +825,32 @@ __global__ void __launch_bounds__(kMeasureBlock) k_body_measures(StepArgs a, int
     }
 }
 
+template <int PREC, bool BATCHED, bool PERIODIC, bool FREC, bool QUAD>
+void launch_q(const StepArgs* args, int parity, int grid, int block, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1)
+{
+    const dim3 g(grid > 0 ? grid : 1), b(block);
+    // each wave's list and shared rounds
+    const size_t lds = sizeof(WaveRows) * (size_t)((block + 63) / 64);
+    if (ev0)
+        hipExtLaunchKernelGGL((k_integrate<PREC, BATCHED, PERIODIC, FREC, QUAD>), g, b, lds, st, ev0, ev1, 0, args,
+                              parity);
+    else
+        hipLaunchKernelGGL((k_integrate<PREC, BATCHED, PERIODIC, FREC, QUAD>), g, b, lds, st, args, parity);
+}
+
+// Bodies from which the history records are read by quads (body_sum_wave).
+constexpr int64_t kQuadBodies = 400000;
+
 template <int PREC, bool BATCHED, bool PERIODIC, bool FREC>
 void launch_t(const StepArgs* args, int parity, int grid, int block, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1)
 {
-    const dim3 g(grid > 0 ? grid : 1), b(block);
-    // each wave's LDS slice for the long rows' cooperative walk
-    const size_t lds = sizeof(double) * kCoopWords * (size_t)((block + 63) / 64);
-    if (ev0)
-        hipExtLaunchKernelGGL((k_integrate<PREC, BATCHED, PERIODIC, FREC>), g, b, lds, st, ev0, ev1, 0, args, parity);
-    else
-        hipLaunchKernelGGL((k_integrate<PREC, BATCHED, PERIODIC, FREC>), g, b, lds, st, args, parity);
+    if constexpr (!FREC) {
+        if ((int64_t)grid * block > kQuadBodies) {
+            launch_q<PREC, BATCHED, PERIODIC, FREC, true>(args, parity, grid, block, st, ev0, ev1);
+            return;
+        }
+    }
+    launch_q<PREC, BATCHED, PERIODIC, FREC, false>(args, parity, grid, block, st, ev0, ev1);
 }
 
 template <int PREC, bool FREC>

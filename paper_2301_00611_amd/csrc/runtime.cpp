@@ -883,7 +883,7 @@ struct World {
         for (const DBuf* d : {&ent_slot, &ent_pid, &ent_cell, &ent_own, &own_scan, &rows_ent, &raw_slot, &raw_pid,
                               &raw_cell, &ent_body})
             b = std::min(b, d->bytes);
-        return (int64_t)std::min<size_t>(b / 4, 0x7ffffff0u) - 1;
+        return (int64_t)std::min<size_t>(b / 4, 0x7ffffff0u) - 1 - kRowPad;
     }
     int64_t pair_room(bool f32) const
     {
@@ -1187,7 +1187,7 @@ struct World {
                     lim_ent = h_n[0];
                     for (DBuf* d : {&ent_slot, &ent_pid, &ent_cell, &ent_own, &own_scan, &rows_ent, &raw_slot,
                                     &raw_pid, &raw_cell, &ent_body})
-                        d->ensure(4 * ((size_t)lim_ent + 1));
+                        d->ensure(4 * ((size_t)lim_ent + 1 + kRowPad));
                 }
                 sw.raw_slot = raw_slot.as<int32_t>();
                 sw.raw_pid = raw_pid.as<int32_t>();
