@@ -147,7 +147,8 @@ typedef struct {
  * velocities, forces and contacts are bit for bit the same whatever the
  * setting; only the per-block energy partial sums regroup). */
 typedef struct {
-    int32_t block_contact;   /* threads per block of the contact kernel: 64..1024, multiple of 64 */
+    int32_t block_contact;   /* threads per block of the contact kernel: 64..1024, multiple of 64
+                                (never changed from 256: fewer where a launch would leave CUs idle) */
     int32_t block_integrate; /* same for the integrate kernel */
     int32_t chunk;           /* steps per captured HIP graph: even, 2..4096 */
     int32_t pad;

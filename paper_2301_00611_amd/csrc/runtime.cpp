@@ -323,7 +323,9 @@ struct World {
     double rebuild_ms_total = 0.0;
     DBuf d_acct;
     int64_t n_candidates = 0;
-    int block_contact = 256, block_integrate = 256;
+    int block_contact = 256, block_integrate = 256;  // as tuned
+    bool blocks_tuned[2] = {false, false};           // set to another value than the default once
+    int block_c = 256, block_i = 256;                // in use (launch_block)
     int chunk = 32;
     double tuned_ms = 0.0;             // ms per step measured by the autotuner
     bool use_graph = true;
@@ -1284,11 +1286,16 @@ struct World {
         // fold the per-block slots before the grids change, then size them
         fold_slots(slots_fetched);
         // the contact kernel gives each of the 8 XCDs one eighth of the
-        // pairs: at least ceil(ceil(npairs / 8) / block) blocks per XCD
-        const int per_xcd = (int)((((int64_t)npairs + 7) / 8 + block_contact - 1) / block_contact);
-        if ((int64_t)grid_c * block_contact < npairs || grid_c < 8 * per_xcd || grid_c < 1)
-            grid_c = std::max({(int)(((int64_t)npairs * 5 / 4 + block_contact - 1) / block_contact), 8 * per_xcd, 1});
-        grid_i = std::max((nslots + block_integrate - 1) / block_integrate, 1);
+        // pairs: at least ceil(ceil(npairs / 8) / block) blocks per XCD; a
+        // grid with room (and its block) is kept, and its graphs with it
+        const int want_c = launch_block(0, npairs);
+        auto per_xcd = [&](int b) { return (int)((((int64_t)npairs + 7) / 8 + b - 1) / b); };
+        if (block_c < want_c || (int64_t)grid_c * block_c < npairs || grid_c < 8 * per_xcd(block_c) || grid_c < 1) {
+            block_c = want_c;
+            grid_c = std::max({(int)(((int64_t)npairs * 5 / 4 + block_c - 1) / block_c), 8 * per_xcd(block_c), 1});
+        }
+        block_i = launch_block(1, nslots);
+        grid_i = std::max((nslots + block_i - 1) / block_i, 1);
         d_part_c.ensure(sizeof(ContactAcc) * (size_t)grid_c);
         d_part_i.ensure(sizeof(IntAcc) * (size_t)grid_i);
         acc_c_n = grid_c;
@@ -1470,6 +1477,22 @@ struct World {
         t.ms_per_step = tuned_ms;
         return t;
     }
+    // Threads per block of a step kernel (0 contact, 1 integrate) over n
+    // items.  Unless tuned, a launch that would have fewer blocks of 256 than
+    // the chip has CUs (256) is cut into smaller ones, down to one wave: a
+    // small scene's waves wait on memory and on instructions, and do so
+    // faster spread over idle CUs than four to one.  us per step in blocks of
+    // 256 / 128 / 64: 1,000 spheres 14.4 / 13.1 / 12.8, 9,000 12.9 / 12.0 /
+    // 11.7, 32,000 dense 27.2 / 25.3 / 25.3; from 60,000 on none is better
+    // by more than the runs differ, and 8 M take 2080 / 2065 / 2110.  The
+    // controlled cell keeps its blocks: its controller feeds their sums back.
+    int launch_block(int kernel, int64_t n) const
+    {
+        int b = kernel == 0 ? block_contact : block_integrate;
+        if (blocks_tuned[kernel] || pt_active) return b;
+        while (b > 64 && n < (int64_t)256 * b) b /= 2;
+        return b;
+    }
     void set_tuning(const dem_tuning& t)
     {
         auto ok_block = [](int b) { return b >= 64 && b <= 1024 && b % 64 == 0; };
@@ -1478,6 +1501,8 @@ struct World {
         if (t.chunk < 2 || t.chunk > 4096 || t.chunk % 2) fail(DEM_EINVAL, "tuning: chunk must be even, 2..4096");
         if (!(t.verlet_factor >= 0.0) || !(t.verlet_factor <= 4.0))
             fail(DEM_EINVAL, "tuning: verlet_factor must be in [0, 4] (0 keeps each scene's own verlet_dist)");
+        blocks_tuned[0] = blocks_tuned[0] || t.block_contact != block_contact;
+        blocks_tuned[1] = blocks_tuned[1] || t.block_integrate != block_integrate;
         block_contact = t.block_contact;
         block_integrate = t.block_integrate;
         chunk = t.chunk;
@@ -1561,6 +1586,11 @@ struct World {
             }
         }
         dem_tuning best = tuning();
+        // every block size is tried as itself, the first as the one in use
+        best.block_contact = block_c;
+        best.block_integrate = block_i;
+        blocks_tuned[0] = blocks_tuned[1] = true;
+        set_tuning(best);
         probe(probe_steps);  // warm the current setting (graph capture, first broad phase)
         best.ms_per_step = probe(probe_steps);
         const int blocks[] = {64, 128, 256, 512, 1024};
@@ -1648,10 +1678,10 @@ struct World {
     void launch_step(int parity, hipEvent_t* ev, bool measure)
     {
         const StepArgs* a = d_args.as<StepArgs>();
-        launch_contact(a, parity, grid_c, precision, batched(), periodic, block_contact, stream, ev ? ev[0] : nullptr,
+        launch_contact(a, parity, grid_c, precision, batched(), periodic, block_c, stream, ev ? ev[0] : nullptr,
                        ev ? ev[1] : nullptr, periodic && pt_active && measure, has_prims(), has_viscel());
         launch_integrate(a, parity, grid_i, precision, batched(), periodic, uses_force_records(precision, has_viscel()),
-                         block_integrate, stream, ev ? ev[2] : nullptr, ev ? ev[3] : nullptr);
+                         block_i, stream, ev ? ev[2] : nullptr, ev ? ev[3] : nullptr);
         if (periodic && pt_active && measure) launch_ctrl_reduce(a, parity, stream);
         if (periodic) launch_cell_update(a, parity, stream);
     }
@@ -1665,7 +1695,7 @@ struct World {
     {
         char buf[256];
         std::snprintf(buf, sizeof buf, "%p/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d/%d", d_args.p, grid_c, grid_i, n,
-                      timing ? 1 : 0, block_contact, block_integrate, pt_active ? 1 : 0, ctrl_period(), phase,
+                      timing ? 1 : 0, block_c, block_i, pt_active ? 1 : 0, ctrl_period(), phase,
                       has_prims() ? 1 : 0, has_viscel() ? 1 : 0);
         return buf;
     }
