@@ -313,15 +313,22 @@ struct History {
 // a single writer, and energies / contact counts go to per-block slots.
 struct Counters {
     int32_t stall[2];               // by step parity: a broad-phase run is needed before the next step
-    int32_t steps_done;             // steps completed since the host last reset it (block 0 of integrate)
+    int32_t steps_done;             // steps completed since the last broad-phase run (block 0 of integrate)
     int32_t halt;                   // the controlled cell reached its goal: the launch chain stops
-    int64_t iter0;                  // the scene's iteration count when the host last reset steps_done
+    int64_t iter0;                  // the scene's iteration count when steps_done was 0
     int32_t nonfinite;              // a NaN/Inf position or velocity appeared
     int32_t unstable;               // an overlap exceeded a radius
     double verlet_limit;            // per-body displacement budget (0.98 Delta L)
     double verlet_cell_step;        // mean-field share of the budget used per step (periodic)
     int32_t measure;                // this step ends an update period of the controlled cell (set by contact)
-    int32_t pad_;
+    uint32_t reports;               // chains of steps reported to the host (k_report)
+};
+// The counters after a chain of steps as the host sees them: a ring in pinned
+// memory, report number seq in place seq % kReports.
+constexpr int kReports = 4;
+struct alignas(128) Report {
+    Counters c;
+    uint32_t seq;
 };
 
 // The stress/strain-controlled periodic cell (PeriTriaxController driven by
@@ -560,6 +567,8 @@ void launch_integrate(const StepArgs* args, int parity, int grid, int precision,
 // controlled cell is on and the step is one of its updates) the
 // controller, from the contact and integrate kernels' partial sums.
 void launch_cell_update(const StepArgs* args, int parity, hipStream_t st);
+// After a chain of steps: the counters into the host's ring.
+void launch_report(const StepArgs* args, Report* ring, hipStream_t st);
 // After a broad-phase run: the step descriptor and the counters are written,
 // the per-block slots of both step kernels cleared (a kernel's arguments carry
 // the values, so nothing is copied from host memory).

@@ -903,6 +903,28 @@ __global__ void __launch_bounds__(256) k_publish(StepArgs a, Counters c, StepArg
     }
 }
 
+// One wave: the counters' words, then the number that the host waits for.
+__global__ void __launch_bounds__(64) k_report(const StepArgs* __restrict__ args, Report* __restrict__ ring)
+{
+    Counters* const ctr = args->ctr;
+    const uint32_t seq = ctr->reports + 1u;
+    Report& r = ring[seq % kReports];
+    constexpr int kWords = sizeof(Counters) / 4;
+    if (threadIdx.x < kWords)
+        reinterpret_cast<uint32_t*>(&r.c)[threadIdx.x] = reinterpret_cast<const uint32_t*>(ctr)[threadIdx.x];
+    __threadfence_system();
+    __builtin_amdgcn_wave_barrier();
+    if (threadIdx.x == 0) {
+        ctr->reports = seq;
+        __hip_atomic_store(&r.seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
+void launch_report(const StepArgs* args, Report* ring, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_report, dim3(1), dim3(64), 0, st, args, ring);
+}
+
 void launch_publish(const StepArgs& a, const Counters& c, StepArgs* dst, int nslots_contact, int nslots_integrate,
                     hipStream_t st)
 {

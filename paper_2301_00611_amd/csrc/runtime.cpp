@@ -300,7 +300,12 @@ struct World {
     std::vector<SceneParams> sp;       // host copy of the scene table
     Counters* h_ctr = nullptr;         // pinned
     HBuf h_slots_c, h_slots_i;         // the per-block slots as read back
-    // pinned: what the host writes into the counters before a launch chain
+    Report* h_report = nullptr;        // pinned ring: the counters after each chain of steps
+    uint32_t reports = 0;              // chains launched
+    int32_t steps_seen = 0;            // steps_done of the last chain heard of
+    bool resync = true;                // the device's counters are not known to match
+    int64_t last_interval = 0;         // steps between the last two broad-phase runs
+    // pinned: what the host writes into the counters where they may not match
     // (steps_done = 0, halt = 0, iter0), the 16 bytes from steps_done on
     struct ChunkStart {
         int32_t steps_done, halt;
@@ -371,6 +376,8 @@ struct World {
         h_scenes.release();
         if (h_chunk) (void)hipHostFree(h_chunk);
         h_chunk = nullptr;
+        if (h_report) (void)hipHostFree(h_report);
+        h_report = nullptr;
         if (own_stream && stream) (void)hipStreamDestroy(stream);
         stream = nullptr;
     }
@@ -418,6 +425,8 @@ struct World {
                       "the chunk-start fields are contiguous");
         HIPC(hipHostMalloc(reinterpret_cast<void**>(&h_chunk), sizeof(ChunkStart), hipHostMallocDefault));
         std::memset(h_chunk, 0, sizeof(ChunkStart));
+        HIPC(hipHostMalloc(reinterpret_cast<void**>(&h_report), sizeof(Report) * kReports, hipHostMallocDefault));
+        std::memset(h_report, 0, sizeof(Report) * kReports);
         d_ctrl_cfg.ensure(sizeof(CtrlConfig));
         d_ctrl_state.ensure(sizeof(CtrlState));
         HIPC(hipMemsetAsync(d_ctrl_cfg.p, 0, sizeof(CtrlConfig), stream));
@@ -1313,7 +1322,10 @@ struct World {
         C.nonfinite = 0;  // positions are finite (checked above); an earlier
         C.unstable = 0;   // failure was repaired with dem_set_state
         C.measure = 0;
+        C.reports = reports;
         next_parity = 0;
+        steps_seen = 0;
+        resync = false;
         // the descriptor, the counters and clear slots in one launch
         d_acc_ctrl.ensure(sizeof(double) * (size_t)kNetworkWords * std::max(grid_c, 1));
         d_acc_ctrl2.ensure(sizeof(double) * (size_t)(kNetworkWords + 2) * kCtrlReduceGrid);
@@ -1323,6 +1335,7 @@ struct World {
         need_rebuild = false;
         state_set = false;
         ++rebuilds;
+        if (scenes[0].iter > iter_at_rebuild) last_interval = scenes[0].iter - iter_at_rebuild;
         iter_at_rebuild = scenes[0].iter;
         // what is left of the run on the device is two short launches
         last_rebuild_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - rb_t0).count();
@@ -1688,7 +1701,7 @@ struct World {
     // phase of the controlled cell's update period at a launch chain's first
     // step; step i of the chain ends a period when (phase + i + 1) % period == 0
     int ctrl_period() const { return pt_active ? std::max(pt_glob_update, 1) : 1; }
-    int ctrl_phase() const { return pt_active ? (int)(scenes[0].iter % ctrl_period()) : 0; }
+    int ctrl_phase(int64_t iter) const { return pt_active ? (int)(iter % ctrl_period()) : 0; }
     bool measure_step(int phase, int i) const { return pt_active && (phase + i + 1) % ctrl_period() == 0; }
 
     std::string graph_key(int n, int phase) const
@@ -1705,21 +1718,55 @@ struct World {
         const std::string key = graph_key(n, phase);
         auto it = graphs.find(key);
         if (it != graphs.end()) return it->second;
-        if (graphs.size() > 16) invalidate_graphs();
+        if (graphs.size() > 16) {
+            HIPC(hipStreamSynchronize(stream));  // one may be running
+            invalidate_graphs();
+        }
         GraphEntry ge;
         hipGraph_t g;
         HIPC(hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal));
         for (int i = 0; i < n; ++i) launch_step(i & 1, nullptr, measure_step(phase, i));
+        launch_report(d_args.as<StepArgs>(), h_report, stream);
         HIPC(hipStreamEndCapture(stream, &g));
         HIPC(hipGraphInstantiate(&ge.exec, g, nullptr, nullptr, 0));
         HIPC(hipGraphDestroy(g));
         return graphs.emplace(key, std::move(ge)).first->second;
     }
 
-    void read_counters()
+    // One chain of steps on its way: its steps, and the parity after it.
+    struct Chain {
+        int n, parity;
+        uint32_t seq;
+    };
+    // Waits for a chain's report and copies the counters to *h_ctr.  A chain
+    // is short (some 0.4 ms where waiting matters), so the report is watched
+    // for.  With the counters copied both ways around a stream
+    // synchronisation 26 us passed between two chains; now 5 with a second
+    // chain behind the first (run_steps).
+    // `last`: nothing follows, and the caller gets an idle stream.
+    void wait_report(const Chain& c, bool last)
     {
-        HIPC(hipMemcpyAsync(h_ctr, d_ctr.p, sizeof(Counters), hipMemcpyDeviceToHost, stream));
-        HIPC(hipStreamSynchronize(stream));
+        const Report& r = h_report[c.seq % kReports];
+        auto there = [&] { return __atomic_load_n(&r.seq, __ATOMIC_ACQUIRE) == c.seq; };
+        if (last) {
+            HIPC(hipStreamSynchronize(stream));
+        } else {
+            const auto t0 = std::chrono::steady_clock::now();
+            int64_t looks = 0;
+            while (!there()) {
+                if (++looks % 256) continue;
+                const auto waited = std::chrono::steady_clock::now() - t0;
+                if (waited < std::chrono::milliseconds(2)) continue;
+                // a long chain: let the processor go, and find out about a
+                // device that has failed
+                const hipError_t e = hipStreamQuery(stream);
+                if (e == hipSuccess) break;
+                if (e != hipErrorNotReady) HIPC(e);
+                std::this_thread::sleep_for(std::chrono::microseconds(50));
+            }
+        }
+        if (!there()) fail(DEM_EDEVICE, "a chain of steps ended without its report");
+        *h_ctr = r.c;
     }
 
     void add_time(const char* name, hipEvent_t a, hipEvent_t b)
@@ -1801,80 +1848,126 @@ struct World {
             return false;
         }
         bool halted = false;
-        int64_t remaining = nsteps;
+        int64_t remaining = nsteps;  // steps not known to be done
+        int64_t ahead = 0;           // of these, launched
+        std::vector<Chain> chains;   // launched and not heard of, oldest first
         std::vector<hipEvent_t> direct_ev;
         hipEvent_t rb0 = nullptr, rb1 = nullptr;
         if (timing) {
             HIPC(hipEventCreate(&rb0));
             HIPC(hipEventCreate(&rb1));
         }
+        // A chain has `chunk` steps, or a quarter of them around the step where
+        // the next broad-phase request is expected (the last interval, less 15
+        // and plus 25 per cent): the steps behind a request are empty
+        // launches (3.3 us each).  A second chain is launched behind the one
+        // under way, so that the device goes straight on, where it
+        // will probably run or is short.
+        const int part = std::max(chunk / 8 * 2, 2);
+        auto chain_length = [&]() {
+            const int64_t at = scenes[0].iter - iter_at_rebuild + ahead;
+            const bool near = 20 * (at + chunk) > 17 * last_interval && 4 * at < 5 * last_interval;
+            return (int)std::min<int64_t>(remaining - ahead, near ? part : chunk);
+        };
+        auto follow = [&](int n) {
+            if (!use_graph || timing || next_parity != 0 || n < part) return false;
+            const int64_t since = scenes[0].iter - iter_at_rebuild;
+            return n == part || 4 * (since + ahead + n) <= 3 * last_interval || since >= 4 * n;
+        };
         try {
             while (remaining > 0) {
-                if (need_rebuild || h_ctr->stall[next_parity ^ 1]) {
-                    if (timing) HIPC(hipEventRecord(rb0, stream));
-                    rebuild();
-                    if (timing) {
-                        HIPC(hipEventRecord(rb1, stream));
-                        HIPC(hipEventSynchronize(rb1));
-                        add_time("rebuild", rb0, rb1);
+                if (chains.empty()) {
+                    if (need_rebuild || h_ctr->stall[next_parity ^ 1]) {
+                        if (timing) HIPC(hipEventRecord(rb0, stream));
+                        rebuild();
+                        if (timing) {
+                            HIPC(hipEventRecord(rb1, stream));
+                            HIPC(hipEventSynchronize(rb1));
+                            add_time("rebuild", rb0, rb1);
+                        }
+                    }
+                    if (resync || h_ctr->iter0 + steps_seen != scenes[0].iter) {
+                        HIPC(hipMemcpyAsync(h_ctr, d_ctr.p, sizeof(Counters), hipMemcpyDeviceToHost, stream));
+                        HIPC(hipStreamSynchronize(stream));
+                        reports = h_ctr->reports;
+                        h_ctr->steps_done = steps_seen = 0;
+                        h_chunk->steps_done = 0;
+                        h_chunk->halt = 0;
+                        h_ctr->iter0 = h_chunk->iter0 = scenes[0].iter;
+                        HIPC(hipMemcpyAsync(reinterpret_cast<char*>(d_ctr.p) + offsetof(Counters, steps_done), h_chunk,
+                                            sizeof(ChunkStart), hipMemcpyHostToDevice, stream));
+                        resync = false;
                     }
                 }
-                h_ctr->steps_done = 0;
-                h_chunk->steps_done = 0;
-                h_chunk->halt = 0;
-                h_chunk->iter0 = scenes[0].iter;
-                HIPC(hipMemcpyAsync(reinterpret_cast<char*>(d_ctr.p) + offsetof(Counters, steps_done), h_chunk,
-                                    sizeof(ChunkStart), hipMemcpyHostToDevice, stream));
-                // graphs hold an even number of steps starting at parity 0
-                const int n = (int)std::min<int64_t>(remaining, chunk);
-                GraphEntry* ge = nullptr;
-                const int par0 = next_parity;
-                // timing mode launches directly: kernel events come from the
-                // dispatch packets, which graph nodes do not expose here
-                if (use_graph && !timing && n == chunk && chunk % 2 == 0 && par0 == 0) {
-                    ge = &get_graph(n, ctrl_phase());
-                    HIPC(hipGraphLaunch(ge->exec, stream));
-                } else {
-                    if (timing && direct_ev.size() < 4 * (size_t)n) {
-                        const size_t old = direct_ev.size();
-                        direct_ev.resize(4 * (size_t)n);
-                        for (size_t q = old; q < direct_ev.size(); ++q) HIPC(hipEventCreate(&direct_ev[q]));
+                while (remaining > ahead && chains.size() < 2) {
+                    // graphs hold an even number of steps starting at parity 0
+                    const int n = chain_length();
+                    if (!chains.empty() && !follow(n)) break;
+                    const int par0 = next_parity, phase = ctrl_phase(scenes[0].iter + ahead);
+                    // timing mode launches directly: kernel events come from the
+                    // dispatch packets, which graph nodes do not expose here
+                    if (use_graph && !timing && (n == chunk || n == part) && par0 == 0) {
+                        HIPC(hipGraphLaunch(get_graph(n, phase).exec, stream));
+                    } else {
+                        if (timing && direct_ev.size() < 4 * (size_t)n) {
+                            const size_t old = direct_ev.size();
+                            direct_ev.resize(4 * (size_t)n);
+                            for (size_t q = old; q < direct_ev.size(); ++q) HIPC(hipEventCreate(&direct_ev[q]));
+                        }
+                        for (int i = 0; i < n; ++i)
+                            launch_step((par0 + i) & 1, timing ? &direct_ev[4 * (size_t)i] : nullptr,
+                                        measure_step(phase, i));
+                        launch_report(d_args.as<StepArgs>(), h_report, stream);
                     }
-                    for (int i = 0; i < n; ++i)
-                        launch_step((par0 + i) & 1, timing ? &direct_ev[4 * (size_t)i] : nullptr,
-                                    measure_step(ctrl_phase(), i));
+                    HIPC(hipGetLastError());
+                    next_parity = (par0 + n) & 1;
+                    chains.push_back({n, next_parity, ++reports});
+                    ahead += n;
                 }
-                next_parity = (par0 + n) & 1;
-                HIPC(hipGetLastError());
-                read_counters();
-                const int done = h_ctr->steps_done;
-                if (done > 0) slots_fresh = false;
-                if (timing)
-                    for (int i = 0; i < done; ++i) {
-                        add_time("contact", direct_ev[4 * (size_t)i], direct_ev[4 * (size_t)i + 1]);
-                        add_time("integrate", direct_ev[4 * (size_t)i + 2], direct_ev[4 * (size_t)i + 3]);
+                // hear of the oldest chain, and of one behind it that a
+                // request or a failure has stopped
+                bool stalled = false, short_of = false;
+                int failed = 0;
+                do {
+                    const Chain c = chains.front();
+                    chains.erase(chains.begin());
+                    wait_report(c, chains.empty() && (remaining == ahead || timing));
+                    const int done = h_ctr->steps_done - steps_seen;
+                    steps_seen = h_ctr->steps_done;
+                    if (done > 0) slots_fresh = false;
+                    if (timing)
+                        for (int i = 0; i < done; ++i) {
+                            add_time("contact", direct_ev[4 * (size_t)i], direct_ev[4 * (size_t)i + 1]);
+                            add_time("integrate", direct_ev[4 * (size_t)i + 2], direct_ev[4 * (size_t)i + 3]);
+                        }
+                    for (auto& S : scenes) {
+                        S.iter += done;
+                        S.time += done * S.p.dt;
                     }
-                for (auto& S : scenes) {
-                    S.iter += done;
-                    S.time += done * S.p.dt;
-                }
-                remaining -= done;
-                contacts_valid = done > 0 || contacts_valid;
-                if (h_ctr->nonfinite) fail(DEM_ENONFINITE, "non-finite position or velocity after a step");
-                if (h_ctr->unstable) fail(DEM_EUNSTABLE, "an overlap exceeded a sphere radius (numerically exploding)");
-                const bool stalled = h_ctr->stall[next_parity ^ 1] != 0;
-                if (done == 0 && !stalled) fail(DEM_EDEVICE, "no step completed");
-                if (done < n && !stalled) fail(DEM_EDEVICE, "steps stopped without a broad-phase request");
+                    remaining -= done;
+                    ahead -= c.n;
+                    contacts_valid = done > 0 || contacts_valid;
+                    if (h_ctr->nonfinite) failed = DEM_ENONFINITE;
+                    else if (h_ctr->unstable) failed = DEM_EUNSTABLE;
+                    stalled = h_ctr->stall[c.parity ^ 1] != 0;
+                    short_of = short_of || (done < c.n && !stalled);
+                } while (!chains.empty() && (stalled || failed || h_ctr->halt));
+                if (failed == DEM_ENONFINITE) fail(DEM_ENONFINITE, "non-finite position or velocity after a step");
+                if (failed) fail(DEM_EUNSTABLE, "an overlap exceeded a sphere radius (numerically exploding)");
+                if (short_of) fail(DEM_EDEVICE, "steps stopped without a broad-phase request");
                 if (h_ctr->halt) {
                     // the controlled cell reached its goal; the stall flags it
                     // raised (with any broad-phase request of the same step)
                     // are cleared by the broad-phase run the next call starts with
                     halted = true;
                     need_rebuild = true;
+                    HIPC(hipStreamSynchronize(stream));
                     break;
                 }
             }
         } catch (...) {
+            (void)hipStreamSynchronize(stream);
+            if (!chains.empty()) resync = true;
             for (auto e : direct_ev) (void)hipEventDestroy(e);
             if (rb0) (void)hipEventDestroy(rb0);
             if (rb1) (void)hipEventDestroy(rb1);
