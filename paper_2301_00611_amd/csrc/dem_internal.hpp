@@ -594,12 +594,28 @@ struct StateArgs {
     const double* slot_force3;
     const double* slot_torque3;
 };
+// A body as the host holds it (kept in step only when bodies are added or
+// the state is overwritten; the device holds the truth while stepping).
+struct HostBody {
+    int kind;  // 0 sphere, 1 wall
+    int scene;
+    int wall;  // wall index when kind == 1
+    double x[3], v[3], w[3], q[4];
+    double r, m;
+    int mat;
+    uint8_t blocked;
+};
+
 struct StateOut {
     double *pos3, *vel3, *angvel3, *ori4, *force3, *torque3;
 };
 struct StateIn {
     const double *pos3, *vel3, *angvel3, *ori4;
 };
+// Records [first, first + n) of all bodies into the slots (spheres in id
+// order) and the id -> slot map; fixed: the boundaries' ids, ascending.
+void launch_unpack_bodies(const HostBody* raw, int first, int n, const int32_t* fixed, int nfixed, const Bodies& b,
+                          int32_t* slot_of_id, hipStream_t st);
 void launch_gather_state(const StateArgs& a, const StateOut& o, hipStream_t st);
 void launch_scatter_state(const StateArgs& a, const StateIn& in, hipStream_t st);
 // boundary pairs that touched at the last step: flags (npairs + 1), then,

@@ -226,18 +226,6 @@ struct HostScene {
     int64_t n_large = 0;
 };
 
-// Host copy of everything per gid (kept in step only when bodies are added
-// or the state is overwritten; the device holds the truth while stepping).
-struct HostBody {
-    int kind;  // 0 sphere, 1 wall
-    int scene;
-    int wall;  // wall index when kind == 1
-    double x[3], v[3], w[3], q[4];
-    double r, m;
-    int mat;
-    uint8_t blocked;
-};
-
 struct KernelTimer {
     double total_ms = 0.0;
     int64_t launches = 0;
@@ -313,6 +301,7 @@ struct World {
     };
     ChunkStart* h_chunk = nullptr;
     int ncells = 0;
+    DBuf d_stage, d_fixed;              // uploads: body records, the boundaries' ids
     DBuf d_flag;                       // broad phase: a body's period out of the packed range
     DBuf d_bpart;                      // bounds partials
     HBuf h_read;                       // pinned: what a broad-phase run reads back
@@ -366,7 +355,7 @@ struct World {
                         &d_scenes, &d_walls, &d_mats, &d_tanphi, &d_ctr, &d_part_c, &d_part_i, &d_bounds, &d_total,
                         &d_tmp3, &d_args, &d_ctrl_cfg, &d_ctrl_state, &d_acc_ctrl, &d_acc_ctrl2, &pb_ca, &pb_cb, &pb_found,
                         &pb_flag, &pb_scan, &d_flag, &d_bpart, &raw_slot, &raw_pid,
-                        &raw_cell, &ent_body, &d_acct})
+                        &raw_cell, &ent_body, &d_acct, &d_stage, &d_fixed})
             d->release();
         if (h_ctr) (void)hipHostFree(h_ctr);
         h_ctr = nullptr;
@@ -742,50 +731,28 @@ struct World {
     // ------------------------------------------------------- uploading
     void upload_bodies()
     {
-        // sphere slots in gid order; the first broad-phase run sorts them
-        std::vector<int32_t> sph;
-        for (int32_t g = 0; g < (int32_t)bodies.size(); ++g)
-            if (bodies[g].kind == 0) sph.push_back(g);
-        nslots = (int)sph.size();
-        const size_t n = std::max<size_t>(nslots, 1);
-        for (auto& b : bs) b.ensure(n);
-        BodySet& B = bs[active];
-        std::vector<double> col(4 * n);
-        // packed 4-vectors: component c of slot i goes to col[4 i + c]
-        auto push = [&](DBuf& d, auto get) {
-            for (int i = 0; i < nslots; ++i) {
-                const HostBody& b = bodies[sph[i]];
-                for (int c = 0; c < 4; ++c) col[4 * (size_t)i + c] = get(b, c);
-            }
-            HIPC(hipMemcpyAsync(d.p, col.data(), 32 * (size_t)nslots, hipMemcpyHostToDevice, stream));
-            HIPC(hipStreamSynchronize(stream));
-        };
-        push(B.xr, [](const HostBody& b, int c) { return c < 3 ? b.x[c] : b.r; });
-        push(B.vm, [](const HostBody& b, int c) { return c < 3 ? b.v[c] : 0.0; });  // fresh Verlet account
-        push(B.w, [](const HostBody& b, int c) { return c < 3 ? b.w[c] : 0.0; });
-        push(B.q, [](const HostBody& b, int c) { return b.q[c]; });
-        std::vector<uint8_t> u8(n);
-        std::vector<int32_t> i32(n);
-        std::vector<uint16_t> u16(n);
-        std::vector<uint16_t> m16(n);
-        for (int i = 0; i < nslots; ++i) m16[i] = (uint16_t)bodies[sph[i]].mat;
-        HIPC(hipMemcpyAsync(B.mat.p, m16.data(), 2 * (size_t)nslots, hipMemcpyHostToDevice, stream));
-        HIPC(hipStreamSynchronize(stream));
-        for (int i = 0; i < nslots; ++i) u8[i] = bodies[sph[i]].blocked;
-        HIPC(hipMemcpyAsync(B.blocked.p, u8.data(), (size_t)nslots, hipMemcpyHostToDevice, stream));
-        HIPC(hipStreamSynchronize(stream));
-        for (int i = 0; i < nslots; ++i) i32[i] = sph[i];
-        HIPC(hipMemcpyAsync(B.id.p, i32.data(), 4 * (size_t)nslots, hipMemcpyHostToDevice, stream));
-        for (int i = 0; i < nslots; ++i) u16[i] = (uint16_t)bodies[sph[i]].scene;
-        HIPC(hipMemcpyAsync(B.scene.p, u16.data(), 2 * (size_t)nslots, hipMemcpyHostToDevice, stream));
-        HIPC(hipStreamSynchronize(stream));
-        // gid -> slot
+        // sphere slots in gid order; the first broad-phase run sorts them.  The
+        // records go up as they are, a chunk at a time, and the device takes
+        // them apart.
         const int ng = (int)bodies.size();
+        nslots = ng - (int)walls.size();
+        for (auto& b : bs) b.ensure(std::max<size_t>(nslots, 1));
         slot_of_id.ensure(4 * (size_t)std::max(ng, 1));
-        std::vector<int32_t> sl((size_t)std::max(ng, 1), -1);
-        for (int i = 0; i < nslots; ++i) sl[sph[i]] = i;
-        for (int i = 0; i < (int)walls.size(); ++i) sl[walls[i].id] = -1 - i;
-        HIPC(hipMemcpyAsync(slot_of_id.p, sl.data(), 4 * (size_t)ng, hipMemcpyHostToDevice, stream));
+        std::vector<int32_t> fixed(std::max<size_t>(walls.size(), 1), 0);
+        for (size_t i = 0; i < walls.size(); ++i) fixed[i] = walls[i].id;
+        std::sort(fixed.begin(), fixed.begin() + walls.size());
+        d_fixed.ensure(4 * fixed.size());
+        HIPC(hipMemcpyAsync(d_fixed.p, fixed.data(), 4 * fixed.size(), hipMemcpyHostToDevice, stream));
+        d_stage.ensure(sizeof(HostBody) * (size_t)std::max(std::min(ng, kUploadChunk), 1));
+        for (int g = 0; g < ng; g += kUploadChunk) {
+            const int m = std::min(ng - g, kUploadChunk);
+            HIPC(hipMemcpyAsync(d_stage.p, bodies.data() + g, sizeof(HostBody) * (size_t)m, hipMemcpyHostToDevice, stream));
+            launch_unpack_bodies(d_stage.as<HostBody>(), g, m, d_fixed.as<int32_t>(), (int)walls.size(),
+                                 bs[active].view(), slot_of_id.as<int32_t>(), stream);
+            HIPC(hipGetLastError());
+        }
+        HIPC(hipStreamSynchronize(stream));
+        d_stage.release();
         // a batch's scenes: their gids one after another (a single scene's ids are its gids)
         std::vector<int32_t> gid_table;
         if (batched()) {
@@ -2193,6 +2160,7 @@ struct World {
 
     // doubles per body of pos, vel, angvel, ori, force, torque
     static constexpr size_t kStateWords[6] = {3, 3, 3, 4, 3, 3};
+    static constexpr int kUploadChunk = 1 << 18;     // 38 MB of body records
     static constexpr int64_t kStateChunk = 1 << 20;  // 159 MB of scratch
     StateArgs state_args(int s, int64_t first) const
     {
