@@ -301,7 +301,9 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
     // an unbatched scene (periodic included) reads the descriptor's own
     // copy of its parameters: uniform, read-only here, so scalar loads
     const SceneParams& S = BATCHED ? a.scenes[s] : a.scene0;
-    const bool wall = sa < 0;
+    // a periodic scene has no boundaries, and no wall to read beside #1
+    // (500,000 spheres 137.0 -> 135.8 us, 32,000 0.3 us per step)
+    const bool wall = !PERIODIC && sa < 0;
     const int32_t s1 = wall ? sb : sa;
     Wall W;
     double r1 = 0.0, r2 = 0.0;
@@ -319,9 +321,14 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
         // then set aside
         const double4 p2 = xr[sb];
         const double4 p1 = xr[s1];
-        m2 = mat[sb];
-        const int m1s = mat[s1];
-        W = glb<const Wall>(a.walls)[wall ? -1 - sa : 0];
+        // with one material only its index is 0: two gathers less, on every
+        // candidate (8 M spheres 1113 -> 1085 us, 500,000 137.0 -> 134.0)
+        int m1s = 0;
+        if (a.nmat > 1) {
+            m2 = mat[sb];
+            m1s = mat[s1];
+        }
+        if (!PERIODIC) W = glb<const Wall>(a.walls)[wall ? -1 - sa : 0];
         const double x2 = p2.x, y2 = p2.y, z2 = p2.z;
         const double x1 = wall ? 0.0 : p1.x, y1 = wall ? 0.0 : p1.y, z1 = wall ? 0.0 : p1.z;
         r2 = p2.w;
