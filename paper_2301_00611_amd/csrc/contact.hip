@@ -254,7 +254,8 @@ struct ContactPartial {
 template <bool VISCEL>
 constexpr int kContactWaves = VISCEL ? 5 : 6;
 
-template <int PREC, bool BATCHED, bool PERIODIC, bool MEASURE = false, bool PRIMS = false, bool VISCEL = false>
+template <int PREC, bool BATCHED, bool PERIODIC, bool MEASURE = false, bool PRIMS = false, bool VISCEL = false,
+          bool LARGE = false>
 __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(kContactWaves<VISCEL>))) k_contact(const StepArgs* __restrict__ args, int parity)
 {
     using R = typename std::conditional<PREC == DEM_FP32_MIXED, float, double>::type;
@@ -271,9 +272,9 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
     int32_t sa = 0, sb = 0, pcell = 0;
     uint8_t was_real = 0;
     if (k >= 0) {
-        sa = glb<const int32_t>(a.pr.a)[k];
-        sb = glb<const int32_t>(a.pr.b)[k];
-        if (PERIODIC) pcell = glb<const int32_t>(a.pr.cell)[k];
+        sa = load_once<LARGE, int32_t>(glb<const int32_t>(a.pr.a) + k);
+        sb = load_once<LARGE, int32_t>(glb<const int32_t>(a.pr.b) + k);
+        if (PERIODIC) pcell = load_once<LARGE, int32_t>(glb<const int32_t>(a.pr.cell) + k);
         was_real = glb<const uint8_t>(a.pr.real)[k];
     }
     // the previous step asked for a broad-phase run: this step does not run
@@ -656,16 +657,40 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
     }
 }
 
-template <int PREC, bool BATCHED, bool PERIODIC, bool MEASURE = false, bool PRIMS = false, bool VISCEL = false>
+template <int PREC, bool BATCHED, bool PERIODIC, bool MEASURE = false, bool PRIMS = false, bool VISCEL = false,
+          bool LARGE = false>
 void launch_t(const StepArgs* args, int parity, int grid, int block, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1)
 {
     const dim3 g(grid > 0 ? grid : 1), b(block);
     const size_t lds = (size_t)kWaveBytes<PREC> * (size_t)((block + 63) / 64);
     if (ev0)
-        hipExtLaunchKernelGGL((k_contact<PREC, BATCHED, PERIODIC, MEASURE, PRIMS, VISCEL>), g, b, lds, st, ev0, ev1, 0,
+        hipExtLaunchKernelGGL((k_contact<PREC, BATCHED, PERIODIC, MEASURE, PRIMS, VISCEL, LARGE>), g, b, lds, st, ev0, ev1, 0,
                               args, parity);
     else
-        hipLaunchKernelGGL((k_contact<PREC, BATCHED, PERIODIC, MEASURE, PRIMS, VISCEL>), g, b, lds, st, args, parity);
+        hipLaunchKernelGGL((k_contact<PREC, BATCHED, PERIODIC, MEASURE, PRIMS, VISCEL, LARGE>), g, b, lds, st, args, parity);
+}
+
+template <int PREC, bool BATCHED, bool PERIODIC>
+void launch_sized(const StepArgs* args, int parity, int grid, int block, hipStream_t st, hipEvent_t ev0,
+                  hipEvent_t ev1, bool large)
+{
+    if (large)
+        launch_t<PREC, BATCHED, PERIODIC, false, false, false, true>(args, parity, grid, block, st, ev0, ev1);
+    else
+        launch_t<PREC, BATCHED, PERIODIC>(args, parity, grid, block, st, ev0, ev1);
+}
+
+// the linear law's instantiation of a scene kind, spheres and planes
+template <int PREC>
+void launch_linear(const StepArgs* args, int parity, int grid, int block, hipStream_t st, hipEvent_t ev0,
+                   hipEvent_t ev1, bool batched, bool periodic, bool large)
+{
+    if (batched)
+        launch_sized<PREC, true, false>(args, parity, grid, block, st, ev0, ev1, large);
+    else if (periodic)
+        launch_sized<PREC, false, true>(args, parity, grid, block, st, ev0, ev1, large);
+    else
+        launch_sized<PREC, false, false>(args, parity, grid, block, st, ev0, ev1, large);
 }
 
 // the visco-elastic instantiation of a scene kind: boundaries of every kind
@@ -685,7 +710,8 @@ void launch_viscel(const StepArgs* args, int parity, int grid, int block, hipStr
 }  // namespace
 
 void launch_contact(const StepArgs* args, int parity, int grid, int precision, bool batched, bool periodic,
-                    int block, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1, bool measure, bool prims, bool viscel)
+                    bool large, int block, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1, bool measure, bool prims,
+                    bool viscel)
 {
     if (viscel) {
         if (precision == DEM_FP32_MIXED)
@@ -709,15 +735,10 @@ void launch_contact(const StepArgs* args, int parity, int grid, int precision, b
         else launch_t<DEM_FP64, false, true, true>(args, parity, grid, block, st, ev0, ev1);
         return;
     }
-    if (precision == DEM_FP32_MIXED) {
-        if (batched) launch_t<DEM_FP32_MIXED, true, false>(args, parity, grid, block, st, ev0, ev1);
-        else if (periodic) launch_t<DEM_FP32_MIXED, false, true>(args, parity, grid, block, st, ev0, ev1);
-        else launch_t<DEM_FP32_MIXED, false, false>(args, parity, grid, block, st, ev0, ev1);
-    } else {
-        if (batched) launch_t<DEM_FP64, true, false>(args, parity, grid, block, st, ev0, ev1);
-        else if (periodic) launch_t<DEM_FP64, false, true>(args, parity, grid, block, st, ev0, ev1);
-        else launch_t<DEM_FP64, false, false>(args, parity, grid, block, st, ev0, ev1);
-    }
+    if (precision == DEM_FP32_MIXED)
+        launch_linear<DEM_FP32_MIXED>(args, parity, grid, block, st, ev0, ev1, batched, periodic, large);
+    else
+        launch_linear<DEM_FP64>(args, parity, grid, block, st, ev0, ev1, batched, periodic, large);
 }
 
 }  // namespace dem

@@ -391,6 +391,15 @@ struct IntAcc {
 // sum looks at a row 24 entries at a time.
 constexpr int kRowPad = 24;
 
+// Scenes of more bodies take other instantiations of the step kernels: what a
+// step reads once and in order (pair ids, orientations) passes by the caches,
+// which then hold more of what is read twice, and history records are read by
+// quads (body_sum_wave).  About there a step's data (150 bytes per body, 13 per
+// candidate and 72 per touching pair) exceed the 256 MB of the Infinity Cache.
+// us per step, cached / passing by: 230,000 spheres FP32-mixed 68 / 82, 131,000
+// under the controlled cell 69 / 73, 390,000 191 / 189, 500,000 242 / 238, 1 M
+// in shear FP32-mixed 297 / 286, 8 M 1980 / 1942.
+constexpr int kLargeBodies = 400000;
 struct StepArgs {
     Bodies bod;
     Pairs pr;
@@ -434,6 +443,15 @@ using gptr = __attribute__((address_space(1))) T*;
 template <typename T>
 using gptr = T*;
 #endif
+// A value read once: with ONCE it passes by the caches.
+template <bool ONCE, typename T>
+__device__ inline T load_once(gptr<const T> p)
+{
+    if constexpr (ONCE)
+        return __builtin_nontemporal_load(p);
+    else
+        return *p;
+}
 template <typename T>
 __device__ inline gptr<T> glb(T* p)
 {
@@ -554,15 +572,16 @@ void launch_partition(const PairBuildArgs& a, hipStream_t st);
 // captured graphs are keyed by the period's phase at their first step)
 // prims: the world holds a box or a facet (aperiodic): the instantiation
 // with their geometry runs; viscel: the world holds visco-elastic materials
-// (their instantiation, which takes every boundary kind, runs)
+// (their instantiation, which takes every boundary kind, runs); large: more
+// than kLargeBodies
 void launch_contact(const StepArgs* args, int parity, int grid, int precision, bool batched, bool periodic,
-                    int block, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr,
+                    bool large, int block, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr,
                     bool measure = false, bool prims = false, bool viscel = false);
 
 // integrate.hip
 // frec: uses_force_records(precision, world has visco-elastic materials)
 void launch_integrate(const StepArgs* args, int parity, int grid, int precision, bool batched, bool periodic,
-                      bool frec, int block, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+                      bool frec, bool large, int block, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // One block after the step: the periodic cell's update, then (when the
 // controlled cell is on and the step is one of its updates) the
 // controller, from the contact and integrate kernels' partial sums.

@@ -353,18 +353,21 @@ __device__ inline void matvec(const double* M, double x, double y, double z, dou
     o[2] = (M[6] * x + M[7] * y) + M[8] * z;
 }
 
+typedef double Quat __attribute__((ext_vector_type(4)));
+
 struct IntPartial {
     double kin, rot, grav, damp, fsum, fcnt;
 };
 
-template <int PREC, bool BATCHED, bool PERIODIC, bool FREC, bool QUAD>
+template <int PREC, bool BATCHED, bool PERIODIC, bool FREC, bool LARGE>
 __global__ void __launch_bounds__(kMaxBlock) k_integrate(const StepArgs* __restrict__ args, int parity)
 {
     const StepArgs& a = *args;
     int slot;
     const int i = logical_block(gridDim.x, &slot) * blockDim.x + threadIdx.x;
     const bool live = i < a.nslots;
-    const gptr<double4> bxr = glb(a.bod.xr), bvm = glb(a.bod.vm), bw = glb(a.bod.w), bq = glb(a.bod.q);
+    const gptr<double4> bxr = glb(a.bod.xr), bvm = glb(a.bod.vm), bw = glb(a.bod.w);
+    const gptr<Quat> bq = glb(reinterpret_cast<Quat*>(a.bod.q));
     // the previous step's stall flag is read first and tested only after the
     // body's loads are issued (they are in bounds, and nothing is stored
     // before the test), so that its latency overlaps theirs; the row bounds
@@ -398,8 +401,8 @@ __global__ void __launch_bounds__(kMaxBlock) k_integrate(const StepArgs* __restr
     // body has an empty row)
     extern __shared__ __align__(16) char s_rows[];
     double F[3], T[3];
-    body_sum_wave<PREC, FREC, QUAD>(a, beg, end, xr0.w, F, T,
-                                    reinterpret_cast<WaveRows*>(s_rows)[threadIdx.x >> 6]);
+    body_sum_wave<PREC, FREC, LARGE && !FREC>(a, beg, end, xr0.w, F, T,
+                                              reinterpret_cast<WaveRows*>(s_rows)[threadIdx.x >> 6]);
     if (live) {
         const int s = BATCHED ? (int)glb<const uint16_t>(a.bod.scene)[i] : 0;
         // an unbatched scene (periodic included) reads the descriptor's own
@@ -469,7 +472,7 @@ __global__ void __launch_bounds__(kMaxBlock) k_integrate(const StepArgs* __restr
         if (ww > 0.0) {
             // the orientation only changes (and is only read) for a spinning body
             const double wn = sqrt(ww);
-            const double4 q0 = bq[i];
+            const Quat q0 = load_once<LARGE, Quat>(bq + i);
             double q[4] = {q0.x, q0.y, q0.z, q0.w};
             const double half = 0.5 * wn * dt;
             double sn, cs;
@@ -485,7 +488,11 @@ __global__ void __launch_bounds__(kMaxBlock) k_integrate(const StepArgs* __restr
             q[1] = n1 * inv_qn;
             q[2] = n2 * inv_qn;
             q[3] = n3 * inv_qn;
-            bq[i] = make_double4(q[0], q[1], q[2], q[3]);
+            const Quat q1 = {q[0], q[1], q[2], q[3]};
+            if constexpr (LARGE)
+                __builtin_nontemporal_store(q1, bq + i);
+            else
+                bq[i] = q1;
         }
         bxr[i] = make_double4(x1[0], x1[1], x1[2], r);
         // the Verlet account (fourth word of vm): non-affine displacement of
@@ -852,55 +859,48 @@ __global__ void __launch_bounds__(kMeasureBlock) k_body_measures(StepArgs a, int
     }
 }
 
-template <int PREC, bool BATCHED, bool PERIODIC, bool FREC, bool QUAD>
-void launch_q(const StepArgs* args, int parity, int grid, int block, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1)
+template <int PREC, bool BATCHED, bool PERIODIC, bool FREC, bool LARGE>
+void launch_t(const StepArgs* args, int parity, int grid, int block, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1)
 {
     const dim3 g(grid > 0 ? grid : 1), b(block);
     // each wave's list and shared rounds
     const size_t lds = sizeof(WaveRows) * (size_t)((block + 63) / 64);
     if (ev0)
-        hipExtLaunchKernelGGL((k_integrate<PREC, BATCHED, PERIODIC, FREC, QUAD>), g, b, lds, st, ev0, ev1, 0, args,
+        hipExtLaunchKernelGGL((k_integrate<PREC, BATCHED, PERIODIC, FREC, LARGE>), g, b, lds, st, ev0, ev1, 0, args,
                               parity);
     else
-        hipLaunchKernelGGL((k_integrate<PREC, BATCHED, PERIODIC, FREC, QUAD>), g, b, lds, st, args, parity);
+        hipLaunchKernelGGL((k_integrate<PREC, BATCHED, PERIODIC, FREC, LARGE>), g, b, lds, st, args, parity);
 }
 
-// Bodies from which the history records are read by quads (body_sum_wave).
-constexpr int64_t kQuadBodies = 400000;
-
-template <int PREC, bool BATCHED, bool PERIODIC, bool FREC>
-void launch_t(const StepArgs* args, int parity, int grid, int block, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1)
-{
-    if constexpr (!FREC) {
-        if ((int64_t)grid * block > kQuadBodies) {
-            launch_q<PREC, BATCHED, PERIODIC, FREC, true>(args, parity, grid, block, st, ev0, ev1);
-            return;
-        }
-    }
-    launch_q<PREC, BATCHED, PERIODIC, FREC, false>(args, parity, grid, block, st, ev0, ev1);
-}
-
-template <int PREC, bool FREC>
+template <int PREC, bool FREC, bool LARGE>
 void launch_kind(const StepArgs* args, int parity, int grid, bool batched, bool periodic, int block, hipStream_t st,
                  hipEvent_t ev0, hipEvent_t ev1)
 {
-    if (batched) launch_t<PREC, true, false, FREC>(args, parity, grid, block, st, ev0, ev1);
-    else if (periodic) launch_t<PREC, false, true, FREC>(args, parity, grid, block, st, ev0, ev1);
-    else launch_t<PREC, false, false, FREC>(args, parity, grid, block, st, ev0, ev1);
+    if (batched) launch_t<PREC, true, false, FREC, LARGE>(args, parity, grid, block, st, ev0, ev1);
+    else if (periodic) launch_t<PREC, false, true, FREC, LARGE>(args, parity, grid, block, st, ev0, ev1);
+    else launch_t<PREC, false, false, FREC, LARGE>(args, parity, grid, block, st, ev0, ev1);
+}
+
+template <int PREC, bool FREC>
+void launch_sized(const StepArgs* args, int parity, int grid, bool batched, bool periodic, bool large, int block,
+                  hipStream_t st, hipEvent_t ev0, hipEvent_t ev1)
+{
+    if (large) launch_kind<PREC, FREC, true>(args, parity, grid, batched, periodic, block, st, ev0, ev1);
+    else launch_kind<PREC, FREC, false>(args, parity, grid, batched, periodic, block, st, ev0, ev1);
 }
 
 }  // namespace
 
 void launch_integrate(const StepArgs* args, int parity, int grid, int precision, bool batched, bool periodic,
-                      bool frec, int block, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1)
+                      bool frec, bool large, int block, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1)
 {
     // FP32-mixed always has its force records
     if (precision == DEM_FP32_MIXED)
-        launch_kind<DEM_FP32_MIXED, true>(args, parity, grid, batched, periodic, block, st, ev0, ev1);
+        launch_sized<DEM_FP32_MIXED, true>(args, parity, grid, batched, periodic, large, block, st, ev0, ev1);
     else if (frec)
-        launch_kind<DEM_FP64, true>(args, parity, grid, batched, periodic, block, st, ev0, ev1);
+        launch_sized<DEM_FP64, true>(args, parity, grid, batched, periodic, large, block, st, ev0, ev1);
     else
-        launch_kind<DEM_FP64, false>(args, parity, grid, batched, periodic, block, st, ev0, ev1);
+        launch_sized<DEM_FP64, false>(args, parity, grid, batched, periodic, large, block, st, ev0, ev1);
 }
 
 // Largest Verlet account (non-affine displacement since the last broad-phase

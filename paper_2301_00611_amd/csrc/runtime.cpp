@@ -1658,10 +1658,11 @@ struct World {
     void launch_step(int parity, hipEvent_t* ev, bool measure)
     {
         const StepArgs* a = d_args.as<StepArgs>();
-        launch_contact(a, parity, grid_c, precision, batched(), periodic, block_c, stream, ev ? ev[0] : nullptr,
+        const bool large = nslots > kLargeBodies;
+        launch_contact(a, parity, grid_c, precision, batched(), periodic, large, block_c, stream, ev ? ev[0] : nullptr,
                        ev ? ev[1] : nullptr, periodic && pt_active && measure, has_prims(), has_viscel());
         launch_integrate(a, parity, grid_i, precision, batched(), periodic, uses_force_records(precision, has_viscel()),
-                         block_i, stream, ev ? ev[2] : nullptr, ev ? ev[3] : nullptr);
+                         large, block_i, stream, ev ? ev[2] : nullptr, ev ? ev[3] : nullptr);
         if (periodic && pt_active && measure) launch_ctrl_reduce(a, parity, stream);
         if (periodic) launch_cell_update(a, parity, stream);
     }
