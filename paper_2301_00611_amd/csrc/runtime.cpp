@@ -342,6 +342,7 @@ struct World {
     }
     void release()
     {
+        if (h_report) (void)hipStreamSynchronize(stream);  // the last report may still be retiring
         for (auto& kv : graphs) {
             if (kv.second.exec) (void)hipGraphExecDestroy(kv.second.exec);
             for (auto e : kv.second.ev) (void)hipEventDestroy(e);
@@ -382,6 +383,7 @@ struct World {
 
     void invalidate_graphs()
     {
+        if (!graphs.empty()) (void)hipStreamSynchronize(stream);  // one may still be retiring
         for (auto& kv : graphs) {
             if (kv.second.exec) (void)hipGraphExecDestroy(kv.second.exec);
             for (auto e : kv.second.ev) (void)hipEventDestroy(e);
@@ -1686,10 +1688,7 @@ struct World {
         const std::string key = graph_key(n, phase);
         auto it = graphs.find(key);
         if (it != graphs.end()) return it->second;
-        if (graphs.size() > 16) {
-            HIPC(hipStreamSynchronize(stream));  // one may be running
-            invalidate_graphs();
-        }
+        if (graphs.size() > 16) invalidate_graphs();
         GraphEntry ge;
         hipGraph_t g;
         HIPC(hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal));
@@ -1710,28 +1709,30 @@ struct World {
     // is short (some 0.4 ms where waiting matters), so the report is watched
     // for.  With the counters copied both ways around a stream
     // synchronisation 26 us passed between two chains; now 5 with a second
-    // chain behind the first (run_steps).
-    // `last`: nothing follows, and the caller gets an idle stream.
-    void wait_report(const Chain& c, bool last)
+    // chain behind the first (run_steps).  The report is the last thing on the
+    // stream: every step's results are there when it is, and the runtime's own
+    // notice of it, 5 us later for one step and 12 for four, is not waited for.
+    // `alone`: no chain is behind it.
+    void wait_report(const Chain& c, bool alone)
     {
         const Report& r = h_report[c.seq % kReports];
         auto there = [&] { return __atomic_load_n(&r.seq, __ATOMIC_ACQUIRE) == c.seq; };
-        if (last) {
-            HIPC(hipStreamSynchronize(stream));
-        } else {
-            const auto t0 = std::chrono::steady_clock::now();
-            int64_t looks = 0;
-            while (!there()) {
-                if (++looks % 256) continue;
-                const auto waited = std::chrono::steady_clock::now() - t0;
-                if (waited < std::chrono::milliseconds(2)) continue;
-                // a long chain: let the processor go, and find out about a
-                // device that has failed
-                const hipError_t e = hipStreamQuery(stream);
-                if (e == hipSuccess) break;
-                if (e != hipErrorNotReady) HIPC(e);
-                std::this_thread::sleep_for(std::chrono::microseconds(50));
+        const auto t0 = std::chrono::steady_clock::now();
+        int64_t looks = 0;
+        while (!there()) {
+            if (++looks % 256) continue;
+            const auto waited = std::chrono::steady_clock::now() - t0;
+            if (waited < std::chrono::milliseconds(2)) continue;
+            // a long chain: let the processor go, and find out about a
+            // device that has failed
+            if (alone) {
+                HIPC(hipStreamSynchronize(stream));
+                break;
             }
+            const hipError_t e = hipStreamQuery(stream);
+            if (e == hipSuccess) break;
+            if (e != hipErrorNotReady) HIPC(e);
+            std::this_thread::sleep_for(std::chrono::microseconds(50));
         }
         if (!there()) fail(DEM_EDEVICE, "a chain of steps ended without its report");
         *h_ctr = r.c;
@@ -1899,7 +1900,8 @@ struct World {
                 do {
                     const Chain c = chains.front();
                     chains.erase(chains.begin());
-                    wait_report(c, chains.empty() && (remaining == ahead || timing));
+                    wait_report(c, chains.empty());
+                    if (timing) HIPC(hipStreamSynchronize(stream));  // for the events
                     const int done = h_ctr->steps_done - steps_seen;
                     steps_seen = h_ctr->steps_done;
                     if (done > 0) slots_fresh = false;
