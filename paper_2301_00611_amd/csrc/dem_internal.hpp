@@ -635,6 +635,14 @@ struct StateIn {
 // order) and the id -> slot map; fixed: the boundaries' ids, ascending.
 void launch_unpack_bodies(const HostBody* raw, int first, int n, const int32_t* fixed, int nfixed, const Bodies& b,
                           int32_t* slot_of_id, hipStream_t st);
+// Up to three arrays into pinned memory (in words of 8 bytes), then `seq` to
+// where the host watches for it.
+struct PostArgs {
+    const void* src[3];
+    void* dst[3];
+    uint32_t words[3];
+};
+void launch_post(const PostArgs& p, uint32_t* flag, uint32_t seq, hipStream_t st);
 void launch_gather_state(const StateArgs& a, const StateOut& o, hipStream_t st);
 void launch_scatter_state(const StateArgs& a, const StateIn& in, hipStream_t st);
 // boundary pairs that touched at the last step: flags (npairs + 1), then,

@@ -290,6 +290,7 @@ struct World {
     HBuf h_slots_c, h_slots_i;         // the per-block slots as read back
     Report* h_report = nullptr;        // pinned ring: the counters after each chain of steps
     uint32_t reports = 0;              // chains launched
+    uint32_t posts = 0;                // read-backs (their place is behind the ring)
     int32_t steps_seen = 0;            // steps_done of the last chain heard of
     bool resync = true;                // the device's counters are not known to match
     int64_t last_interval = 0;         // steps between the last two broad-phase runs
@@ -416,8 +417,8 @@ struct World {
                       "the chunk-start fields are contiguous");
         HIPC(hipHostMalloc(reinterpret_cast<void**>(&h_chunk), sizeof(ChunkStart), hipHostMallocDefault));
         std::memset(h_chunk, 0, sizeof(ChunkStart));
-        HIPC(hipHostMalloc(reinterpret_cast<void**>(&h_report), sizeof(Report) * kReports, hipHostMallocDefault));
-        std::memset(h_report, 0, sizeof(Report) * kReports);
+        HIPC(hipHostMalloc(reinterpret_cast<void**>(&h_report), sizeof(Report) * (kReports + 1), hipHostMallocDefault));
+        std::memset(h_report, 0, sizeof(Report) * (kReports + 1));
         d_ctrl_cfg.ensure(sizeof(CtrlConfig));
         d_ctrl_state.ensure(sizeof(CtrlState));
         HIPC(hipMemsetAsync(d_ctrl_cfg.p, 0, sizeof(CtrlConfig), stream));
@@ -904,8 +905,7 @@ struct World {
             d_bpart.ensure(bounds_temp_bytes());
             launch_bounds(bs[active].view(), nslots, nsc, d_bounds.as<double>(), d_bpart.p, stream);
             HIPC(hipGetLastError());
-            HIPC(hipMemcpyAsync(h_read.p, d_bounds.p, sizeof(double) * 6 * nsc, hipMemcpyDeviceToHost, stream));
-            HIPC(hipStreamSynchronize(stream));
+            fetch_and_wait({{d_bounds.p, h_read.p, sizeof(double) * 6 * nsc}});
             for (int s = 0; s < nsc; ++s)
                 if (scenes[s].n_spheres > 0)
                     for (int k = 0; k < 6; ++k)
@@ -1228,11 +1228,12 @@ struct World {
                 HIPC(hipGetLastError());
                 if (!guess) break;
                 // the slots' read-back (fold_slots) is waited for with the counts
-                fetch_slots();
+                h_slots_c.ensure(sizeof(ContactAcc) * (size_t)std::max(acc_c_n, 1));
+                h_slots_i.ensure(sizeof(IntAcc) * (size_t)std::max(acc_i_n, 1));
+                fetch_and_wait({{d_nent, h_n, 8},
+                                {d_part_c.p, h_slots_c.p, sizeof(ContactAcc) * (size_t)acc_c_n},
+                                {d_part_i.p, h_slots_i.p, sizeof(IntAcc) * (size_t)acc_i_n}});
                 slots_fetched = true;
-                HIPC(hipMemcpyAsync(h_n, d_nent, 8, hipMemcpyDeviceToHost, stream));
-                HIPC(hipStreamSynchronize(stream));
-                HIPC(hipGetLastError());
                 if ((int64_t)h_n[0] <= lim_ent && (int64_t)h_n[1] <= lim_pairs) break;
                 sized = true;  // run again from the fill, by the true counts
             }
@@ -1700,6 +1701,59 @@ struct World {
         return graphs.emplace(key, std::move(ge)).first->second;
     }
 
+    // Waits until the device has written `seq` to `word` (pinned), the last
+    // thing on the stream if `alone`.
+    void watch(const uint32_t& word, uint32_t seq, bool alone)
+    {
+        auto there = [&] { return __atomic_load_n(&word, __ATOMIC_ACQUIRE) == seq; };
+        const auto t0 = std::chrono::steady_clock::now();
+        int64_t looks = 0;
+        while (!there()) {
+            if (++looks % 256) continue;
+            const auto waited = std::chrono::steady_clock::now() - t0;
+            if (waited < std::chrono::milliseconds(2)) continue;
+            // a long wait: let the processor go, and find out about a device
+            // that has failed
+            if (alone) {
+                HIPC(hipStreamSynchronize(stream));
+                break;
+            }
+            const hipError_t e = hipStreamQuery(stream);
+            if (e == hipSuccess) break;
+            if (e != hipErrorNotReady) HIPC(e);
+            std::this_thread::sleep_for(std::chrono::microseconds(50));
+        }
+        if (!there()) fail(DEM_EDEVICE, "the device ended without its report");
+    }
+    // Reads back into pinned memory, in words of 8 bytes, and waits.
+    struct Fetch {
+        const void* src;
+        void* dst;
+        size_t bytes;
+    };
+    static constexpr size_t kPostBytes = 1 << 17;  // above, copies and a synchronisation are as fast
+    void fetch_and_wait(std::initializer_list<Fetch> what)
+    {
+        size_t all = 0;
+        for (const Fetch& f : what) all += f.bytes;
+        if (all > kPostBytes) {
+            for (const Fetch& f : what)
+                if (f.bytes) HIPC(hipMemcpyAsync(f.dst, f.src, f.bytes, hipMemcpyDeviceToHost, stream));
+            HIPC(hipStreamSynchronize(stream));
+            return;
+        }
+        PostArgs p{};
+        int q = 0;
+        for (const Fetch& f : what) {
+            p.src[q] = f.src;
+            p.dst[q] = f.dst;
+            p.words[q++] = (uint32_t)(f.bytes / 8);
+        }
+        launch_post(p, &h_report[kReports].seq, ++posts, stream);
+        HIPC(hipGetLastError());
+        watch(h_report[kReports].seq, posts, true);
+    }
+
     // One chain of steps on its way: its steps, and the parity after it.
     struct Chain {
         int n, parity;
@@ -1716,25 +1770,7 @@ struct World {
     void wait_report(const Chain& c, bool alone)
     {
         const Report& r = h_report[c.seq % kReports];
-        auto there = [&] { return __atomic_load_n(&r.seq, __ATOMIC_ACQUIRE) == c.seq; };
-        const auto t0 = std::chrono::steady_clock::now();
-        int64_t looks = 0;
-        while (!there()) {
-            if (++looks % 256) continue;
-            const auto waited = std::chrono::steady_clock::now() - t0;
-            if (waited < std::chrono::milliseconds(2)) continue;
-            // a long chain: let the processor go, and find out about a
-            // device that has failed
-            if (alone) {
-                HIPC(hipStreamSynchronize(stream));
-                break;
-            }
-            const hipError_t e = hipStreamQuery(stream);
-            if (e == hipSuccess) break;
-            if (e != hipErrorNotReady) HIPC(e);
-            std::this_thread::sleep_for(std::chrono::microseconds(50));
-        }
-        if (!there()) fail(DEM_EDEVICE, "a chain of steps ended without its report");
+        watch(r.seq, c.seq, alone);
         *h_ctr = r.c;
     }
 
