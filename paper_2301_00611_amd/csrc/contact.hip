@@ -132,10 +132,11 @@ __device__ inline PairRange xcd_pairs(int npairs)
 // hold no registers while they are in flight.  The new records go back the
 // same way.  The kernel, before -> now: 8 M spheres in shear (42 M candidates,
 // 16 M touching, FP64) 1.46 -> 1.11 ms, 500,000 under the controlled cell (4.5
-// M, 2.5 M) 182 -> 140 us, 1 M in shear FP32-mixed 208 -> 178 us; scenes with
-// few contacts within 0.2 us.  A grid of resident blocks that loop over tiles
-// took 1.53 ms at 8 M (the values kept across tiles spill), adding the counts
-// with atomics that return nothing 1.50.
+// M, 2.5 M) 182 -> 140 us, 1 M in shear FP32-mixed 208 -> 178 us (with what
+// came after 1.04 ms, 131 and 165 us); scenes with few contacts within 0.2 us.
+// A grid of resident blocks that loop over tiles took 1.53 ms at 8 M (the
+// values kept across tiles spill), adding the counts with atomics that return
+// nothing 1.50.
 using Lds = __attribute__((address_space(3))) char*;
 
 // bytes of LDS per wave: its records

@@ -156,11 +156,13 @@ __device__ inline void body_sum(const StepArgs& a, int beg, int end, double r, d
 //
 // Before (entries and records four at a time, no list) -> now, per launch:
 // 8 M spheres in shear 974 -> 906 us, 500,000 under the controlled cell 126 ->
-// 96 us, 1 M in shear FP32-mixed 142 -> 131 us, 32,000 dense equal spheres
-// 10.8 -> 9.9 us (in blocks of 64), 24 scenes of 8,000 10.6 -> 9.2 us; a bed
-// of 1,000 within 0.2 us.  Taking the wave's rows as one stream of 64 entries
-// per load, ranked by ballots, took 924 us at 8 M and 5 us more for the
-// 32,000; records brought straight into LDS 951 us.
+// 96 us, 1 M in shear FP32-mixed 142 -> 131 us (these three, with the direction
+// of the walk and what passes by the caches in large scenes: 875, 93 and 115
+// us), 32,000 dense equal spheres 10.8 -> 9.9 us in blocks of 64, 24 scenes of
+// 158,625 in all 10.6 -> 9.2 us; a bed of 1,000 within 0.2 us.  Taking the
+// wave's rows as one stream of 64 entries per load, ranked by ballots, took 924
+// us at 8 M and 5 us more for the 32,000; records brought straight into LDS 951
+// us.
 //
 // What is left of rows much longer than the rest (a large sphere among small
 // ones has ~10x their entries) is finished by the wave together, one row's

@@ -1689,7 +1689,7 @@ struct World {
         const std::string key = graph_key(n, phase);
         auto it = graphs.find(key);
         if (it != graphs.end()) return it->second;
-        if (graphs.size() > 16) invalidate_graphs();
+        if (graphs.size() > 32) invalidate_graphs();
         GraphEntry ge;
         hipGraph_t g;
         HIPC(hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal));
