@@ -547,7 +547,7 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
                 hnew = H{fs64.x, fs64.y, fs64.z, pen, (float)n.x, (float)n.y, (float)n.z, (float)fn_mag};
             else
                 hnew = H{fs64.x, fs64.y, fs64.z, pen, (double)n.x, (double)n.y, (double)n.z, (double)fn_mag};
-            // the force record (F, n x F); the FP64 linear law's integrate
+            // the force record (F, n x F); under the linear law the integrate
             // kernel reads the history instead
             frec = ForceRec<R>{F.x, F.y, F.z, tau.x, tau.y, tau.z};
             if (wall)
@@ -572,7 +572,7 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
             }
         }
         wave_store<uint4>(reinterpret_cast<H*>(a.pr.h) + range.first, touch | erase, hnew, lds);
-        if constexpr (PREC == DEM_FP32_MIXED)
+        if constexpr (VISCEL && PREC == DEM_FP32_MIXED)
             wave_store<uint2>(reinterpret_cast<ForceRec<R>*>(a.pr.frecf) + range.first, touch, frec, lds);
         else if (VISCEL)
             wave_store<uint4>(reinterpret_cast<ForceRec<R>*>(a.pr.frec) + range.first, touch, frec, lds);

@@ -15,6 +15,7 @@
 #include "dem_internal.hpp"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace dem {
 
@@ -43,25 +44,28 @@ __device__ inline int logical_block(int nb, int* slot)
 
 __device__ inline double sgn(double x) { return x > 0.0 ? 1.0 : (x < 0.0 ? -1.0 : 0.0); }
 
+// A history record as it is loaded: parts of 16 bytes.
+typedef uint32_t Part __attribute__((ext_vector_type(4)));
+template <int PREC>
+struct HistParts {
+    Part v[sizeof(typename HistOf<PREC>::T) / 16];
+};
+
 // One touching pair as a row entry sees it: the force on #2 and n x F, from
 // the pair's force record (FREC: F on #2, n x F) or from its history record
-// (FP64 linear law: F = fn n + Fs).  Without contraction, so that every
+// (linear law: F = fn n + Fs).  Without contraction, so that every
 // walk over a row (one thread, or the wave together) gives the same bits.
 template <int PREC, bool FREC>
 __device__ inline void pair_force(const StepArgs& a, uint32_t k, double* f)
 {
 #pragma clang fp contract(off)
-    if (!FREC) {
-        // the history record, one 64-byte segment read as two halves
-        const gptr<const double4> h = glb<const double4>(reinterpret_cast<const double4*>(a.pr.h)) + 2 * (size_t)k;
-        const double4 h0 = h[0], h1 = h[1];
-        const double fx = h1.w * h1.x + h0.x, fy = h1.w * h1.y + h0.y, fz = h1.w * h1.z + h0.z;
-        f[0] = fx;
-        f[1] = fy;
-        f[2] = fz;
-        f[3] = h1.y * fz - h1.z * fy;
-        f[4] = h1.z * fx - h1.x * fz;
-        f[5] = h1.x * fy - h1.y * fx;
+    if constexpr (!FREC) {
+        using H = typename HistOf<PREC>::T;
+        constexpr int kParts = sizeof(H) / 16;
+        const gptr<const Part> p = glb<const Part>(reinterpret_cast<const Part*>(a.pr.h)) + kParts * (size_t)k;
+        HistParts<PREC> h;
+        for (int c = 0; c < kParts; ++c) h.v[c] = p[c];
+        hist_force(__builtin_bit_cast(H, h), f);
     } else if (PREC == DEM_FP32_MIXED) {
         // a record is read as three pairs (it starts on an 8-byte boundary)
         const gptr<const float2> q = glb<const float2>(reinterpret_cast<const float2*>(a.pr.frecf)) + 3 * (size_t)k;
@@ -204,57 +208,53 @@ struct Record {
     }
 };
 
-typedef uint32_t Chunk __attribute__((ext_vector_type(4)));
 constexpr int quad_ctrl(int a, int b, int c, int d) { return a | (b << 2) | (c << 4) | (d << 6); }
 template <int CTRL>
-__device__ inline Chunk quad_perm(Chunk x)
+__device__ inline Part quad_perm(Part x)
 {
-    Chunk y;
+    Part y;
     for (int d = 0; d < 4; ++d) y[d] = (uint32_t)__builtin_amdgcn_mov_dpp((int)x[d], CTRL, 0xf, 0xf, true);
     return y;
 }
 // In: lane s of a quad holds part s of the quad's records 0..3; out: parts
 // 0..3 of record s.
-__device__ inline void quad_transpose(Chunk* v)
+__device__ inline void quad_transpose(Part* v)
 {
     const bool odd = threadIdx.x & 1, high = threadIdx.x & 2;
     for (int p = 0; p < 4; p += 2) {
-        const Chunk a = v[p], b = v[p + 1];
-        const Chunk xa = quad_perm<quad_ctrl(1, 0, 3, 2)>(a), xb = quad_perm<quad_ctrl(1, 0, 3, 2)>(b);
+        const Part a = v[p], b = v[p + 1];
+        const Part xa = quad_perm<quad_ctrl(1, 0, 3, 2)>(a), xb = quad_perm<quad_ctrl(1, 0, 3, 2)>(b);
         v[p] = odd ? xb : a;
         v[p + 1] = odd ? b : xa;
     }
     for (int p = 0; p < 2; ++p) {
-        const Chunk a = v[p], b = v[p + 2];
-        const Chunk xa = quad_perm<quad_ctrl(2, 3, 0, 1)>(a), xb = quad_perm<quad_ctrl(2, 3, 0, 1)>(b);
+        const Part a = v[p], b = v[p + 2];
+        const Part xa = quad_perm<quad_ctrl(2, 3, 0, 1)>(a), xb = quad_perm<quad_ctrl(2, 3, 0, 1)>(b);
         v[p] = high ? xb : a;
         v[p + 2] = high ? b : xa;
     }
 }
 template <int PREC>
 struct Record<PREC, false, true> {
-    Chunk v[4];
+    using H = typename HistOf<PREC>::T;
+    static constexpr int kParts = sizeof(H) / 16;
+    Part v[4];
     __device__ void fetch(const StepArgs& a, uint32_t k)
     {
-        const gptr<const char> part = glb(reinterpret_cast<const char*>(a.pr.h)) + (threadIdx.x & 3) * 16;
+        const gptr<const char> part =
+            glb(reinterpret_cast<const char*>(a.pr.h)) + min((int)(threadIdx.x & 3), kParts - 1) * 16;
         const uint32_t q[4] = {(uint32_t)__builtin_amdgcn_mov_dpp((int)k, quad_ctrl(0, 0, 0, 0), 0xf, 0xf, true),
                                (uint32_t)__builtin_amdgcn_mov_dpp((int)k, quad_ctrl(1, 1, 1, 1), 0xf, 0xf, true),
                                (uint32_t)__builtin_amdgcn_mov_dpp((int)k, quad_ctrl(2, 2, 2, 2), 0xf, 0xf, true),
                                (uint32_t)__builtin_amdgcn_mov_dpp((int)k, quad_ctrl(3, 3, 3, 3), 0xf, 0xf, true)};
-        for (int i = 0; i < 4; ++i) v[i] = *(gptr<const Chunk>)(part + (size_t)q[i] * sizeof(HistRec));
+        for (int i = 0; i < 4; ++i) v[i] = *(gptr<const Part>)(part + (size_t)q[i] * sizeof(H));
     }
     __device__ void force(double* f)
     {
-#pragma clang fp contract(off)
         quad_transpose(v);
-        const HistRec h = __builtin_bit_cast(HistRec, v);
-        const double fx = h.fn * h.nx + h.fsx, fy = h.fn * h.ny + h.fsy, fz = h.fn * h.nz + h.fsz;
-        f[0] = fx;
-        f[1] = fy;
-        f[2] = fz;
-        f[3] = h.ny * fz - h.nz * fy;
-        f[4] = h.nz * fx - h.nx * fz;
-        f[5] = h.nx * fy - h.ny * fx;
+        HistParts<PREC> h;
+        for (int c = 0; c < kParts; ++c) h.v[c] = v[c];
+        hist_force(__builtin_bit_cast(H, h), f);
     }
 };
 
@@ -891,18 +891,27 @@ void launch_sized(const StepArgs* args, int parity, int grid, bool batched, bool
     else launch_kind<PREC, FREC, false>(args, parity, grid, batched, periodic, block, st, ev0, ev1);
 }
 
+// f(precision, force records) with both as types
+template <typename F>
+void by_records(int precision, bool frec, F&& f)
+{
+    using Fp32 = std::integral_constant<int, DEM_FP32_MIXED>;
+    using Fp64 = std::integral_constant<int, DEM_FP64>;
+    if (precision == DEM_FP32_MIXED)
+        frec ? f(Fp32{}, std::true_type{}) : f(Fp32{}, std::false_type{});
+    else
+        frec ? f(Fp64{}, std::true_type{}) : f(Fp64{}, std::false_type{});
+}
+
 }  // namespace
 
 void launch_integrate(const StepArgs* args, int parity, int grid, int precision, bool batched, bool periodic,
                       bool frec, bool large, int block, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1)
 {
-    // FP32-mixed always has its force records
-    if (precision == DEM_FP32_MIXED)
-        launch_sized<DEM_FP32_MIXED, true>(args, parity, grid, batched, periodic, large, block, st, ev0, ev1);
-    else if (frec)
-        launch_sized<DEM_FP64, true>(args, parity, grid, batched, periodic, large, block, st, ev0, ev1);
-    else
-        launch_sized<DEM_FP64, false>(args, parity, grid, batched, periodic, large, block, st, ev0, ev1);
+    by_records(precision, frec, [&](auto prec, auto rec) {
+        launch_sized<decltype(prec)::value, decltype(rec)::value>(args, parity, grid, batched, periodic, large, block,
+                                                                  st, ev0, ev1);
+    });
 }
 
 // Largest Verlet account (non-affine displacement since the last broad-phase
@@ -980,28 +989,23 @@ void launch_body_measures(const StepArgs& a, int precision, bool batched, int sc
     const int grid = body_blocks(a.nslots);
     if (grid == 0) return;
     const dim3 g(grid), b(kMeasureBlock);
-    if (precision == DEM_FP32_MIXED) {
-        if (batched) hipLaunchKernelGGL((k_body_measures<DEM_FP32_MIXED, true, true>), g, b, 0, st, a, scene, part);
-        else hipLaunchKernelGGL((k_body_measures<DEM_FP32_MIXED, false, true>), g, b, 0, st, a, scene, part);
-    } else if (a.use_frec) {
-        if (batched) hipLaunchKernelGGL((k_body_measures<DEM_FP64, true, true>), g, b, 0, st, a, scene, part);
-        else hipLaunchKernelGGL((k_body_measures<DEM_FP64, false, true>), g, b, 0, st, a, scene, part);
-    } else {
-        if (batched) hipLaunchKernelGGL((k_body_measures<DEM_FP64, true, false>), g, b, 0, st, a, scene, part);
-        else hipLaunchKernelGGL((k_body_measures<DEM_FP64, false, false>), g, b, 0, st, a, scene, part);
-    }
+    auto launch = [&](auto prec, auto frec) {
+        constexpr int P = decltype(prec)::value;
+        constexpr bool F = decltype(frec)::value;
+        if (batched) hipLaunchKernelGGL((k_body_measures<P, true, F>), g, b, 0, st, a, scene, part);
+        else hipLaunchKernelGGL((k_body_measures<P, false, F>), g, b, 0, st, a, scene, part);
+    };
+    by_records(precision, a.use_frec != 0, launch);
 }
 
 void launch_body_forces(const StepArgs& a, int precision, double* f3, double* t3, hipStream_t st)
 {
     if (a.nslots <= 0) return;
     const int grid = (a.nslots + 255) / 256;
-    if (precision == DEM_FP32_MIXED)
-        hipLaunchKernelGGL((k_body_forces<DEM_FP32_MIXED, true>), dim3(grid), dim3(256), 0, st, a, f3, t3);
-    else if (a.use_frec)
-        hipLaunchKernelGGL((k_body_forces<DEM_FP64, true>), dim3(grid), dim3(256), 0, st, a, f3, t3);
-    else
-        hipLaunchKernelGGL((k_body_forces<DEM_FP64, false>), dim3(grid), dim3(256), 0, st, a, f3, t3);
+    by_records(precision, a.use_frec != 0, [&](auto prec, auto frec) {
+        hipLaunchKernelGGL((k_body_forces<decltype(prec)::value, decltype(frec)::value>), dim3(grid), dim3(256), 0, st,
+                           a, f3, t3);
+    });
 }
 
 }  // namespace dem

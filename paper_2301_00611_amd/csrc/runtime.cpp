@@ -1649,7 +1649,7 @@ struct World {
         a.acc_ctrl2 = d_acc_ctrl2.as<double>();
         a.nblocks_contact = grid_c;
         a.nblocks_integrate = grid_i;
-        a.use_frec = uses_force_records(precision, has_viscel()) ? 1 : 0;
+        a.use_frec = uses_force_records(has_viscel()) ? 1 : 0;
         a.pad_ = 0;
         return a;
     }
@@ -1664,7 +1664,7 @@ struct World {
         const bool large = nslots > kLargeBodies;
         launch_contact(a, parity, grid_c, precision, batched(), periodic, large, block_c, stream, ev ? ev[0] : nullptr,
                        ev ? ev[1] : nullptr, periodic && pt_active && measure, has_prims(), has_viscel());
-        launch_integrate(a, parity, grid_i, precision, batched(), periodic, uses_force_records(precision, has_viscel()),
+        launch_integrate(a, parity, grid_i, precision, batched(), periodic, uses_force_records(has_viscel()),
                          large, block_i, stream, ev ? ev[2] : nullptr, ev ? ev[3] : nullptr);
         if (periodic && pt_active && measure) launch_ctrl_reduce(a, parity, stream);
         if (periodic) launch_cell_update(a, parity, stream);

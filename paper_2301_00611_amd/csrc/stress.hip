@@ -29,7 +29,7 @@ namespace {
 constexpr int kStressBlock = 256;
 
 // Force on #2 of pair k (0 unless the pair touched at the last step): from
-// its force record, or (FP64 linear law) its history record, fn n + Fs
+// its force record, or (linear law) its history record, fn n + Fs
 // (without contraction, as the force sum forms it).
 template <int PREC>
 __device__ inline void pair_force(const StepArgs& a, int k, double* F)
@@ -38,10 +38,9 @@ __device__ inline void pair_force(const StepArgs& a, int k, double* F)
     F[0] = F[1] = F[2] = 0.0;
     if (!a.pr.real[k]) return;
     if (!a.use_frec) {
-        const HistRec h = hist_load<PREC>(a.pr.h, k);
-        F[0] = h.fn * h.nx + h.fsx;
-        F[1] = h.fn * h.ny + h.fsy;
-        F[2] = h.fn * h.nz + h.fsz;
+        double f[kForceWords];
+        hist_force(reinterpret_cast<const typename HistOf<PREC>::T*>(a.pr.h)[k], f);
+        for (int q = 0; q < 3; ++q) F[q] = f[q];
     } else if (PREC == DEM_FP32_MIXED) {
         const float* q = a.pr.frecf + (size_t)kForceWords * k;
         F[0] = q[0];
