@@ -271,7 +271,9 @@ dem_status dem_get_energy(dem_scene* s, dem_energy* out);
  * l the branch vector from #2 to #1 (negative under compression).  Wall
  * contacts are left out.  volume <= 0 takes the periodic cell's volume
  * (DEM_EINVAL for an aperiodic scene).  sigma9 is a host buffer of 9
- * doubles, row-major. */
+ * doubles, row-major.  When bodies were added since the last step, this call,
+ * dem_get_unbalanced_force and dem_stiffness_dt first run the broad phase
+ * that dem_step would run; it keeps the last step's contacts. */
 dem_status dem_get_stress(dem_scene* s, double volume, double* sigma9);
 /* dem_get_stress for callers that cannot allocate (code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation): the same
@@ -283,7 +285,7 @@ dem_status dem_get_stress(dem_scene* s, double volume, double* sigma9);
  * (relative 1e-12), not bit for bit; each is deterministic.  Limits: at most
  * 67,108,864 candidate pairs (DEM_EINVAL beyond); the device state must be
  * current (DEM_EINVAL when bodies were added or the state set since the last
- * step, which dem_get_stress would upload).  Calls that overlap on one GPU
+ * step).  Calls that overlap on one GPU
  * (other threads, other scenes) share the array and race. */
 dem_status dem_get_stress_noalloc(dem_scene* s, double volume, double* sigma9);
 dem_status dem_get_stats(dem_scene* s, dem_stats* out);

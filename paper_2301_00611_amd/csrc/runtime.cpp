@@ -255,6 +255,9 @@ struct World {
     // the state was set on the device since the last broad-phase run: what
     // the last step's contacts gave (forces, contact list) no longer applies
     bool state_set = false;
+    // the bodies' slots changed since the pair list was built (bodies were
+    // uploaded): the list and its rows mean nothing until the next run
+    bool pairs_stale = false;
     bool need_rebuild = true;
     bool contacts_valid = false;
 
@@ -795,6 +798,7 @@ struct World {
         ngids_dev = ng;
         host_dirty = false;
         state_set = false;
+        pairs_stale = true;
         on_device = true;
         need_rebuild = true;
         last_ent = last_pairs = -1;
@@ -832,6 +836,15 @@ struct World {
         d_args.ensure(sizeof(StepArgs));
         HIPC(hipMemcpyAsync(d_args.p, &a, sizeof(StepArgs), hipMemcpyHostToDevice, stream));
         HIPC(hipStreamSynchronize(stream));
+    }
+
+    // Before a report that follows the pair list to the bodies: both current.
+    // A pending broad-phase run keeps the touching pairs and their history, so
+    // the report is still the last step's.
+    void current_pairs()
+    {
+        if (host_dirty) upload_bodies();
+        if (pairs_stale && contacts_valid) rebuild();
     }
 
     // ------------------------------------------------------- broad phase
@@ -1304,6 +1317,7 @@ struct World {
         HIPC(hipGetLastError());
         need_rebuild = false;
         state_set = false;
+        pairs_stale = false;
         ++rebuilds;
         if (scenes[0].iter > iter_at_rebuild) last_interval = scenes[0].iter - iter_at_rebuild;
         iter_at_rebuild = scenes[0].iter;
@@ -1407,7 +1421,7 @@ struct World {
     // last step (0 before the first step), from their history records.
     double max_overlap()
     {
-        if (npairs <= 0 || !contacts_valid) return 0.0;
+        if (npairs <= 0 || !contacts_valid || pairs_stale) return 0.0;
         d_acct.ensure(8);
         HIPC(hipMemsetAsync(d_acct.p, 0, 8, stream));
         StepArgs a = step_args();
@@ -2129,7 +2143,7 @@ struct World {
         }
         // the device puts a range of bodies in id order, at most
         // kStateChunk at a time through one scratch buffer
-        const bool forces = (force3 || torque3) && nslots > 0 && contacts_valid && !state_set;
+        const bool forces = (force3 || torque3) && nslots > 0 && contacts_valid && !state_set && !pairs_stale;
         std::vector<double> wallF;
         StateArgs g = state_args(s, first);
         if (forces) {
@@ -2379,7 +2393,7 @@ struct World {
     Measures measures(int s)
     {
         Measures m;
-        if (host_dirty) upload_bodies();
+        current_pairs();
         if (!contacts_valid || nslots == 0) return m;
         const int np = npairs > 0 ? stress_blocks(npairs) : 0;
         const int nb = body_blocks(nslots);
@@ -2550,7 +2564,7 @@ struct World {
         }
         if (!std::isfinite(V) || !(V > 0.0)) fail(DEM_EINVAL, "dem_get_stress: volume must be > 0");
         double sum[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-        if (host_dirty) upload_bodies();
+        current_pairs();
         const int nb = (contacts_valid && npairs > 0) ? stress_blocks(npairs) : 0;
         if (nb > 0) {
             d_tmp3.ensure(sizeof(double) * kNetworkWords * (size_t)nb);
@@ -2571,7 +2585,7 @@ struct World {
     // or a state set since the last step are refused rather than uploaded).
     void stress_noalloc(int s, double volume, double* out9)
     {
-        if (host_dirty || state_set)
+        if (host_dirty || state_set || pairs_stale)
             fail(DEM_EINVAL, "dem_get_stress_noalloc: bodies or state changed since the last step; step first");
         double V = volume;
         if (!(V > 0.0)) {
@@ -2600,7 +2614,7 @@ struct World {
     std::vector<dem_contact> contacts(int s)
     {
         std::vector<dem_contact> out;
-        if (!contacts_valid || host_dirty || state_set || npairs == 0) return out;
+        if (!contacts_valid || host_dirty || state_set || pairs_stale || npairs == 0) return out;
         Snapshot sn = snapshot();
         PairSnapshot p = pair_snapshot();
         const std::vector<int64_t> loc = local_ids();
@@ -2690,7 +2704,7 @@ struct World {
     void set_history(int s, int64_t n, const dem_history* in)
     {
         if (n < 0 || (n > 0 && !in)) fail(DEM_EINVAL, "dem_set_history: bad arguments");
-        if (host_dirty) upload_bodies();
+        current_pairs();
         const HostScene& S = scenes[s];
         struct Rec {
             int32_t owner, partner, cell;
