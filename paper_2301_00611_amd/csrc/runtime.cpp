@@ -256,7 +256,8 @@ struct World {
     // the last step's contacts gave (forces, contact list) no longer applies
     bool state_set = false;
     // the bodies' slots changed since the pair list was built (bodies were
-    // uploaded): the list and its rows mean nothing until the next run
+    // uploaded, or a broad-phase run failed half way): the list and its rows
+    // mean nothing until the next run
     bool pairs_stale = false;
     bool need_rebuild = true;
     bool contacts_valid = false;
@@ -1138,6 +1139,7 @@ struct World {
             PairSet& OP = ps[pactive];
             NP.own_begin.ensure(4 * (size_t)std::max(ng, 1));
             NP.own_count.ensure(4 * (size_t)std::max(ng, 1));
+            pairs_stale = need_rebuild = true;  // until this run ends
             launch_cell_place(g, cs, bs[1 - active].view(), periodic, slot_of_id.as<int32_t>(),
                               NP.own_begin.as<int32_t>(), NP.own_count.as<int32_t>(), scan_tmp.p, stream);
             active = 1 - active;
