@@ -284,9 +284,9 @@ struct Pairs {
 };
 constexpr int kForceWords = 6;
 
-// Where the integrate kernel and the reports take a pair's force from: the
-// history record itself (linear law), or a force record (visco-elastic law: its
-// shear dashpot is not in the history).  FP32-mixed had force records under
+// Where the integrate kernel takes a pair's force from: the history record
+// itself (linear law), or a force record (visco-elastic law: its shear dashpot
+// is not in the history).  Reports take it from where the last step put it.  FP32-mixed had force records under
 // both laws: 24 bytes are less to gather than the 48 of the history, but they
 // are written beside it every step.  us per step with them / without: 1 M
 // spheres in shear 282 / 257 (contact 162 / 134, integrate 117 / 117), 780,000
@@ -455,7 +455,7 @@ struct StepArgs {
     double* acc_ctrl2;              // kCtrlReduceGrid x (kNetworkWords + 2)
     int32_t nblocks_contact;        // blocks of the contact kernel (its grid)
     int32_t nblocks_integrate;      // slots of acc_integrate written by the integrate kernel
-    int32_t use_frec;               // forces come from the force records (uses_force_records), else the history
+    int32_t use_frec;               // reports: the last step's forces are in the force records, else in the history
     int32_t pad_;
 };
 

@@ -261,6 +261,7 @@ struct World {
     bool pairs_stale = false;
     bool need_rebuild = true;
     bool contacts_valid = false;
+    bool frec_current = false;         // the last step's forces are in the force records (it ran the visco-elastic kernels)
 
     // device
     BodySet bs[2];
@@ -1665,7 +1666,7 @@ struct World {
         a.acc_ctrl2 = d_acc_ctrl2.as<double>();
         a.nblocks_contact = grid_c;
         a.nblocks_integrate = grid_i;
-        a.use_frec = uses_force_records(has_viscel()) ? 1 : 0;
+        a.use_frec = frec_current ? 1 : 0;
         a.pad_ = 0;
         return a;
     }
@@ -1956,7 +1957,10 @@ struct World {
                     if (timing) HIPC(hipStreamSynchronize(stream));  // for the events
                     const int done = h_ctr->steps_done - steps_seen;
                     steps_seen = h_ctr->steps_done;
-                    if (done > 0) slots_fresh = false;
+                    if (done > 0) {
+                        slots_fresh = false;
+                        frec_current = uses_force_records(has_viscel());
+                    }
                     if (timing)
                         for (int i = 0; i < done; ++i) {
                             add_time("contact", direct_ev[4 * (size_t)i], direct_ev[4 * (size_t)i + 1]);
@@ -2823,6 +2827,7 @@ struct World {
         old_ngids = ng;
         npairs = 0;  // the active set now only holds history: nothing to report until the next step
         contacts_valid = false;
+        frec_current = false;
         need_rebuild = true;
         invalidate_graphs();
     }
