@@ -871,6 +871,14 @@ __global__ void __launch_bounds__(kBlock) k_partition(PairBuildArgs a)
             f >= 0 ? reinterpret_cast<const HistRec32*>(a.hist_old.h)[f] : HistRec32{};
     else
         a.pr.h[pos] = f >= 0 ? a.hist_old.h[f] : HistRec{};
+    // the force of a pair that touched, for reports before the next step
+    if (a.carry_frec && f >= 0) {
+        for (int q = 0; q < kForceWords; ++q)
+            if (a.hist_f32)
+                a.pr.frecf[kForceWords * (size_t)pos + q] = static_cast<const float*>(a.hist_old.frec)[kForceWords * (size_t)f + q];
+            else
+                a.pr.frec[kForceWords * (size_t)pos + q] = static_cast<const double*>(a.hist_old.frec)[kForceWords * (size_t)f + q];
+    }
     a.pr.real[pos] = touched ? 1 : 0;
     a.pr.ea[pos] = -1;  // set below from the rows (stays -1 for a boundary pair)
     a.pr.eb[pos] = -1;

@@ -335,6 +335,7 @@ struct History {
     int32_t *cell;            // canonical: image
     int32_t *map;             // canonical -> index of the pair in the partitioned arrays
     const HistRec *h;         // partitioned order
+    const void *frec;         // partitioned order (Pairs::frec or frecf)
 };
 
 // Device-side flags and counters (one struct in device memory).  The hot
@@ -585,6 +586,7 @@ struct PairBuildArgs {
     int32_t lim_pairs;
     int32_t has_old;
     int32_t hist_f32;          // history records are HistRec32 (FP32-mixed)
+    int32_t carry_frec;        // the previous list's force records hold the last step: kept for the reports
 };
 // canonical pair arrays and rows (pair_build), history lookup (carry_find),
 // then, after the host scans `flag`, the partition into the final arrays

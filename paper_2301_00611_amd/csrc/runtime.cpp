@@ -189,6 +189,7 @@ struct PairSet {
         h.cell = hcell.as<int32_t>();
         h.map = hmap.as<int32_t>();
         h.h = hist.as<HistRec>();
+        h.frec = frec.p;
         return h;
     }
     void release()
@@ -1235,6 +1236,7 @@ struct World {
                 pb.lim_pairs = (int32_t)lim_pairs;
                 pb.has_old = (OP.cap > 0 && OP.own_begin.p && old_ngids > 0) ? 1 : 0;
                 pb.hist_f32 = f32 ? 1 : 0;
+                pb.carry_frec = frec_current ? 1 : 0;
                 launch_pair_build(pb, stream);
                 launch_carry_find(pb, stream, std::min(old_ngids, ng));
                 // touching pairs first: ranks from a scan of the carried flags

@@ -1,6 +1,7 @@
 """Reports of the last step's forces whichever record they are read from: the
 history (linear law) or the force records (visco-elastic law), when a material
-of the other law is added between steps."""
+of the other law is added between steps and when a broad-phase run renews the
+pair list."""
 import numpy as np
 import pytest
 
@@ -66,4 +67,27 @@ def test_material_of_the_other_law_added_between_steps(precision):
     _same(before, _reports(s))
     s.step(3)
     _consistent(s, precision)
+    after = _reports(s)
+    s.set_tuning(chunk=32)
+    s.step(0)
+    _same(after, _reports(s))
+    s.close()
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_viscoelastic_forces_through_a_run(precision):
+    s = _scene(1, precision)
+    s.step(60)
+    _consistent(s, precision)
+    before = _reports(s)
+    runs = s.stats()["rebuilds"]
+    s.set_tuning(chunk=32)
+    s.step(0)
+    assert s.stats()["rebuilds"] == runs + 1
+    _same(before, _reports(s))
+    s.add_spheres([[0.1, 0.1, 0.1]], [1e-3], default_mat=0)
+    stress = s.get_stress(VOLUME)
+    f = np.linalg.norm(before["contacts"]["fn"] + before["contacts"]["fs"], axis=1).sum()
+    assert np.abs(stress - before["stress"]).max() <= 1e-12 * f * 3e-3 / VOLUME
+    assert np.array_equal(s.get_state()["force"][3:-1], before["force"])
     s.close()
