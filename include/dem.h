@@ -222,6 +222,9 @@ dem_status dem_set_velgrad(dem_scene* s, const double* velgrad9);
 dem_status dem_get_cell(dem_scene* s, double* hsize9, double* trsf9);
 
 /* Advance nsteps steps (O.run(n, wait=True)); returns when they are done.
+ * A step that fails (DEM_ENONFINITE, DEM_EUNSTABLE) ends the call, at the
+ * latest dem_tuning.chunk - 1 steps after it; dem_get_stats gives the steps
+ * done.
  * nsteps = 0 advances nothing but runs a pending broad phase (after bodies
  * were added or moved, or when the last step asked for one), so that the
  * next step starts from an up-to-date candidate list. */

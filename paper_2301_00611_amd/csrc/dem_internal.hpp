@@ -617,8 +617,9 @@ void launch_integrate(const StepArgs* args, int parity, int grid, int precision,
 // controlled cell is on and the step is one of its updates) the
 // controller, from the contact and integrate kernels' partial sums.
 void launch_cell_update(const StepArgs* args, int parity, hipStream_t st);
-// After a chain of steps: the counters into the host's ring.
-void launch_report(const StepArgs* args, Report* ring, hipStream_t st);
+// After a chain of steps, the last of parity `last`: the counters into the
+// host's ring; a failure stops the chain behind this one.
+void launch_report(const StepArgs* args, Report* ring, int last, hipStream_t st);
 // After a broad-phase run: the step descriptor and the counters are written,
 // the per-block slots of both step kernels cleared (a kernel's arguments carry
 // the values, so nothing is copied from host memory).

@@ -942,7 +942,11 @@ __global__ void __launch_bounds__(256) k_publish(StepArgs a, Counters c, StepArg
 }
 
 // One wave: the counters' words, then the number that the host waits for.
-__global__ void __launch_bounds__(64) k_report(const StepArgs* __restrict__ args, Report* __restrict__ ring)
+// After a failed step (non-finite or unstable) the chain behind finds the
+// stall flag raised and does nothing, so that the state the host hears of is
+// no more than this chain past the failure; the report has the flag as the
+// steps left it, and the host puts it back (run_steps).
+__global__ void __launch_bounds__(64) k_report(const StepArgs* __restrict__ args, Report* __restrict__ ring, int last)
 {
     Counters* const ctr = args->ctr;
     const uint32_t seq = ctr->reports + 1u;
@@ -954,13 +958,14 @@ __global__ void __launch_bounds__(64) k_report(const StepArgs* __restrict__ args
     __builtin_amdgcn_wave_barrier();
     if (threadIdx.x == 0) {
         ctr->reports = seq;
+        if (ctr->nonfinite || ctr->unstable) ctr->stall[last] = 1;
         __hip_atomic_store(&r.seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
-void launch_report(const StepArgs* args, Report* ring, hipStream_t st)
+void launch_report(const StepArgs* args, Report* ring, int last, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_report, dim3(1), dim3(64), 0, st, args, ring);
+    hipLaunchKernelGGL(k_report, dim3(1), dim3(64), 0, st, args, ring, last);
 }
 
 void launch_publish(const StepArgs& a, const Counters& c, StepArgs* dst, int nslots_contact, int nslots_integrate,

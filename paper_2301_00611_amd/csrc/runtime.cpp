@@ -1713,7 +1713,7 @@ struct World {
         hipGraph_t g;
         HIPC(hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal));
         for (int i = 0; i < n; ++i) launch_step(i & 1, nullptr, measure_step(phase, i));
-        launch_report(d_args.as<StepArgs>(), h_report, stream);
+        launch_report(d_args.as<StepArgs>(), h_report, (n - 1) & 1, stream);
         HIPC(hipStreamEndCapture(stream, &g));
         HIPC(hipGraphInstantiate(&ge.exec, g, nullptr, nullptr, 0));
         HIPC(hipGraphDestroy(g));
@@ -1941,7 +1941,7 @@ struct World {
                         for (int i = 0; i < n; ++i)
                             launch_step((par0 + i) & 1, timing ? &direct_ev[4 * (size_t)i] : nullptr,
                                         measure_step(phase, i));
-                        launch_report(d_args.as<StepArgs>(), h_report, stream);
+                        launch_report(d_args.as<StepArgs>(), h_report, (par0 + n - 1) & 1, stream);
                     }
                     HIPC(hipGetLastError());
                     next_parity = (par0 + n) & 1;
@@ -1950,7 +1950,7 @@ struct World {
                 }
                 // hear of the oldest chain, and of one behind it that a
                 // request or a failure has stopped
-                bool stalled = false, short_of = false;
+                bool stalled = false, short_of = false, asked = false;
                 int failed = 0;
                 do {
                     const Chain c = chains.front();
@@ -1975,11 +1975,19 @@ struct World {
                     remaining -= done;
                     ahead -= c.n;
                     contacts_valid = done > 0 || contacts_valid;
+                    stalled = h_ctr->stall[c.parity ^ 1] != 0;
+                    if (!failed) asked = stalled;
                     if (h_ctr->nonfinite) failed = DEM_ENONFINITE;
                     else if (h_ctr->unstable) failed = DEM_EUNSTABLE;
-                    stalled = h_ctr->stall[c.parity ^ 1] != 0;
                     short_of = short_of || (done < c.n && !stalled);
                 } while (!chains.empty() && (stalled || failed || h_ctr->halt));
+                if (failed && !asked) {
+                    // the flag that kept the chain behind from running
+                    h_ctr->stall[0] = h_ctr->stall[1] = 0;
+                    HIPC(hipMemcpyAsync(reinterpret_cast<char*>(d_ctr.p) + offsetof(Counters, stall), h_ctr->stall,
+                                        sizeof h_ctr->stall, hipMemcpyHostToDevice, stream));
+                    HIPC(hipStreamSynchronize(stream));
+                }
                 if (failed == DEM_ENONFINITE) fail(DEM_ENONFINITE, "non-finite position or velocity after a step");
                 if (failed) fail(DEM_EUNSTABLE, "an overlap exceeded a sphere radius (numerically exploding)");
                 if (short_of) fail(DEM_EDEVICE, "steps stopped without a broad-phase request");
