@@ -269,6 +269,50 @@ __global__ void __launch_bounds__(kBlock) k_cell_count(GridArgs g, CellSortArgs 
     }
 }
 
+// How crowded it is around a scene's bodies, for the choice of its grid
+// levels: the number of bodies in each body's cube of cells (consecutive in
+// their brick, so two reads of the scan), summed.  A block adds its sum once
+// where there is one scene; a batch's waves add theirs to their scene's word.
+constexpr int kCrowdBlocks = 512;
+template <bool BATCHED>
+__global__ void __launch_bounds__(kBlock) k_crowd(GridArgs g, CellSortArgs c, unsigned long long* __restrict__ out)
+{
+    unsigned long long sum = 0ull;
+    for (int i0 = blockIdx.x * blockDim.x; i0 < g.nslots; i0 += gridDim.x * blockDim.x) {
+        const int i = i0 + threadIdx.x;
+        const bool valid = i < g.nslots;
+        const int s = BATCHED && valid ? (int)g.bod.scene[i] : 0;
+        unsigned long long n = 0ull;
+        if (valid) {
+            const SceneParams& P = BATCHED ? g.scenes[s] : g.scene0;
+            const int m = 3 * P.crowd_bits;
+            const uint32_t off = (uint32_t)P.cell_offset;
+            const uint32_t cube = off + (((c.cell[i] - off) >> m) << m);
+            n = c.start[cube + (1u << m)] - c.start[cube];
+        }
+        if (!BATCHED) {
+            sum += n;
+            continue;
+        }
+        const int s0 = __shfl(s, 0, 64);
+        if (__all(!valid || s == s0)) {
+            for (int w = 32; w > 0; w >>= 1) n += __shfl_down(n, w, 64);
+            if ((threadIdx.x & 63) == 0 && valid) atomicAdd(&out[s], n);
+        } else if (valid) {
+            atomicAdd(&out[s], n);
+        }
+    }
+    if (BATCHED) return;
+    for (int w = 32; w > 0; w >>= 1) sum += __shfl_down(sum, w, 64);
+    __shared__ unsigned long long sh[kBlock / 64];
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kBlock / 64; ++w) sum += sh[w];
+        atomicAdd(out, sum);
+    }
+}
+
 __global__ void __launch_bounds__(kBlock) k_cell_bucket(GridArgs g, CellSortArgs c)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -929,7 +973,7 @@ void launch_bounds(const Bodies& b, int nslots, int nscenes, double* out6, void*
     hipLaunchKernelGGL(k_bounds_decode, dim3(nblocks(6 * nscenes)), dim3(kBlock), 0, st, bits, out6, 6 * nscenes);
 }
 
-void launch_cell_count(const GridArgs& g, const CellSortArgs& c, bool periodic, hipStream_t st)
+void launch_cell_count(const GridArgs& g, const CellSortArgs& c, bool periodic, void* scan_temp, hipStream_t st)
 {
     if (g.nslots <= 0) return;
     const bool batched = g.nscenes > 1;
@@ -941,15 +985,25 @@ void launch_cell_count(const GridArgs& g, const CellSortArgs& c, bool periodic, 
         hipLaunchKernelGGL((k_cell_count<false, true>), grid, blk, 0, st, g, c);
     else
         hipLaunchKernelGGL((k_cell_count<false, false>), grid, blk, 0, st, g, c);
+    exclusive_scan_u32(c.count, c.start, c.ncells, nullptr, scan_temp, nullptr, st);
+}
+
+void launch_crowd(const GridArgs& g, const CellSortArgs& c, unsigned long long* crowd, hipStream_t st)
+{
+    if (g.nslots <= 0) return;
+    const int nblk = nblocks(g.nslots);
+    if (g.nscenes > 1)
+        hipLaunchKernelGGL((k_crowd<true>), dim3(nblk), dim3(kBlock), 0, st, g, c, crowd);
+    else
+        hipLaunchKernelGGL((k_crowd<false>), dim3(std::min(nblk, kCrowdBlocks)), dim3(kBlock), 0, st, g, c, crowd);
 }
 
 void launch_cell_place(const GridArgs& g, const CellSortArgs& c, const Bodies& dst, bool periodic, int32_t* slot_of_id,
-                       int32_t* own_begin, int32_t* own_count, void* scan_temp, hipStream_t st)
+                       int32_t* own_begin, int32_t* own_count, hipStream_t st)
 {
     if (g.nslots <= 0) return;
     const bool batched = g.nscenes > 1;
     const dim3 grid(nblocks(g.nslots)), blk(kBlock);
-    exclusive_scan_u32(c.count, c.start, c.ncells, nullptr, scan_temp, nullptr, st);
     hipLaunchKernelGGL(k_cell_bucket, grid, blk, 0, st, g, c);
     if (batched)
         hipLaunchKernelGGL((k_permute<true>), grid, blk, 0, st, g, c, dst, 0, slot_of_id, own_begin, own_count);

@@ -42,7 +42,7 @@ struct SceneParams {
     int32_t cell_offset;      // first cell of this scene in the cell table
     // periodic cell
     int32_t periodic;
-    int32_t pad_;
+    int32_t crowd_bits;       // level-0 cells a side, as a power of two, of the cubes the bodies are counted in (k_crowd)
     double H[9];              // current cell
     double Hinv[9];
     double dH[9];             // H - H_prev: the image shift moved by dH c over the last step
@@ -529,12 +529,15 @@ struct CellSortArgs {
     int32_t ncells;
     int32_t nlarge;
 };
-// the cells' counts (and, periodic, the bodies' periods and their check),
-// then scan, bucket and permute g.bod into dst; own_begin / own_count (the
-// next pair list's ranges, by id) are cleared
-void launch_cell_count(const GridArgs& g, const CellSortArgs& c, bool periodic, hipStream_t st);
+// the cells' counts (and, periodic, the bodies' periods and their check) and
+// their scan; how crowded the bodies are (with `crowd`, one word per scene,
+// zero before: over its bodies, the number in the body's cube of 2^crowd_bits
+// cells a side); then bucket and permute g.bod into dst; own_begin / own_count
+// (the next pair list's ranges, by id) are cleared
+void launch_cell_count(const GridArgs& g, const CellSortArgs& c, bool periodic, void* scan_temp, hipStream_t st);
+void launch_crowd(const GridArgs& g, const CellSortArgs& c, unsigned long long* crowd, hipStream_t st);
 void launch_cell_place(const GridArgs& g, const CellSortArgs& c, const Bodies& dst, bool periodic, int32_t* slot_of_id,
-                       int32_t* own_begin, int32_t* own_count, void* scan_temp, hipStream_t st);
+                       int32_t* own_begin, int32_t* own_count, hipStream_t st);
 struct SweepArgs {
     GridArgs g;
     const uint32_t* cell_start;  // ncells + 1

@@ -225,6 +225,9 @@ struct HostScene {
     // level), n_large of them
     double r_split = 0.0;
     int64_t n_large = 0;
+    // bodies per volume around a body, as a broad-phase run last counted
+    // them for a scene of two possible levels (< 0: not known for its bodies)
+    double density = -1.0;
 };
 
 struct KernelTimer {
@@ -805,6 +808,7 @@ struct World {
         on_device = true;
         need_rebuild = true;
         last_ent = last_pairs = -1;
+        for (HostScene& S : scenes) S.density = -1.0;
         invalidate_graphs();
     }
 
@@ -913,7 +917,7 @@ struct World {
         }
         // grid per scene
         h_read.ensure(std::max(sizeof(double) * 6 * (size_t)nsc, sizeof(uint32_t) * 4));
-        const double* bnd = h_read.as<double>();
+        std::vector<double> bnd(6 * (size_t)nsc, 0.0);
         // bounds: the grid of an aperiodic scene; in both cases the check
         // that no position went non-finite before it is binned
         if (nslots > 0) {
@@ -922,16 +926,17 @@ struct World {
             launch_bounds(bs[active].view(), nslots, nsc, d_bounds.as<double>(), d_bpart.p, stream);
             HIPC(hipGetLastError());
             fetch_and_wait({{d_bounds.p, h_read.p, sizeof(double) * 6 * nsc}});
+            std::memcpy(bnd.data(), h_read.p, sizeof(double) * bnd.size());
             for (int s = 0; s < nsc; ++s)
                 if (scenes[s].n_spheres > 0)
                     for (int k = 0; k < 6; ++k)
                         if (!std::isfinite(bnd[6 * s + k])) fail(DEM_ENONFINITE, "non-finite sphere position");
         }
-        std::vector<double> bnd_none;
-        if (nslots == 0) {
-            bnd_none.assign(6 * (size_t)nsc, 0.0);
-            bnd = bnd_none.data();
-        }
+        // the scenes' grids; true when the levels of some scene were chosen
+        // without knowing how crowded its bodies are (see below)
+        int64_t nlarge = 0;
+        auto lay_grids = [&]() -> bool {
+        bool guessed = false;
         for (int s = 0; s < nsc; ++s) {
             SceneParams& P = sp[s];
             const double dl2 = 2.0 * P.verlet;
@@ -1013,46 +1018,79 @@ struct World {
             // Two levels only where they are estimated to save work, in tests
             // of one sphere against another: a group of three neighbour cells
             // costs about four tests (its two dependent range reads), a cell
-            // holds its volume times the mean density, and a sphere of level 1
-            // takes a wave of 64 lanes for at least six tests' time.  A loose
-            // column of radii 0.5 to 1.5 mm, three quarters of which fall on
-            // level 1, is searched faster on one level (200,000 spheres,
+            // holds its volume times the density of bodies, and a sphere of
+            // level 1 takes a wave of 64 lanes for at least six tests' time.  A
+            // loose column of radii 0.5 to 1.5 mm, three quarters of which fall
+            // on level 1, is searched faster on one level (200,000 spheres,
             // 1,000 steps with about 10 runs: 33.2 ms on two levels, 25.3 on
             // one); 8 M dense spheres of 0.5 and 2 mm would test 18 times as
             // many pairs on one.
+            // The density is that around a body, as a run last counted it
+            // (k_crowd): that of the bounding box falls without limit when one
+            // sphere leaves an open bed.  The first run on new bodies takes the
+            // box's where it is enough for two levels; else it bins them on two
+            // levels, counts, and chooses again.
             if (rs > 0.0) {
-                double vol = 1.0;
-                if (periodic) {
-                    const double* H = P.H;
-                    vol = std::fabs(H[0] * (H[4] * H[8] - H[5] * H[7]) - H[1] * (H[3] * H[8] - H[5] * H[6]) +
-                                    H[2] * (H[3] * H[7] - H[4] * H[6]));
-                } else {
-                    for (int k = 0; k < 3; ++k) vol *= std::max(bnd[6 * s + 3 + k] - bnd[6 * s + k], hmax);
-                }
-                const double n = (double)scenes[s].n_spheres, nl = (double)scenes[s].n_large;
-                const double h0 = 2.0 * rs + dl2, group = 4.0;
-                const double fine = h0 * h0 * h0 * n / vol, coarse = hmax * hmax * hmax * nl / vol;
-                const double plain = 9.0 * group + 27.0 * hmax * hmax * hmax * n / vol;
-                const double w = 2.0 * std::ceil((rmax[s] + rs + dl2) / h0) + 1.0;
-                const double on0 = 18.0 * group + 27.0 * (fine + coarse);
-                const double on1 = std::max(64.0 * 6.0, w * w * std::ceil(w / 3.0) * group + 9.0 * group +
-                                                            w * w * w * fine + 27.0 * coarse);
-                if (n * plain <= (n - nl) * on0 + nl * on1) rs = 0.0;
-            }
-            if (rs > 0.0) {
-                // level 0 (radii <= r_split) and level 1 (the others)
+                // level 0 (radii <= r_split), level 1 (the others), and the one
+                // level of the plain cell
+                struct Level {
+                    int32_t dims[3];
+                    double inv_h[3], origin[3], cellw[3];
+                    double volume() const { return cellw[0] * cellw[1] * cellw[2]; }
+                } l0, l1, one;
                 const double h0 = (2.0 * rs + dl2) * (1.0 + 1e-9);
-                bool ok;
+                bool ok = true;  // else the cell is too small for the fine level: one level
                 if (periodic) {
-                    ok = periodic_level(h0, (rmax[s] + rs) + dl2, scenes[s].n_spheres, P.dims, P.inv_h, P.origin, P.cellw) &&
-                         periodic_level(hmax, 2.0 * rmax[s] + dl2, scenes[s].n_large, P.dims2, P.inv_h2, P.origin2,
-                                        P.cellw2);
+                    ok = periodic_level(h0, (rmax[s] + rs) + dl2, scenes[s].n_spheres, l0.dims, l0.inv_h, l0.origin,
+                                        l0.cellw) &&
+                         periodic_level(hmax, 2.0 * rmax[s] + dl2, scenes[s].n_large, l1.dims, l1.inv_h, l1.origin,
+                                        l1.cellw) &&
+                         periodic_level(hmax, 2.0 * rmax[s] + dl2, scenes[s].n_spheres, one.dims, one.inv_h,
+                                        one.origin, one.cellw);
                 } else {
-                    box_level(h0, scenes[s].n_spheres - scenes[s].n_large, P.dims, P.inv_h, P.origin, P.cellw);
-                    box_level(hmax, scenes[s].n_large, P.dims2, P.inv_h2, P.origin2, P.cellw2);
-                    ok = true;
+                    box_level(h0, scenes[s].n_spheres - scenes[s].n_large, l0.dims, l0.inv_h, l0.origin, l0.cellw);
+                    box_level(hmax, scenes[s].n_large, l1.dims, l1.inv_h, l1.origin, l1.cellw);
+                    box_level(hmax, scenes[s].n_spheres, one.dims, one.inv_h, one.origin, one.cellw);
                 }
-                if (!ok) rs = 0.0;  // the cell is too small for the fine level: one level
+                if (ok) {
+                    const double n = (double)scenes[s].n_spheres, nl = (double)scenes[s].n_large, group = 4.0;
+                    auto saves = [&](double density) {
+                        const double fine = l0.volume() * density, coarse = l1.volume() * density * nl / n;
+                        const double plain = 9.0 * group + 27.0 * one.volume() * density;
+                        double w[3];  // cells of level 0 that a sphere of level 1 searches
+                        for (int k = 0; k < 3; ++k)
+                            w[k] = 2.0 * std::ceil((rmax[s] + rs + dl2) / l0.cellw[k]) + 1.0;
+                        const double on0 = 18.0 * group + 27.0 * (fine + coarse);
+                        const double on1 = std::max(64.0 * 6.0, std::ceil(w[0] / 3.0) * w[1] * w[2] * group + 9.0 * group +
+                                                                    w[0] * w[1] * w[2] * fine + 27.0 * coarse);
+                        return n * plain > (n - nl) * on0 + nl * on1;
+                    };
+                    if (scenes[s].density >= 0.0) {
+                        ok = saves(scenes[s].density);
+                    } else {
+                        double vol = 1.0;
+                        if (periodic) {
+                            const double* H = P.H;
+                            vol = std::fabs(H[0] * (H[4] * H[8] - H[5] * H[7]) - H[1] * (H[3] * H[8] - H[5] * H[6]) +
+                                            H[2] * (H[3] * H[7] - H[4] * H[6]));
+                        } else {
+                            for (int k = 0; k < 3; ++k) vol *= std::max(bnd[6 * s + 3 + k] - bnd[6 * s + k], hmax);
+                        }
+                        if (!saves(n / vol)) guessed = true;
+                    }
+                }
+                if (!ok) rs = 0.0;
+                if (rs > 0.0)
+                    for (int k = 0; k < 3; ++k) {
+                        P.dims[k] = l0.dims[k];
+                        P.inv_h[k] = l0.inv_h[k];
+                        P.origin[k] = l0.origin[k];
+                        P.cellw[k] = l0.cellw[k];
+                        P.dims2[k] = l1.dims[k];
+                        P.inv_h2[k] = l1.inv_h[k];
+                        P.origin2[k] = l1.origin[k];
+                        P.cellw2[k] = l1.cellw[k];
+                    }
             }
             if (rs == 0.0) {
                 if (periodic) {
@@ -1065,6 +1103,11 @@ struct World {
             P.r_split = rs;
             P.brick_bits = brick_bits(P.dims, periodic);
             P.brick_bits2 = brick_bits(P.dims2, periodic);
+            // the cubes that crowding is counted in: as large as the plain cell
+            // where the bricks allow
+            P.crowd_bits = 0;
+            while (P.crowd_bits < P.brick_bits && std::ldexp(std::min({P.cellw[0], P.cellw[1], P.cellw[2]}), P.crowd_bits) < hmax)
+                ++P.crowd_bits;
             // mean-field share of the Verlet budget (periodic)
             double lf = 0.0;
             for (int k = 0; k < 9; ++k) lf += P.L[k] * P.L[k];
@@ -1083,13 +1126,13 @@ struct World {
                 if (cells > 0x7ffffff0LL) fail(DEM_EINVAL, "broad-phase grid too large");
             }
         ncells = (int)std::max<int64_t>(cells, 1);
-        int64_t nlarge = 0;
+        nlarge = 0;
         for (int s = 0; s < nsc; ++s)
             if (sp[s].r_split > 0.0) nlarge += scenes[s].n_large;
-        if (nslots > 0)
-            push_scene_table_async();
-        else
-            push_scene_table();
+        return guessed;
+        };
+        bool guessed = lay_grids();
+        if (nslots == 0) push_scene_table();
 
         Counters& C = *h_ctr;
         int npairs_new = 0;
@@ -1097,45 +1140,87 @@ struct World {
         if (nslots > 0) {
             const int ng = (int)bodies.size();
             const bool f32 = precision == DEM_FP32_MIXED;
+            // what the run reads back besides its flags: entries, pairs, and the
+            // crowding of each scene that may take two levels
+            d_total.ensure(8 + 8 * (size_t)nsc);
+            uint32_t* const d_nent = d_total.as<uint32_t>();
+            uint32_t* const d_np = d_nent + 1;
+            unsigned long long* const d_crowd = reinterpret_cast<unsigned long long*>(d_nent + 2);
+            uint32_t* const h_n = h_read.as<uint32_t>();  // entries, pairs
+            const unsigned long long* const h_crowd = reinterpret_cast<const unsigned long long*>(h_n + 2);
+            // Between two runs no body moves much farther than Delta L, so every
+            // eighth run counts, and a run on bodies or a state not seen before.
+            bool crowds = false;
+            for (const HostScene& S : scenes)
+                crowds = crowds || (S.r_split > 0.0 && (S.density < 0.0 || state_set || rebuilds % 8 == 0));
+            auto take_density = [&] {
+                for (int s = 0; s < nsc; ++s) {
+                    HostScene& S = scenes[s];
+                    if (!(S.r_split > 0.0)) continue;
+                    const SceneParams& P = sp[s];
+                    const double cells = std::ldexp(1.0, 3 * P.crowd_bits);
+                    const double side = std::ldexp(std::min({P.cellw[0], P.cellw[1], P.cellw[2]}), P.crowd_bits);
+                    // without the body itself, which says nothing where few are
+                    // near; in cubes too small to hold its neighbours, with it
+                    const double self = side >= 2.0 * P.rmax ? 1.0 : 0.0;
+                    const double mean = (double)h_crowd[s] / (double)S.n_spheres;
+                    S.density = std::max(mean - self, 0.0) / (cells * P.cellw[0] * P.cellw[1] * P.cellw[2]);
+                }
+            };
             GridArgs g;
-            g.bod = bs[active].view();
-            g.scenes = d_scenes.as<SceneParams>();
-            g.scene0 = sp[0];
-            g.nscenes = nsc;
-            g.nslots = nslots;
-            d_flag.ensure(4);
-            g.period_range = d_flag.as<int32_t>();
-            g.large_slot = nullptr;
-            // the bodies into cell order, in the other body set
             CellSortArgs cs{};
-            cell_count.ensure(4 * (size_t)ncells);
-            cell_start.ensure(4 * ((size_t)ncells + 1));
-            for (DBuf* d : {&body_cell, &body_arrival, &bucket}) d->ensure(4 * (size_t)nslots);
-            if (nlarge > 0) {
-                body_cell1.ensure(4 * (size_t)nslots);
-                body_arrival1.ensure(4 * (size_t)nslots);
-                large_slot.ensure(4 * (size_t)nlarge);
-            }
-            cs.count = cell_count.as<uint32_t>();
-            cs.start = cell_start.as<uint32_t>();
-            cs.cell = body_cell.as<uint32_t>();
-            cs.arrival = body_arrival.as<uint32_t>();
-            cs.cell1 = body_cell1.as<uint32_t>();
-            cs.arrival1 = body_arrival1.as<uint32_t>();
-            cs.bucket = bucket.as<uint32_t>();
-            cs.large_slot = large_slot.as<uint32_t>();
-            cs.ncells = ncells;
-            cs.nlarge = (int)nlarge;
-            scan_tmp.ensure(scan_temp_bytes(std::max(ncells, nslots)));
-            if (periodic) HIPC(hipMemsetAsync(d_flag.p, 0, 4, stream));
-            launch_cell_count(g, cs, periodic, stream);
-            if (periodic) {
-                int32_t* far = h_read.as<int32_t>();
-                HIPC(hipMemcpyAsync(far, d_flag.p, 4, hipMemcpyDeviceToHost, stream));
+            for (;;) {
+                push_scene_table_async();
+                g.bod = bs[active].view();
+                g.scenes = d_scenes.as<SceneParams>();
+                g.scene0 = sp[0];
+                g.nscenes = nsc;
+                g.nslots = nslots;
+                d_flag.ensure(4);
+                g.period_range = d_flag.as<int32_t>();
+                g.large_slot = nullptr;
+                // the bodies into cell order, in the other body set
+                cell_count.ensure(4 * (size_t)ncells);
+                cell_start.ensure(4 * ((size_t)ncells + 1));
+                for (DBuf* d : {&body_cell, &body_arrival, &bucket}) d->ensure(4 * (size_t)nslots);
+                if (nlarge > 0) {
+                    body_cell1.ensure(4 * (size_t)nslots);
+                    body_arrival1.ensure(4 * (size_t)nslots);
+                    large_slot.ensure(4 * (size_t)nlarge);
+                }
+                cs.count = cell_count.as<uint32_t>();
+                cs.start = cell_start.as<uint32_t>();
+                cs.cell = body_cell.as<uint32_t>();
+                cs.arrival = body_arrival.as<uint32_t>();
+                cs.cell1 = body_cell1.as<uint32_t>();
+                cs.arrival1 = body_arrival1.as<uint32_t>();
+                cs.bucket = bucket.as<uint32_t>();
+                cs.large_slot = large_slot.as<uint32_t>();
+                cs.ncells = ncells;
+                cs.nlarge = (int)nlarge;
+                scan_tmp.ensure(scan_temp_bytes(std::max(ncells, nslots)));
+                if (periodic) HIPC(hipMemsetAsync(d_flag.p, 0, 4, stream));
+                launch_cell_count(g, cs, periodic, scan_tmp.p, stream);
+                if (periodic) {
+                    int32_t* far = h_read.as<int32_t>();
+                    HIPC(hipMemcpyAsync(far, d_flag.p, 4, hipMemcpyDeviceToHost, stream));
+                    HIPC(hipStreamSynchronize(stream));
+                    if (*far)
+                        fail(DEM_EPERIODIC, "a sphere is more than 511 periods from the periodic cell's origin; "
+                                            "bring the positions back into the cell (dem_set_state)");
+                }
+                if (crowds) {
+                    HIPC(hipMemsetAsync(d_crowd, 0, 8 * (size_t)nsc, stream));
+                    launch_crowd(g, cs, d_crowd, stream);
+                }
+                if (!guessed) break;
+                HIPC(hipMemcpyAsync(h_n, d_nent, 8 + 8 * (size_t)nsc, hipMemcpyDeviceToHost, stream));
                 HIPC(hipStreamSynchronize(stream));
-                if (*far)
-                    fail(DEM_EPERIODIC, "a sphere is more than 511 periods from the periodic cell's origin; "
-                                        "bring the positions back into the cell (dem_set_state)");
+                HIPC(hipGetLastError());
+                take_density();
+                const int64_t large_before = nlarge;
+                guessed = lay_grids();
+                if (nlarge == large_before) break;  // the guess holds
             }
             PairSet& NP = ps[1 - pactive];
             PairSet& OP = ps[pactive];
@@ -1143,7 +1228,7 @@ struct World {
             NP.own_count.ensure(4 * (size_t)std::max(ng, 1));
             pairs_stale = need_rebuild = true;  // until this run ends
             launch_cell_place(g, cs, bs[1 - active].view(), periodic, slot_of_id.as<int32_t>(),
-                              NP.own_begin.as<int32_t>(), NP.own_count.as<int32_t>(), scan_tmp.p, stream);
+                              NP.own_begin.as<int32_t>(), NP.own_count.as<int32_t>(), stream);
             active = 1 - active;
             g.bod = bs[active].view();
             if (nlarge > 0) g.large_slot = large_slot.as<uint32_t>();
@@ -1158,10 +1243,6 @@ struct World {
             sw.count = counts.as<uint32_t>();
             sw.row_start = row_start.as<int32_t>();
             launch_sweep_count(sw, stream);
-            d_total.ensure(16);
-            uint32_t* const d_nent = d_total.as<uint32_t>();
-            uint32_t* const d_np = d_nent + 1;
-            uint32_t* const h_n = h_read.as<uint32_t>();  // entries, pairs
             exclusive_scan_u32(counts.as<uint32_t>(), row_start.as<uint32_t>(), nslots, nullptr, scan_tmp.p, d_nent,
                                stream);
             // What follows is sized either by the counts, read back one after
@@ -1201,7 +1282,7 @@ struct World {
                 exclusive_scan_u32(ent_own.as<uint32_t>(), own_scan.as<uint32_t>(), (int)lim_ent, d_nent, scan_tmp.p,
                                    d_np, stream);
                 if (!guess) {
-                    HIPC(hipMemcpyAsync(h_n + 1, d_np, 4, hipMemcpyDeviceToHost, stream));
+                    HIPC(hipMemcpyAsync(h_n + 1, d_np, crowds ? 4 + 8 * (size_t)nsc : 4, hipMemcpyDeviceToHost, stream));
                     HIPC(hipStreamSynchronize(stream));
                     HIPC(hipGetLastError());
                     if (h_n[1] >= kPairMask) fail(DEM_ENOMEM, "too many candidate pairs");
@@ -1248,7 +1329,7 @@ struct World {
                 // the slots' read-back (fold_slots) is waited for with the counts
                 h_slots_c.ensure(sizeof(ContactAcc) * (size_t)std::max(acc_c_n, 1));
                 h_slots_i.ensure(sizeof(IntAcc) * (size_t)std::max(acc_i_n, 1));
-                fetch_and_wait({{d_nent, h_n, 8},
+                fetch_and_wait({{d_nent, h_n, crowds ? 8 + 8 * (size_t)nsc : 8},
                                 {d_part_c.p, h_slots_c.p, sizeof(ContactAcc) * (size_t)acc_c_n},
                                 {d_part_i.p, h_slots_i.p, sizeof(IntAcc) * (size_t)acc_i_n}});
                 slots_fetched = true;
@@ -1261,6 +1342,7 @@ struct World {
             n_candidates = (int64_t)np;
             last_ent = h_n[0];
             last_pairs = (int64_t)np;
+            if (crowds) take_density();
             NP.cap = std::max<size_t>(np, 1);
             pactive = 1 - pactive;
             old_ngids = ng;
