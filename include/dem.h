@@ -148,7 +148,8 @@ typedef struct {
  * setting; only the per-block energy partial sums regroup). */
 typedef struct {
     int32_t block_contact;   /* threads per block of the contact kernel: 64..1024, multiple of 64
-                                (never changed from 256: fewer where a launch would leave CUs idle) */
+                                (never changed from 256 and not timed, ms_per_step = 0: fewer where a
+                                launch would leave CUs idle) */
     int32_t block_integrate; /* same for the integrate kernel */
     int32_t chunk;           /* steps per captured HIP graph: even, 2..4096 */
     int32_t pad;

@@ -328,7 +328,7 @@ struct World {
     DBuf d_acct;
     int64_t n_candidates = 0;
     int block_contact = 256, block_integrate = 256;  // as tuned
-    bool blocks_tuned[2] = {false, false};           // set to another value than the default once
+    bool blocks_tuned[2] = {false, false};           // set to another value than the default once, or timed
     int block_c = 256, block_i = 256;                // in use (launch_block)
     int chunk = 32;
     double tuned_ms = 0.0;             // ms per step measured by the autotuner
@@ -1585,8 +1585,10 @@ struct World {
         if (t.chunk < 2 || t.chunk > 4096 || t.chunk % 2) fail(DEM_EINVAL, "tuning: chunk must be even, 2..4096");
         if (!(t.verlet_factor >= 0.0) || !(t.verlet_factor <= 4.0))
             fail(DEM_EINVAL, "tuning: verlet_factor must be in [0, 4] (0 keeps each scene's own verlet_dist)");
-        blocks_tuned[0] = blocks_tuned[0] || t.block_contact != block_contact;
-        blocks_tuned[1] = blocks_tuned[1] || t.block_integrate != block_integrate;
+        // a setting that the autotuner timed runs as it was timed
+        const bool timed = t.ms_per_step > 0.0;
+        blocks_tuned[0] = blocks_tuned[0] || timed || t.block_contact != block_contact;
+        blocks_tuned[1] = blocks_tuned[1] || timed || t.block_integrate != block_integrate;
         block_contact = t.block_contact;
         block_integrate = t.block_integrate;
         chunk = t.chunk;
