@@ -148,20 +148,22 @@ struct PairSet {
     DBuf hpid, hcell, hmap;                     // canonical (owner-sorted) order, for the next run's lookup
     DBuf own_begin, own_count;  // by gid, into the canonical order
     size_t cap = 0;
-    void ensure(size_t n, bool fp32)
+    static size_t record_bytes(bool fp32) { return kForceWords * (fp32 ? sizeof(float) : sizeof(double)); }
+    // records: force records too (uses_force_records)
+    void ensure(size_t n, bool fp32, bool records)
     {
         n = std::max<size_t>(n, 1);
         for (DBuf* d : {&a, &b, &cell, &pid, &ea, &eb, &hpid, &hcell, &hmap}) d->ensure(n * 4);
         real.ensure(n);
         hist.ensure(n * hist_bytes(fp32 ? DEM_FP32_MIXED : DEM_FP64));
-        frec.ensure(n * kForceWords * (fp32 ? sizeof(float) : sizeof(double)));
+        if (records) frec.ensure(n * record_bytes(fp32));
         cap = n;
     }
     // pairs its buffers hold
-    size_t room(bool fp32) const
+    size_t room(bool fp32, bool records) const
     {
-        size_t n = std::min({real.bytes, hist.bytes / hist_bytes(fp32 ? DEM_FP32_MIXED : DEM_FP64),
-                             frec.bytes / (kForceWords * (fp32 ? sizeof(float) : sizeof(double)))});
+        size_t n = std::min(real.bytes, hist.bytes / hist_bytes(fp32 ? DEM_FP32_MIXED : DEM_FP64));
+        if (records) n = std::min(n, frec.bytes / record_bytes(fp32));
         for (const DBuf* d : {&a, &b, &cell, &pid, &ea, &eb, &hpid, &hcell, &hmap}) n = std::min(n, d->bytes / 4);
         return n;
     }
@@ -494,6 +496,10 @@ struct World {
     {
         if (!(tc > 0.0) || !std::isfinite(tc) || !(en > 0.0 && en <= 1.0) || !(et > 0.0 && et <= 1.0))
             fail(DEM_EINVAL, "dem_add_viscel_material: need tc > 0 and restitution coefficients in (0, 1]");
+        // the next step writes force records: the pair lists get theirs
+        if (!has_viscel())
+            for (PairSet& P : ps)
+                if (P.cap > 0) P.frec.ensure(P.cap * PairSet::record_bytes(precision == DEM_FP32_MIXED));
         const int id = add_material(density, 1e9, 0.25, friction);
         mats[id].kind = 1;
         mats[id].tc = tc;
@@ -888,7 +894,7 @@ struct World {
     }
     int64_t pair_room(bool f32) const
     {
-        size_t n = ps[1 - pactive].room(f32);
+        size_t n = ps[1 - pactive].room(f32, uses_force_records(has_viscel()));
         for (const DBuf* d : {&pb_ca, &pb_cb, &pb_found, &pb_flag, &pb_scan}) n = std::min(n, d->bytes / 4);
         return (int64_t)std::min<size_t>(n, kPairMask - 1) - 1;
     }
@@ -1287,7 +1293,7 @@ struct World {
                     HIPC(hipGetLastError());
                     if (h_n[1] >= kPairMask) fail(DEM_ENOMEM, "too many candidate pairs");
                     lim_pairs = h_n[1];
-                    NP.ensure((size_t)lim_pairs, f32);
+                    NP.ensure((size_t)lim_pairs, f32, uses_force_records(has_viscel()));
                     for (DBuf* d : {&pb_ca, &pb_cb, &pb_found, &pb_flag, &pb_scan})
                         d->ensure(4 * ((size_t)lim_pairs + 1));
                 }
@@ -1351,7 +1357,7 @@ struct World {
             // run (which fills it) allocates nothing.  A buffer it outgrows
             // is freed by hipFree, which waits for the device first.
             PairSet& spare = ps[1 - pactive];
-            spare.ensure(np + np / 8 + 1024, f32);
+            spare.ensure(np + np / 8 + 1024, f32, uses_force_records(has_viscel()));
             spare.own_begin.ensure(4 * (size_t)std::max(ng, 1));
             spare.own_count.ensure(4 * (size_t)std::max(ng, 1));
         } else {
@@ -2890,7 +2896,7 @@ struct World {
         }
         const size_t m = recs.size();
         PairSet& P = ps[pactive];
-        P.ensure(std::max<size_t>(m, (size_t)npairs), precision == DEM_FP32_MIXED);
+        P.ensure(std::max<size_t>(m, (size_t)npairs), precision == DEM_FP32_MIXED, uses_force_records(has_viscel()));
         P.own_begin.ensure(4 * (size_t)std::max(ng, 1));
         P.own_count.ensure(4 * (size_t)std::max(ng, 1));
         std::vector<int32_t> pid(m), cell(m);

@@ -91,3 +91,28 @@ def test_viscoelastic_forces_through_a_run(precision):
     assert np.abs(stress - before["stress"]).max() <= 1e-12 * f * 3e-3 / VOLUME
     assert np.array_equal(s.get_state()["force"][3:-1], before["force"])
     s.close()
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_only_the_viscoelastic_law_keeps_records(precision):
+    """48 (FP32-mixed: 24) bytes per pair of each list."""
+    import torch
+    from paper_2301_00611_amd import dem
+    n = 100_000
+    i = np.arange(n)
+    x = (np.stack([i % 47, i // 47 % 47, i // 47 ** 2], 1) + 0.5) * 2.001e-3
+    used = []
+    for law in (0, 1, 0):  # (the first warms the device up)
+        s = dem.Scene(gravity=(0, 0, -9.81), precision=precision)
+        m = s.add_viscel_material(2600.0, 2e-4, 0.6, 0.7, 0.5) if law else s.add_material(2600.0, 1e7, 0.3, 0.5)
+        s.add_spheres(x, np.full(n, 1e-3), default_mat=m)
+        s.set_dt(1e-6)
+        free = torch.cuda.mem_get_info()[0]
+        s.step(2)
+        s.set_state(pos=x)
+        s.step(2)
+        pairs = s.stats()["n_candidates"]
+        used.append(free - torch.cuda.mem_get_info()[0])
+        s.close()
+    assert pairs > 2 * n
+    assert used[1] - used[2] >= 2 * pairs * (48 if precision == 0 else 24)
