@@ -493,7 +493,7 @@ __device__ inline gptr<T> glb(T* p)
 
 // prim.hip
 // out[0 .. n] = exclusive scan of in[0 .. n), out[n] the total (also into
-// *total_dev when given), n = n_max, or *n_dev when given (a count above
+// *total_dev when given, 2^32 - 1 for any that is larger), n = n_max, or *n_dev when given (a count above
 // n_max scans nothing: the run is abandoned).  in != out; both 16-byte
 // aligned; temp holds scan_temp_bytes(n_max).
 size_t scan_temp_bytes(int n);

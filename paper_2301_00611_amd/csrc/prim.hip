@@ -16,13 +16,17 @@ constexpr int kItems = 8;             // consecutive elements per thread
 constexpr int kTile = kBlock * kItems;
 constexpr int kOneBlock = 2 * kTopBlock * kItems;
 
+// Sums saturate, so that a total past 2^32 - 1 is not taken for a small one:
+// the caller abandons the run then, and the places scanned are not used.
+__device__ inline uint32_t sat_add(uint32_t a, uint32_t b) { return __builtin_elementwise_add_sat(a, b); }
+
 __device__ inline uint32_t wave_inclusive_scan(uint32_t v)
 {
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
         uint32_t y = __shfl_up(v, off, 64);
-        if (lane >= off) v += y;
+        if (lane >= off) v = sat_add(v, y);
     }
     return v;
 }
@@ -41,8 +45,8 @@ __device__ inline uint32_t block_exclusive_scan(uint32_t v, uint32_t* total)
 #pragma unroll
     for (int w = 0; w < BLOCK / 64; ++w) {
         uint32_t t = wave_tot[w];
-        if (w < wave) before += t;
-        all += t;
+        if (w < wave) before = sat_add(before, t);
+        all = sat_add(all, t);
     }
     __syncthreads();
     *total = all;
@@ -77,7 +81,7 @@ __device__ inline uint32_t load_items(const uint32_t* __restrict__ in, long i, i
     }
     uint32_t s = 0;
 #pragma unroll
-    for (int k = 0; k < kItems; ++k) s += v[k];
+    for (int k = 0; k < kItems; ++k) s = sat_add(s, v[k]);
     return s;
 }
 
@@ -114,7 +118,7 @@ __global__ void __launch_bounds__(kTopBlock) k_scan_one(const uint32_t* __restri
         const uint32_t s = load_items(in, i, n, v);
         const uint32_t ex = block_exclusive_scan<kTopBlock>(s, &tot);
         store_items(out, i, n, carry + ex, v);
-        carry += tot;
+        carry = sat_add(carry, tot);
     }
     if (threadIdx.x == 0) {
         if (n == 0) out[0] = 0u;
@@ -145,7 +149,7 @@ __global__ void __launch_bounds__(kTopBlock) k_scan_top(uint32_t* __restrict__ s
         uint32_t tot;
         const uint32_t ex = block_exclusive_scan<kTopBlock>(v, &tot);
         if (i < nsums) sums[i] = carry + ex;
-        carry += tot;
+        carry = sat_add(carry, tot);
     }
     if (threadIdx.x == 0) {
         if (scan_length(n_max, n_dev) == 0) out[0] = 0u;

@@ -12,10 +12,10 @@ def _lattice(n):
     return (np.stack([i % k, i // k % k, i // k ** 2], 1) + 0.5) * 1.99e-3
 
 
-@pytest.mark.parametrize("n", [50_000])
+@pytest.mark.parametrize("n", [50_000, 70_000])
 def test_too_many_candidates(n):
     """Every sphere beside every other: n^2 row entries, more than an index
-    holds."""
+    holds, and at 70,000 more than 32 bits count."""
     from paper_2301_00611_amd import dem
     x = _lattice(n)
     s, twin = dem.Scene(gravity=(0, 0, -9.81)), dem.Scene(gravity=(0, 0, -9.81))
