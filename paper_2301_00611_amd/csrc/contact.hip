@@ -3,9 +3,9 @@
 // (class ScGeom; section 2.1.3), Ip2_FrictMat_FrictMat_FrictPhys (section
 // 2.1.2) and Law2_ScGeom_FrictPhys_CundallStrack (section 2.1.4), and writes
 // the pair's history record (shear force, normal, overlap, normal force),
-// plus a force record (force on #2, n x F) in FP32-mixed mode and under the
-// visco-elastic law.  No sum happens here: each body adds its pairs' forces
-// later, in a fixed order (integrate.hip).
+// plus a force record (force on #2, n x F) under the visco-elastic law.  No
+// sum happens here: each body adds its pairs' forces later, in a fixed order
+// (integrate.hip).
 //
 // FP64 mode computes everything in double.  FP32-mixed mode keeps the
 // contact test, the branch length and the overlap in double (they are

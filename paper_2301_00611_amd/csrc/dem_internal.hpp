@@ -222,9 +222,10 @@ __device__ inline double sphere_mass(double r, double rho)
 // A pair's history record (64 bytes, one aligned segment): the shear force
 // on #2 after the Coulomb cap, the normal, the overlap and the normal force
 // of its last evaluation; a zero normal marks a pair that did not touch.
-// Under the linear law in FP64 the record is also the pair's force record:
-// the force on #2 is fn n + Fs and its torque term n x (fn n + Fs), so no
-// separate force record is written (one 64-byte segment per gather).
+// Under the linear law the record (in FP32-mixed the one below) is also the
+// pair's force record: the force on #2 is fn n + Fs and its torque term
+// n x (fn n + Fs), so no separate force record is written or allocated (one
+// 64-byte segment per gather).
 struct HistRec {
     double fsx, fsy, fsz;     // shear force (the spring's part under the visco-elastic law)
     double pen;               // overlap of the last evaluation
@@ -286,9 +287,9 @@ constexpr int kForceWords = 6;
 
 // Where the integrate kernel takes a pair's force from: the history record
 // itself (linear law), or a force record (visco-elastic law: its shear dashpot
-// is not in the history).  Reports take it from where the last step put it.  FP32-mixed had force records under
-// both laws: 24 bytes are less to gather than the 48 of the history, but they
-// are written beside it every step.  us per step with them / without: 1 M
+// is not in the history).  Reports take it from where the last step put it.
+// FP32-mixed had force records under both laws: 24 bytes are less to gather
+// than the 48 of the history, but they are written beside it every step.  us per step with them / without: 1 M
 // spheres in shear 282 / 257 (contact 162 / 134, integrate 117 / 117), 780,000
 // 221 / 207, 200,000 46.2 / 46.4; scenes with few contacts the same.
 inline bool uses_force_records(bool viscel) { return viscel; }

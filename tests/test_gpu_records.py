@@ -48,7 +48,7 @@ def _consistent(s, precision):
     want = np.zeros_like(st["force"])
     np.add.at(want, c["id2"], c["fn"] + c["fs"])
     np.add.at(want, c["id1"], -(c["fn"] + c["fs"]))
-    # the records hold FP64 (or FP32) sums of what the contact list holds apart
+    # FP64 (or FP32) sums of what the contact list holds apart
     scale = np.linalg.norm(c["fn"] + c["fs"], axis=1).max()
     assert np.abs(st["force"] - want).max() <= (1e-12 if precision == 0 else 1e-5) * scale
 
@@ -57,6 +57,7 @@ def _consistent(s, precision):
 def test_material_of_the_other_law_added_between_steps(precision):
     s = _scene(0, precision)
     s.step(60)
+    _consistent(s, precision)
     before = _reports(s)
     s.add_viscel_material(2600.0, 2e-4, 0.6, 0.7, 0.5)  # no body's
     _same(before, _reports(s))
