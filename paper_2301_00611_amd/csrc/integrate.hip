@@ -15,6 +15,7 @@
 #include "dem_internal.hpp"
 
 #include <algorithm>
+#include <cstddef>
 #include <type_traits>
 
 namespace dem {
@@ -952,14 +953,19 @@ __global__ void __launch_bounds__(64) k_report(const StepArgs* __restrict__ args
     const uint32_t seq = ctr->reports + 1u;
     Report& r = ring[seq % kReports];
     constexpr int kWords = sizeof(Counters) / 4;
-    if (threadIdx.x < kWords)
-        reinterpret_cast<uint32_t*>(&r.c)[threadIdx.x] = reinterpret_cast<const uint32_t*>(ctr)[threadIdx.x];
+    uint32_t word = 0u;
+    if (threadIdx.x < kWords) {
+        word = reinterpret_cast<const uint32_t*>(ctr)[threadIdx.x];
+        reinterpret_cast<uint32_t*>(&r.c)[threadIdx.x] = word;
+    }
+    const bool failed = __any(word != 0u && (threadIdx.x == offsetof(Counters, nonfinite) / 4 ||
+                                             threadIdx.x == offsetof(Counters, unstable) / 4));
     __threadfence_system();
     __builtin_amdgcn_wave_barrier();
     if (threadIdx.x == 0) {
         ctr->reports = seq;
-        if (ctr->nonfinite || ctr->unstable) ctr->stall[last] = 1;
         __hip_atomic_store(&r.seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        if (failed) ctr->stall[last] = 1;
     }
 }
 
