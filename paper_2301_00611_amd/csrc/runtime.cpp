@@ -1863,6 +1863,9 @@ struct World {
         watch(h_report[kReports].seq, posts, true);
     }
 
+    // A scene at rest may go on for ever without a broad-phase run: its count
+    // of steps since the last starts again before it leaves 32 bits.
+    static constexpr int32_t kManySteps = 1 << 30;
     // One chain of steps on its way: its steps, and the parity after it.
     struct Chain {
         int n, parity;
@@ -1984,7 +1987,7 @@ struct World {
             return (int)std::min<int64_t>(remaining - ahead, near ? part : chunk);
         };
         auto follow = [&](int n) {
-            if (!use_graph || timing || next_parity != 0 || n < part) return false;
+            if (!use_graph || timing || next_parity != 0 || n < part || steps_seen >= kManySteps) return false;
             const int64_t since = scenes[0].iter - iter_at_rebuild;
             return n == part || 4 * (since + ahead + n) <= 3 * last_interval || since >= 4 * n;
         };
@@ -2000,7 +2003,7 @@ struct World {
                             add_time("rebuild", rb0, rb1);
                         }
                     }
-                    if (resync || h_ctr->iter0 + steps_seen != scenes[0].iter) {
+                    if (resync || steps_seen >= kManySteps || h_ctr->iter0 + steps_seen != scenes[0].iter) {
                         HIPC(hipMemcpyAsync(h_ctr, d_ctr.p, sizeof(Counters), hipMemcpyDeviceToHost, stream));
                         HIPC(hipStreamSynchronize(stream));
                         reports = h_ctr->reports;
